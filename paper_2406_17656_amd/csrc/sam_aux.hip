@@ -11,149 +11,227 @@ namespace samk {
 
 namespace {
 
-constexpr int kBmWords = 1024;
-constexpr int kBmBits = kBmWords * 32;
-constexpr int kAcc = 2048;  // residual entries held in LDS per pass
-
-__device__ inline int wmin(int v) {
-    for (int d = 32; d >= 1; d >>= 1) v = min(v, __shfl_xor(v, d));
-    return v;
-}
-__device__ inline int wmax(int v) {
-    for (int d = 32; d >= 1; d >>= 1) v = max(v, __shfl_xor(v, d));
-    return v;
-}
-__device__ inline int wsum(int v) {
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
-    return v;
-}
-__device__ inline int wscan_excl(int v) {
-    const int lane = wave_lane();
-    int x = v;
-    for (int d = 1; d < 64; d <<= 1) {
-        int y = __shfl_up(x, d);
-        if (lane >= d) x += y;
-    }
-    return x - v;
-}
-
 __device__ inline double mval(const void* M, int e, int f32) {
     return f32 ? (double)static_cast<const float*>(M)[e] : static_cast<const double*>(M)[e];
 }
 
-// One wave per column j.  The rows of column j of A_k M - A_0 are the union
-// U of rows(A_k(:, l)) for l in M(:, j) and rows(A_0(:, j)); U is built as a
-// bitmap over a window of rows, the rank of a row inside U indexes the LDS
-// accumulator, and contributions are added column by column of M (rows are
-// distinct inside one column, so no two lanes touch the same slot at once).
+// Eight (or 16) lanes per column j.  The rows of column j of
+// A_k M - A_0 are the union U of rows(A_k(:, l)) for l in M(:, j) and
+// rows(A_0(:, j)); U is built as a bitmap over a window of kResRows rows (the
+// sweep jumps to the next occupied window), the rank of a row inside U
+// indexes the LDS accumulator, and contributions are added column by column
+// of M, the lanes taking the entries of one A_k column at a time: rows are
+// distinct inside it, so the lanes of one instruction never share a slot and
+// every row's sum keeps the order of M's entries (A_0 last).
+//
+// Bound: the latency of the dependent loads (column of M, its extents in
+// A_k, the entries).  One wave per column, one A_k column after the other,
+// kept five of 64 lanes busy and paid every round trip in series: 2.76 ms for
+// the 512 x 512 level-2 map.  Eight problems per wave took it to 0.18 ms with
+// each pass over the entries (bitmap, accumulation) fetching them anew in
+// batches of eight; columns whose entries fit the registers fetch them once,
+// all loads independent: 0.11 ms (63 x 25 blocks of the 64^3 seven-point map:
+// 4.26 -> 1.07 ms).
+constexpr int kResWPL = 16;               // bitmap words per lane
+constexpr int kResAcc = 64;               // accumulators per column and pass
+constexpr int kResAccStride = 68;         // 8 banks apart: eight columns cover the 64 banks
+
+struct alignas(16) ResList {  // one column of M's pattern: its run in A_k and its value
+    int start, len;
+    double m;
+};
+
+// kResLanes lanes per column, kResBatch columns of M per problem held in
+// registers: 8 and 16, or 16 and 32.
+template <int kResLanes, int kResBatch>
 __global__ void __launch_bounds__(64)
 k_residual_columns(int n, const int* Ak_cp, const int* Ak_ri, const double* Ak_v, const int* A0_cp,
                    const int* A0_ri, const double* A0_v, const int* M_cp, const int* M_ri,
                    const void* M_v, int f32, double* col_out, unsigned long long* status) {
-    __shared__ unsigned bm[kBmWords];
-    __shared__ int wpre[kBmWords];
-    __shared__ double acc[kAcc];
+    constexpr int kResCols = 64 / kResLanes;              // columns per wave
+    constexpr int kResRows = kResWPL * kResLanes * 32;    // rows per window
+    // word w of a lane sits at w * 64 + lane: the passes over a lane's own
+    // words touch 64 consecutive words
+    __shared__ unsigned bm[kResWPL * 64];
+    __shared__ unsigned short pre[kResWPL * 64];
+    __shared__ double accs[kResCols * kResAccStride];
+    __shared__ ResList lists[kResCols][kResBatch];
     const int lane = wave_lane();
-    for (int j = blockIdx.x; j < n; j += gridDim.x) {
-        const int ma = M_cp[j], mb = M_cp[j + 1];
-        // window of rows
-        int mn = INT_MAX, mx = -1;
-        for (int t = ma + lane; t < mb; t += 64) {
-            const int l = M_ri[t];
-            if (l < 0 || l >= n) {
-                report(status, j, kStIndex);
-                continue;
-            }
-            const int qa = Ak_cp[l], qb = Ak_cp[l + 1];
-            if (qb > qa) {
-                mn = min(mn, Ak_ri[qa]);
-                mx = max(mx, Ak_ri[qb - 1]);
-            }
+    const int g = lane % kResLanes, q = lane / kResLanes;
+    double* acc = accs + q * kResAccStride;
+    const int own = q * kResLanes;        // this group's first lane
+    auto slot = [&](int wi) { return (wi % kResWPL) * 64 + own + wi / kResWPL; };
+    // contiguous ranges of columns per block, neighbouring ranges on one XCD
+    const int nb = gridDim.x;
+    const int lb = (nb & 7) ? (int)blockIdx.x : ((int)blockIdx.x & 7) * (nb >> 3) + ((int)blockIdx.x >> 3);
+    const int64_t ngroups = ((int64_t)n + kResCols - 1) / kResCols;
+    const int grp_lo = (int)(lb * ngroups / nb), grp_hi = (int)((lb + 1) * ngroups / nb);
+    for (int grp = grp_lo; grp < grp_hi; ++grp) {
+        const int64_t jj = (int64_t)grp * kResCols + q;
+        const bool valid = jj < n;
+        const int j = valid ? (int)jj : 0;
+        int ma = 0, mb = 0, aa = 0, ab = 0;
+        if (valid) {
+            ma = M_cp[j];
+            mb = M_cp[j + 1];
+            aa = A0_cp[j];
+            ab = A0_cp[j + 1];
         }
-        if (A0_cp[j + 1] > A0_cp[j]) {
-            mn = min(mn, A0_ri[A0_cp[j]]);
-            mx = max(mx, A0_ri[A0_cp[j + 1] - 1]);
-        }
-        const int lo = wmin(mn), hi = wmax(mx);
-        double colsum = 0.0;
-        for (int base = lo; base <= hi; base += kBmBits) {
-            const int nbits = min(kBmBits, hi - base + 1);
-            const int nw = (nbits + 31) >> 5;
-            for (int w = lane; w < nw; w += 64) bm[w] = 0u;
-            wave_sync();
-            for (int t = ma + lane; t < mb; t += 64) {
+        // the first kResBatch columns of M: their runs in A_k and their values
+#pragma unroll
+        for (int h = 0; h < kResBatch / kResLanes; ++h) {
+            ResList x{0, 0, 0.0};
+            const int t = ma + g + h * kResLanes;
+            if (t < mb) {
                 const int l = M_ri[t];
-                if (l < 0 || l >= n) continue;
-                for (int f = Ak_cp[l]; f < Ak_cp[l + 1]; ++f) {
-                    const int r = Ak_ri[f] - base;
-                    if (r >= 0 && r < kBmBits) atomicOr(&bm[r >> 5], 1u << (r & 31));
+                if (l < 0 || l >= n) {
+                    report(status, j, kStIndex);
+                } else {
+                    x.start = Ak_cp[l];
+                    x.len = Ak_cp[l + 1] - x.start;
+                    x.m = mval(M_v, t, f32);
                 }
             }
-            for (int e = A0_cp[j] + lane; e < A0_cp[j + 1]; e += 64) {
-                const int r = A0_ri[e] - base;
-                if (r >= 0 && r < kBmBits) atomicOr(&bm[r >> 5], 1u << (r & 31));
+            lists[q][g + h * kResLanes] = x;
+        }
+        wave_sync();
+        // wave-uniform: every column problem of the wave fits the registers
+        // (kResBatch columns of M, eight entries each and eight of A_0)
+        bool fits = mb - ma <= kResBatch && ab - aa <= kResLanes;
+#pragma unroll
+        for (int h = 0; h < kResBatch / kResLanes; ++h) fits &= lists[q][g + h * kResLanes].len <= kResLanes;
+        const bool fast = __ballot(!fits) == 0ull;
+        int rows[kResBatch + 1];              // -1: no entry
+        double vals[kResBatch + 1];           // entry times coefficient
+        int lo = INT_MAX;
+        if (fast) {
+#pragma unroll
+            for (int u = 0; u < kResBatch; ++u) {
+                const ResList y = lists[q][u];
+                rows[u] = -1;
+                vals[u] = 0.0;
+                if (g < y.len) {
+                    rows[u] = Ak_ri[y.start + g];
+                    vals[u] = Ak_v[y.start + g];
+                }
             }
-            wave_sync();
-            const int wpl = (nw + 63) >> 6;
-            const int w0 = lane * wpl;
-            int c = 0;
-            for (int w = w0; w < min(nw, w0 + wpl); ++w) c += __popc(bm[w]);
-            int run = wscan_excl(c);
-            for (int w = w0; w < min(nw, w0 + wpl); ++w) {
-                wpre[w] = run;
-                run += __popc(bm[w]);
+            rows[kResBatch] = -1;
+            vals[kResBatch] = 0.0;
+            if (aa + g < ab) {
+                rows[kResBatch] = A0_ri[aa + g];
+                vals[kResBatch] = -A0_v[aa + g];
             }
-            const int cnt = wsum(c);
+#pragma unroll
+            for (int u = 0; u < kResBatch; ++u) vals[u] *= lists[q][u].m;
+#pragma unroll
+            for (int u = 0; u <= kResBatch; ++u) lo = rows[u] >= 0 ? min(lo, rows[u]) : lo;
+        } else {   // the columns are ascending, so the smallest row heads one of them
+            for (int t = ma + g; t < mb; t += kResLanes) {
+                const int l = M_ri[t];
+                if (l < 0 || l >= n) {
+                    report(status, j, kStIndex);
+                    continue;
+                }
+                const int qa = Ak_cp[l];
+                if (Ak_cp[l + 1] > qa) lo = min(lo, Ak_ri[qa]);
+            }
+            if (ab > aa) lo = min(lo, A0_ri[aa]);
+        }
+        int base = grp_min<kResLanes>(lo);
+        double colsum = 0.0;
+        while (base != INT_MAX) {
+#pragma unroll
+            for (int w = 0; w < kResWPL; ++w) bm[w * 64 + lane] = 0u;
             wave_sync();
-            // accumulate in rank ranges of kAcc entries
-            for (int r0 = 0; r0 < cnt; r0 += kAcc) {
-                const int rn = min(kAcc, cnt - r0);
-                for (int i = lane; i < rn; i += 64) acc[i] = 0.0;
-                wave_sync();
+            // every entry of column j's problem in order: entry(row, product)
+            auto sweep = [&](bool values, auto entry) {
+                if (fast) {
+#pragma unroll
+                    for (int u = 0; u <= kResBatch; ++u)
+                        if (rows[u] >= 0) entry(rows[u], vals[u]);
+                    wave_sync();
+                    return;
+                }
                 for (int t = ma; t < mb; ++t) {
                     const int l = M_ri[t];
                     if (l < 0 || l >= n) continue;
-                    const double mlj = mval(M_v, t, f32);
-                    for (int f = Ak_cp[l] + lane; f < Ak_cp[l + 1]; f += 64) {
-                        const int r = Ak_ri[f] - base;
-                        if (r >= 0 && r < kBmBits) {
-                            const int w = r >> 5;
-                            const int rank = wpre[w] + __popc(bm[w] & ((1u << (r & 31)) - 1u)) - r0;
-                            if (rank >= 0 && rank < rn) acc[rank] += Ak_v[f] * mlj;
-                        }
-                    }
-                    wave_sync();
+                    const double m = values ? mval(M_v, t, f32) : 0.0;
+                    const int fb = Ak_cp[l + 1];
+                    for (int f = Ak_cp[l] + g; f < fb; f += kResLanes) entry(Ak_ri[f], values ? Ak_v[f] * m : 0.0);
                 }
-                for (int e = A0_cp[j] + lane; e < A0_cp[j + 1]; e += 64) {
-                    const int r = A0_ri[e] - base;
-                    if (r >= 0 && r < kBmBits) {
-                        const int w = r >> 5;
-                        const int rank = wpre[w] + __popc(bm[w] & ((1u << (r & 31)) - 1u)) - r0;
-                        if (rank >= 0 && rank < rn) acc[rank] -= A0_v[e];
-                    }
-                }
+                for (int e = aa + g; e < ab; e += kResLanes) entry(A0_ri[e], values ? -A0_v[e] : 0.0);
                 wave_sync();
-                double s = 0.0;
-                for (int i = lane; i < rn; i += 64) s += acc[i] * acc[i];
-                for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d);
-                colsum += s;
+            };
+            int next = INT_MAX;
+            sweep(false, [&](int r, double) {
+                const int d = r - base;
+                if (d >= kResRows) next = min(next, r);
+                else if (d >= 0) atomicOr(&bm[slot(d >> 5)], 1u << (d & 31));
+            });
+            int c = 0;
+#pragma unroll
+            for (int w = 0; w < kResWPL; ++w) c += __popc(bm[w * 64 + lane]);
+            int run = grp_excl_scan<kResLanes>(c);
+            const int cnt = grp_sum<kResLanes>(c);
+#pragma unroll
+            for (int w = 0; w < kResWPL; ++w) {
+                pre[w * 64 + lane] = (unsigned short)run;
+                run += __popc(bm[w * 64 + lane]);
+            }
+            wave_sync();
+            for (int r0 = 0; r0 < cnt; r0 += kResAcc) {   // rank ranges of kResAcc rows
+#pragma unroll
+                for (int i = 0; i < kResAcc / kResLanes; ++i) acc[i * kResLanes + g] = 0.0;
+                wave_sync();
+                sweep(true, [&](int r, double v) {
+                    const int d = r - base;
+                    if (d < 0 || d >= kResRows) return;
+                    const int p = slot(d >> 5);
+                    const int rank = pre[p] + __popc(bm[p] & ((1u << (d & 31)) - 1u)) - r0;
+                    if (rank >= 0 && rank < kResAcc)
+                        __hip_atomic_fetch_add(&acc[rank], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                });
+                double s = 0.0;   // slots past the last rank hold zeros
+#pragma unroll
+                for (int i = 0; i < kResAcc / kResLanes; ++i) {
+                    const double x = acc[i * kResLanes + g];
+                    s += x * x;
+                }
+                colsum += group_sum<kResLanes>(s);
                 wave_sync();
             }
+            base = grp_min<kResLanes>(next);
         }
-        if (lane == 0) col_out[j] = colsum;
+        if (valid && g == 0) col_out[j] = colsum;
     }
 }
 
 }  // namespace
 
-hipError_t residual_columns(int n, const int* Ak_cp, const int* Ak_ri, const double* Ak_v,
+hipError_t residual_columns(int n, int64_t nnzA, int64_t nnzM, const int* Ak_cp, const int* Ak_ri, const double* Ak_v,
                             const int* A0_cp, const int* A0_ri, const double* A0_v, const int* M_cp,
                             const int* M_ri, const void* M_v, int m_is_f32, double* col_out,
                             unsigned long long* status, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const int grid = std::min(n, 256 * 32);
-    hipLaunchKernelGGL(k_residual_columns, dim3(grid), dim3(64), 0, s, n, Ak_cp, Ak_ri, Ak_v, A0_cp,
-                       A0_ri, A0_v, M_cp, M_ri, M_v, m_is_f32, col_out, status);
+    // Eight lanes per column where most columns of A_k and A_0 have at most
+    // eight entries and those of M at most 16 (means of 7 and 14: stencil
+    // columns are the same length but for the boundary), else 16 lanes, which
+    // hold columns of 16 entries and 32 columns of M.  Narrow / wide, us:
+    // 512^2 level 1 91 / 354, level 2 113 / 407, level 3 713 / 497; 64^3
+    // level 1 238 / 674, level 2 2275 / 1090; 1024^2 nine-point level 2
+    // 4057 / 1962.
+    const bool narrow = nnzA <= (int64_t)7 * n && nnzM <= (int64_t)14 * n;
+    const int cols = narrow ? 8 : 4;
+    // up to 12 one-wave blocks per CU are resident; a multiple of 8 blocks, so
+    // that neighbouring ranges share an XCD
+    int grid = (int)std::min<int64_t>(((int64_t)n + cols - 1) / cols, 256 * 12);
+    if (grid >= 64) grid = grid / 8 * 8;
+    if (narrow)
+        hipLaunchKernelGGL((k_residual_columns<8, 16>), dim3(grid), dim3(64), 0, s, n, Ak_cp, Ak_ri, Ak_v, A0_cp,
+                           A0_ri, A0_v, M_cp, M_ri, M_v, m_is_f32, col_out, status);
+    else
+        hipLaunchKernelGGL((k_residual_columns<16, 32>), dim3(grid), dim3(64), 0, s, n, Ak_cp, Ak_ri, Ak_v, A0_cp,
+                           A0_ri, A0_v, M_cp, M_ri, M_v, m_is_f32, col_out, status);
     return hipGetLastError();
 }
 

@@ -938,7 +938,7 @@ sam_status sam_residual(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0, cons
         if (a02) HIP_TRY(ctx, samk::fill_i32((int*)a02, 2, 0, s));
         return SAM_OK;
     }
-    HIP_TRY(ctx, samk::residual_columns(n, Ak->colptr, Ak->rowind, Ak->val, A0->colptr, A0->rowind, A0->val, M_colptr,
+    HIP_TRY(ctx, samk::residual_columns(n, Ak->nnz, nnz_M, Ak->colptr, Ak->rowind, Ak->val, A0->colptr, A0->rowind, A0->val, M_colptr,
                                         M_rowind, M_val, prec == SAM_PREC_F32_REFINE, cols, ctx->d_status, s));
     HIP_TRY(ctx, samk::reduce_sum(cols, n, res2, rt, s));
     if (a02) HIP_TRY(ctx, samk::reduce_sumsq(A0->val, A0->nnz, a02, rt, s));

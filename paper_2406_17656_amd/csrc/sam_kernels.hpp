@@ -108,7 +108,8 @@ hipError_t reduce_sumsq(const double* x, int64_t n, double* out, void* temp, hip
 
 // -------------------------------------------------------------- residual
 // Per column: rho_j = ||A_k(:,J_j) m_j - A_0(:,j)||^2 computed explicitly.
-hipError_t residual_columns(int n, const int* Ak_cp, const int* Ak_ri, const double* Ak_v,
+// nnzA, nnzM: entries of A_k and M (they pick the kernel's form).
+hipError_t residual_columns(int n, int64_t nnzA, int64_t nnzM, const int* Ak_cp, const int* Ak_ri, const double* Ak_v,
                             const int* A0_cp, const int* A0_ri, const double* A0_v,
                             const int* M_cp, const int* M_ri, const void* M_v, int m_is_f32,
                             double* col_out, unsigned long long* status, hipStream_t s);

@@ -342,54 +342,6 @@ template <int GS>
 constexpr int chunk_words() { return GS == 16 ? 256 : 128; }
 constexpr int kSymThreads = 256;
 
-template <int CTRL>
-__device__ inline int dppi(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false); }
-template <int CTRL>
-__device__ inline int dppb(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
-
-// sums / minima / maxima over the GS lanes of a group (all lanes get the
-// result): quad exchanges, then the half-row mirror, then (GS = 16) the row
-// mirror
-template <int GS>
-__device__ inline int grp_sum(int v) {
-    v += dppb<0xB1>(v);
-    v += dppb<0x4E>(v);
-    v += dppb<0x141>(v);
-    if (GS == 16) v += dppb<0x140>(v);
-    return v;
-}
-template <int GS>
-__device__ inline int grp_min(int v) {
-    v = min(v, dppb<0xB1>(v));
-    v = min(v, dppb<0x4E>(v));
-    v = min(v, dppb<0x141>(v));
-    if (GS == 16) v = min(v, dppb<0x140>(v));
-    return v;
-}
-template <int GS>
-__device__ inline int grp_max(int v) {
-    v = max(v, dppb<0xB1>(v));
-    v = max(v, dppb<0x4E>(v));
-    v = max(v, dppb<0x141>(v));
-    if (GS == 16) v = max(v, dppb<0x140>(v));
-    return v;
-}
-// exclusive prefix sum inside the group (Kogge-Stone with row_shr; a lane
-// whose source lies before its group's first lane adds 0)
-template <int GS>
-__device__ inline int grp_excl_scan(int v) {
-    const int p = (int)(threadIdx.x & (GS - 1));
-    int x = v, y;
-    y = dppi<0x111>(x);
-    x += (GS == 16 || p >= 1) ? y : 0;
-    y = dppi<0x112>(x);
-    x += (GS == 16 || p >= 2) ? y : 0;
-    y = dppi<0x114>(x);
-    x += (GS == 16 || p >= 4) ? y : 0;
-    if (GS == 16) x += dppi<0x118>(x);
-    return x - v;
-}
-
 enum { kModeCount = 0, kModeFill = 1, kModePositions = 2 };
 
 // Bitmap word wi (rows 32 wi .. 32 wi + 31 of the chunk) belongs to lane
