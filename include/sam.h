@@ -383,6 +383,39 @@ sam_status sam_apply(sam_ctx* ctx, int32_t n, const int32_t* T_rowptr, const int
                      const int32_t* T_perm, const void* M_val, int32_t prec,
                      const double* x, double* y, sam_stream_t stream);
 
+/* ------------------------------------------------------------------ GMRES */
+
+#define SAM_GMRES_MAX_RESTART 512
+
+/* Bytes of the workspace of sam_gmres_steps (host output).  Errors:
+ * SAM_ERR_ARG (n < 1, restart outside [1, SAM_GMRES_MAX_RESTART]). */
+sam_status sam_gmres_workspace_size(int32_t n, int32_t restart, size_t* bytes);
+
+/* Steps first .. first + count - 1 of one cycle of right-preconditioned
+ * GMRES on A with the preconditioner N diag(d) (Section 1: the map N updates
+ * the preconditioner of the target; N_rowptr = NULL: diag(d) alone).  A and N
+ * are row views with their values in row order (sam_apply_prepare,
+ * sam_apply_permute; A's in double, N's per N_prec).  V ((restart + 1) n) holds
+ * the basis: the caller writes v_0 = r / ||r||; Z (restart n) receives
+ * N diag(d) v_k.  H ((restart + 1) restart, a column of restart + 1 per step)
+ * receives the rotated Hessenberg matrix (upper triangular).  beta = ||r||
+ * starts the right side (read when first = 0).  state (2 restart + 3
+ * doubles): [0] steps done, [1] nonzero once |residual| <= tol or the basis is
+ * exhausted (later steps then return without work), [2 + i] |residual| after
+ * step i, [2 + restart + i] the rotated right side.  ws must not change
+ * between the calls of a cycle.  Orthogonalisation: classical Gram-Schmidt,
+ * twice, every sum in a fixed order.  Asynchronous; allocates nothing. */
+sam_status sam_gmres_steps(sam_ctx* ctx, int32_t n, const int32_t* A_rowptr, const int32_t* A_colind,
+                           const double* A_val, const int32_t* N_rowptr, const int32_t* N_colind,
+                           const void* N_val, int32_t N_prec, const double* d, int32_t restart, int32_t first,
+                           int32_t count, double beta, double tol, double* V, double* Z, double* H,
+                           double* state, void* ws, size_t ws_bytes, sam_stream_t stream);
+
+/* x += sum_{i < used} y_i Z_i (the end of a cycle; y, Z, x on the device).
+ * Asynchronous; allocates nothing. */
+sam_status sam_gmres_solution(sam_ctx* ctx, int32_t n, int32_t used, const double* y, const double* Z,
+                              double* x, sam_stream_t stream);
+
 /* --------------------------------------------------------------- sequence */
 
 /* Bytes of sequence memory for sam_sequence_create with the same arguments

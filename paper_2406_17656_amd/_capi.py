@@ -30,6 +30,7 @@ STATUS_NAMES = {
 SAM_PREC_F64 = 0
 SAM_PREC_F32_REFINE = 1
 SAM_NO_DEVICE = -1
+SAM_GMRES_MAX_RESTART = 512
 SPARSIFY = {"none": 0, "global": 1, "column": 2, "lfil": 3}
 
 
@@ -83,6 +84,10 @@ SIGNATURES = {
     "sam_apply_prepare": (c_int32, [P, c_int32, P, P, c_int64, P, P, P, P, c_size_t, P]),
     "sam_apply": (c_int32, [P, c_int32, P, P, P, P, c_int32, P, P, P]),
     "sam_apply_permute": (c_int32, [P, c_int64, P, P, c_int32, P, P]),
+    "sam_gmres_workspace_size": (c_int32, [c_int32, c_int32, SZ]),
+    "sam_gmres_steps": (c_int32, [P, c_int32, P, P, P, P, P, P, c_int32, P, c_int32, c_int32, c_int32, c_double,
+                                  c_double, P, P, P, P, P, c_size_t, P]),
+    "sam_gmres_solution": (c_int32, [P, c_int32, c_int32, P, P, P, P]),
     "sam_sequence_size": (c_int32, [P, CSCP, CSCP, SPECP, c_int32, c_int32, c_int32, P, c_size_t, SZ, P]),
     "sam_sequence_create": (c_int32, [P, CSCP, CSCP, SPECP, c_int32, c_int32, c_int32, P, c_size_t,
                                       ctypes.POINTER(c_void_p), P]),

@@ -21,8 +21,9 @@ OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsam_mi355x.so")
 ARCH = "gfx950"
 
-SOURCES = ["sam_symbolic.hip", "sam_numeric.hip", "sam_aux.hip", "sam_adjoint.hip", "sam_adaptive.hip", "sam_capi.cpp",
-           "sam_sequence.cpp", "sam_backward.cpp", "sam_adaptive_api.cpp", "sam_noalloc.cpp"]
+SOURCES = ["sam_symbolic.hip", "sam_numeric.hip", "sam_aux.hip", "sam_adjoint.hip", "sam_adaptive.hip", "sam_krylov.hip",
+           "sam_capi.cpp",
+           "sam_sequence.cpp", "sam_backward.cpp", "sam_adaptive_api.cpp", "sam_krylov_api.cpp", "sam_noalloc.cpp"]
 HEADERS = ["sam_device.hpp", "sam_kernels.hpp", "sam_numeric_args.hpp", "sam_host.hpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -93,7 +94,7 @@ def build(force: bool = False, jobs: int = 4) -> str:
     return LIB
 
 
-HOST_SOURCES = ["sam_capi.cpp", "sam_sequence.cpp", "sam_backward.cpp", "sam_adaptive_api.cpp", "sam_noalloc.cpp"]
+HOST_SOURCES = ["sam_capi.cpp", "sam_sequence.cpp", "sam_backward.cpp", "sam_adaptive_api.cpp", "sam_krylov_api.cpp", "sam_noalloc.cpp"]
 ASAN_DIR = os.path.join(OBJDIR, "asan")
 ASAN_LIB = os.path.join(ASAN_DIR, "libsam_mi355x_asan.so")
 

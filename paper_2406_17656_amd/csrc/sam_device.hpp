@@ -202,6 +202,47 @@ __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Row i of M x over the row view, by the kSpmvLanes consecutive lanes of the
+// row, so that the lanes of a wave read each row's column indices (and values)
+// as one contiguous run instead of one entry of 64 different rows.  Lane g
+// sums entries g, g + 4, ... of the row in ascending order; the four partials
+// are added by the quad exchanges of group_sum (the same order on every call).
+// Each lane issues the loads of kSpmvUnroll of its entries (indices and
+// values, then the x values they select) before it adds them, so a row of up
+// to 16 entries costs two dependent round trips instead of two per entry;
+// slots past the row's end load a valid entry of the row with a zero value,
+// which adds an exact zero.  Every lane takes part; rows with live = false
+// give 0.
+// PERM: the values are read through the row view's permutation (else they
+// are in the row view's order).  SCALE: x is scale .* x.
+constexpr int kSpmvLanes = 4;
+constexpr int kSpmvUnroll = 4;
+template <bool F32, bool PERM, bool SCALE>
+__device__ inline double row_product(bool live, int i, const int* rowptr, const int* colind, const int* perm,
+                                     const void* val, const double* x, const double* scale) {
+    const int g = threadIdx.x % kSpmvLanes;
+    double s = 0.0;
+    if (live) {
+        const int b = rowptr[i + 1];
+        for (int e = rowptr[i] + g; e < b; e += kSpmvLanes * kSpmvUnroll) {
+            int c[kSpmvUnroll];
+            double v[kSpmvUnroll], xv[kSpmvUnroll];
+#pragma unroll
+            for (int u = 0; u < kSpmvUnroll; ++u) {
+                const int eu = e + u * kSpmvLanes < b ? e + u * kSpmvLanes : e;   // e < b: in the row
+                c[u] = colind[eu];
+                const int ev = PERM ? perm[eu] : eu;
+                v[u] = F32 ? (double)static_cast<const float*>(val)[ev] : static_cast<const double*>(val)[ev];
+            }
+#pragma unroll
+            for (int u = 0; u < kSpmvUnroll; ++u) xv[u] = SCALE ? scale[c[u]] * x[c[u]] : x[c[u]];
+#pragma unroll
+            for (int u = 0; u < kSpmvUnroll; ++u) s = fma(e + u * kSpmvLanes < b ? v[u] : 0.0, xv[u], s);
+        }
+    }
+    return group_sum<kSpmvLanes>(s);
+}
+
 template <typename T>
 __device__ inline bool finite_val(T x) { return isfinite(x); }
 

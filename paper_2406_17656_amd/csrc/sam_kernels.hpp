@@ -129,6 +129,27 @@ hipError_t spmv_rows(int n, const int* rowptr, const int* colind, const int* per
 hipError_t permute_vals(int64_t nnz, const int* perm, const void* val, int val_f32, void* out,
                         hipStream_t s);
 
+// ------------------------------------------------------------------ GMRES
+// One cycle's operands (sam_gmres_steps) and scratch: w (n), part and part2
+// ((restart + 1) gmres_chunks(n)), nrm (gmres_chunks(n)), h1, h2, cs, sn
+// (restart + 1 each).
+struct GmresArgs {
+    int n, restart;
+    const int *A_rowptr, *A_colind;
+    const double* A_val;
+    const int *N_rowptr, *N_colind;   // null: no map
+    const void* N_val;
+    int N_f32;
+    const double* d;
+    double *V, *Z, *H, *state;
+    double tol;
+    double *w, *part, *part2, *nrm, *h1, *h2, *cs, *sn;
+};
+int gmres_chunks(int n);
+hipError_t gmres_init(int restart, double beta, double* state, hipStream_t s);
+hipError_t gmres_step(const GmresArgs& a, int k, hipStream_t s);
+hipError_t gmres_solution(int n, int used, const double* y, const double* Z, double* x, hipStream_t s);
+
 // ---------------------------------------------------------------- adjoint
 // gAk[f] = sum over the S entries (l, j) with l the column of entry f, in
 // ascending j (row view of S: ST_rowptr / ST_perm), of the staged

@@ -7,8 +7,10 @@ Jacobi, P_0 = diag(A_0)^-1), the updated right preconditioner is N_k P_0:
 A_k N_k P_0 ~ A_0 P_0.  ``gmres`` is restarted GMRES(m) with modified
 Gram-Schmidt and Givens rotations, right-preconditioned.  The sparse products
 (A_k x and N_k y) are library calls (``sam_apply`` on row views built by
-``sam_apply_prepare``); the vector arithmetic of the Krylov driver (dot
-products, updates, the small Hessenberg system) uses torch and the host.
+``sam_apply_prepare``).  For operators given as callables the vector arithmetic
+of the driver (dot products, updates, the small Hessenberg system) uses torch
+and the host; ``solve_with_map`` on the device runs whole Arnoldi steps in the
+library (``sam_gmres_steps``).
 """
 from __future__ import annotations
 
@@ -16,7 +18,8 @@ import math
 
 import torch
 
-from .sam import Context, DeviceCSC
+from . import _capi as C
+from .sam import Context, DeviceCSC, _buf, _prec, _ptr, _size
 
 
 class SparseOp:
@@ -102,16 +105,83 @@ def gmres(apply_A, apply_M, b, tol=1e-8, restart=50, maxiter=2000):
     return x, its, hist
 
 
+# Basis and preconditioned vectors the device driver keeps at once.
+BASIS_BYTES = 4 << 30
+
+
+def _gmres_device(A: SparseOp, N: SparseOp | None, dinv, b, tol, restart, maxiter):
+    """``gmres`` with the Arnoldi steps in the library: the residual test runs
+    on the device, so the host looks after 1, 2, 4, ... 16 steps instead of
+    after every dot product (steps enqueued past the last one needed return
+    at once)."""
+    ctx, n, dev = A.ctx, b.numel(), b.device
+    m = min(restart, maxiter)
+    x = torch.zeros_like(b)
+    bnorm = float(torch.linalg.vector_norm(b))
+    hist = []
+    its, batch = 0, 1
+    V = torch.empty((m + 1, n), dtype=torch.float64, device=dev)
+    Z = torch.empty((m, n), dtype=torch.float64, device=dev)
+    H = torch.empty((m, m + 1), dtype=torch.float64, device=dev)       # a column per row of the tensor
+    state = torch.empty(2 * m + 3, dtype=torch.float64, device=dev)
+    nb = _size(ctx.lib.sam_gmres_workspace_size, n, m)
+    ws = _buf(nb, dev)
+    rp, ci, _ = A.T
+    nrp, nci = (None, None) if N is None else N.T[:2]
+    while its < maxiter:
+        r = b - A(x)
+        beta = float(torch.linalg.vector_norm(r))
+        hist.append(beta / bnorm)
+        if beta <= tol * bnorm:
+            break
+        torch.div(r, beta, out=V[0])
+        left = min(m, maxiter - its)
+        k = 0
+        while True:
+            count = min(batch, left - k)
+            ctx.check(ctx.lib.sam_gmres_steps(
+                ctx.h, n, _ptr(rp), _ptr(ci), _ptr(A.val), _ptr(nrp), _ptr(nci), None if N is None else _ptr(N.val),
+                C.SAM_PREC_F64 if N is None else _prec(N.prec), _ptr(dinv), m, k, count, beta, tol * bnorm, _ptr(V),
+                _ptr(Z), _ptr(H), _ptr(state), _ptr(ws), nb, ctx.stream()))
+            k += count
+            seen = state.tolist()
+            if seen[1] != 0.0 or k == left:
+                break
+            batch = min(16, 2 * batch)
+        used = int(seen[0])
+        its += used
+        hist.extend(v / bnorm for v in seen[2:2 + used])
+        g = seen[2 + m:2 + m + used + 1]
+        R = H[:used, :used].cpu().numpy().T
+        y = [0.0] * used
+        for i in range(used - 1, -1, -1):
+            y[i] = (g[i] - float(R[i, i + 1:] @ y[i + 1:])) / float(R[i, i])
+        yd = torch.tensor(y, dtype=torch.float64).to(dev)
+        ctx.check(ctx.lib.sam_gmres_solution(ctx.h, n, used, _ptr(yd), _ptr(Z), _ptr(x), ctx.stream()))
+        if abs(g[used]) <= tol * bnorm:
+            r = b - A(x)
+            hist.append(float(torch.linalg.vector_norm(r)) / bnorm)
+            break
+    return x, its, hist
+
+
 def solve_with_map(ctx: Context, Ak: DeviceCSC, A0: DeviceCSC, M_colptr, M_rowind, M_val, b,
                    prec="f32", tol=1e-8, restart=50, maxiter=2000):
     """GMRES on A_k x = b with the right preconditioner N_k diag(A_0)^-1
     (M_val None: the frozen preconditioner diag(A_0)^-1 alone)."""
     A = SparseOp(ctx, Ak.n, Ak.colptr, Ak.rowind, Ak.val, "f64")
     dinv = 1.0 / jacobi_diag(A0)
-    if M_val is None:
+    N = None if M_val is None else SparseOp(ctx, Ak.n, M_colptr, M_rowind, M_val, prec)
+    m = min(restart, maxiter)
+    # the library's steps take vectors of the context's device in FP64, up to
+    # its longest cycle and a bounded basis; anything else runs on callables
+    if (b.is_cuda and b.device.index == ctx.device and b.dtype == torch.float64 and b.dim() == 1
+            and b.numel() == Ak.n and b.is_contiguous() and not b.requires_grad
+            and 1 <= m <= C.SAM_GMRES_MAX_RESTART and (2 * m + 1) * Ak.n * 8 <= BASIS_BYTES):
+        return _gmres_device(A, N, dinv, b, tol, restart, maxiter)
+    if N is None:
         apply_M = lambda v: dinv * v                       # noqa: E731
     else:
-        N = SparseOp(ctx, Ak.n, M_colptr, M_rowind, M_val, prec)
         apply_M = lambda v: N(dinv * v)                    # noqa: E731
     return gmres(A, apply_M, b, tol, restart, maxiter)
 
