@@ -174,8 +174,8 @@ sam_status sam_check_csc(sam_ctx* ctx, const sam_csc* A, sam_stream_t stream);
 /* Bytes of the workspace sam_pattern_count / sam_pattern_fill need for this
  * A_k structure and spec->power (host output).  B = S(A~_k) needs
  * nnz(A_k) + n entries.  An intermediate level of power q (p >= 3) needs at
- * most n min(n, (1 + longest column)^q) entries.  Synchronising: reads
- * colptr to the host and checks it.  Errors: as sam_pattern_count, and
+ * most n min(n, (1 + longest column)^q) entries.  Synchronising: checks
+ * colptr on the device.  Errors: as sam_pattern_count, and
  * SAM_ERR_UNSORTED for a bad colptr. */
 sam_status sam_pattern_workspace_size(sam_ctx* ctx, const sam_csc* Ak, const sam_pattern_spec* spec,
                                       size_t* bytes, sam_stream_t stream);
@@ -523,7 +523,7 @@ sam_status sam_backward(sam_plan* plan, const double* Ak_val, const double* A0_v
  * also in B (same column and row), w_cand elsewhere.  S and B are CSC
  * patterns on the device with rows ascending per column.  Errors:
  * SAM_ERR_ARG (NULL, negative sizes), SAM_ERR_SHAPE / SAM_ERR_UNSORTED (the
- * column pointers, checked on the host), SAM_ERR_OVERFLOW.  Synchronising
+ * column pointers), SAM_ERR_OVERFLOW.  Synchronising
  * (the column-pointer check). */
 sam_status sam_candidate_weights(sam_ctx* ctx, int32_t n, const int32_t* S_colptr, const int32_t* S_rowind,
                                  int64_t nnz_S, const int32_t* B_colptr, const int32_t* B_rowind, int64_t nnz_B,

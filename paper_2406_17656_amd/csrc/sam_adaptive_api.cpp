@@ -10,9 +10,16 @@ using namespace samh;
 
 namespace {
 
-// Host check of a column-pointer array (synchronising): cp[0] = 0,
-// non-decreasing, cp[n] = nnz.
-sam_status check_colptr(sam_ctx* ctx, const int32_t* cp, int n, int64_t nnz, const char* name, hipStream_t s) {
+// Check of a column-pointer array (synchronising): cp[0] = 0, non-decreasing,
+// cp[n] = nnz.  The device checks it; a bad one is copied for its message.
+sam_status check_pointers(sam_ctx* ctx, const int32_t* cp, int n, int64_t nnz, const char* name, hipStream_t s) {
+    if (n > 0) {
+        const samk::CscRef ref{(int)nnz, cp, nullptr, nullptr, nullptr};
+        StructureFacts f;
+        sam_status st;
+        if ((st = structure_facts(ctx, n, &ref, 1, &f, s)) || (st = read_facts(ctx, n, &f, s))) return st;
+        if (f.m[0].bad_cp == n) return SAM_OK;
+    }
     std::vector<int> h((size_t)n + 1);
     HIP_TRY(ctx, hipMemcpyAsync(h.data(), cp, h.size() * 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
@@ -71,8 +78,8 @@ sam_status sam_candidate_weights(sam_ctx* ctx, int32_t n, const int32_t* S_colpt
     sam_status st = need_device(ctx);
     if (st) return st;
     hipStream_t s = S(stream);
-    if ((st = check_colptr(ctx, S_colptr, n, nnz_S, "S_colptr", s))) return st;
-    if ((st = check_colptr(ctx, B_colptr, n, nnz_B, "B_colptr", s))) return st;
+    if ((st = check_pointers(ctx, S_colptr, n, nnz_S, "S_colptr", s))) return st;
+    if ((st = check_pointers(ctx, B_colptr, n, nnz_B, "B_colptr", s))) return st;
     HIP_TRY(ctx, samk::candidate_weights(n, S_colptr, S_rowind, B_colptr, B_rowind, w_base, w_cand, w, s));
     return SAM_OK;
 }
@@ -93,7 +100,7 @@ sam_status sam_pattern_topk(sam_ctx* ctx, int32_t n, const int32_t* S_colptr, co
     int64_t* off = nullptr;
     void* stemp = nullptr;
     if ((st = check_ws(ctx, ws, ws_bytes, topk_layout(cv, n, &counts, &off, &stemp), "top-k workspace"))) return st;
-    if ((st = check_colptr(ctx, S_colptr, n, nnz_S, "S_colptr", s))) return st;
+    if ((st = check_pointers(ctx, S_colptr, n, nnz_S, "S_colptr", s))) return st;
     HIP_TRY(ctx, samk::topk_count(n, S_colptr, S_rowind, w, grad, k, counts, s));
     HIP_TRY(ctx, samk::scan_counts(counts, n, off, out_colptr, nullptr, stemp, s));
     int64_t tot = 0;

@@ -301,7 +301,7 @@ __global__ void k_permute_vals(int64_t nnz, const int* perm, const void* val, in
 
 __global__ void k_identity_queue(int n, int* queue, int* bstart) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) queue[i] = i;
+    if (queue && i < n) queue[i] = i;
     if (i == 0) {
         bstart[0] = 0;
         bstart[1] = n;
@@ -309,8 +309,15 @@ __global__ void k_identity_queue(int n, int* queue, int* bstart) {
 }
 
 hipError_t identity_queue(int n, int* queue, int* bstart, hipStream_t s) {
-    hipLaunchKernelGGL(k_identity_queue, dim3((unsigned)((std::max(n, 1) + 255) / 256)), dim3(256), 0, s, n, queue,
-                       bstart);
+    const int blocks = queue ? (std::max(n, 1) + 255) / 256 : 1;
+    hipLaunchKernelGGL(k_identity_queue, dim3((unsigned)blocks), dim3(256), 0, s, n, queue, bstart);
+    return hipGetLastError();
+}
+
+__global__ void k_set4(int* p, int4 v) { *reinterpret_cast<int4*>(p) = v; }
+
+hipError_t set4_i32(int* p, int a, int b, int c, int d, hipStream_t s) {
+    hipLaunchKernelGGL(k_set4, dim3(1), dim3(1), 0, s, p, make_int4(a, b, c, d));
     return hipGetLastError();
 }
 

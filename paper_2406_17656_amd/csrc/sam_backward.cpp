@@ -126,7 +126,7 @@ sam_status sam_backward(sam_plan* plan, const double* Ak_val, const double* A0_v
         const int cnt = cb.counts[k];
         if (cnt <= 0) continue;
         const samk::NumericVariant* v = cb.variants[k];
-        a.bucket = (int)k;
+        a.bucket = cb.slot.empty() ? (int)k : cb.slot[k];
         int groups = (cnt + v->per_wave() - 1) / v->per_wave();
         int grid = std::min(groups, ctx->CUs * 16);
         if (grid >= 64) grid = grid / 8 * 8;

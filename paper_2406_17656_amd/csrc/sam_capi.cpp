@@ -82,38 +82,71 @@ samk::SparsifySpec to_sp(const sam_pattern_spec* spec) {
     return sp;
 }
 
-sam_status host_colptr(sam_ctx* ctx, const int32_t* cp, int n, int64_t nnz, const char* name, int* longest,
-                       hipStream_t s, std::vector<int>* keep) {
-    std::vector<int> local;
-    std::vector<int>& h = keep ? *keep : local;
-    h.assign((size_t)n + 1, 0);
+// The error of bad column pointers, from a copy of them.
+sam_status colptr_error(sam_ctx* ctx, const int32_t* cp, int n, int64_t nnz, const char* name, hipStream_t s) {
+    std::vector<int> h((size_t)n + 1, 0);
     HIP_TRY(ctx, hipMemcpyAsync(h.data(), cp, h.size() * 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
     if (h[0] != 0 || h[(size_t)n] != nnz)
         return fail(ctx, SAM_ERR_UNSORTED, "%s: colptr[0] = %d and colptr[n] = %d, expected 0 and %lld", name, h[0],
                     h[(size_t)n], (long long)nnz);
-    int most = 0;
-    for (int j = 0; j < n; ++j) {
-        const int len = h[(size_t)j + 1] - h[(size_t)j];
-        if (len < 0) return fail(ctx, SAM_ERR_UNSORTED, "%s: colptr decreases at column %d", name, j);
-        most = std::max(most, len);
-    }
-    if (longest) *longest = most;
+    for (int j = 0; j < n; ++j)
+        if (h[(size_t)j + 1] < h[(size_t)j])
+            return fail(ctx, SAM_ERR_UNSORTED, "%s: colptr decreases at column %d", name, j);
     return SAM_OK;
 }
 
-sam_status validate_csc(sam_ctx* ctx, int n, int64_t nnz, const int32_t* cp, const int32_t* ri, const char* name,
+sam_status check_colptr(sam_ctx* ctx, const int32_t* cp, int n, int64_t nnz, const char* name, int* longest,
                         hipStream_t s) {
+    if (longest) *longest = 0;
+    if (n == 0) return colptr_error(ctx, cp, n, nnz, name, s);
+    const samk::CscRef ref{(int)nnz, cp, nullptr, nullptr, nullptr};
+    StructureFacts f;
+    sam_status st;
+    if ((st = structure_facts(ctx, n, &ref, 1, &f, s)) || (st = read_facts(ctx, n, &f, s))) return st;
+    if (f.m[0].bad_cp != n) return colptr_error(ctx, cp, n, nnz, name, s);
+    if (longest) *longest = f.m[0].longest;
+    return SAM_OK;
+}
+
+sam_status structure_facts(sam_ctx* ctx, int n, const samk::CscRef* refs, int count, StructureFacts* out,
+                           hipStream_t s) {
+    *out = StructureFacts{};
     if (n == 0) return SAM_OK;
-    int h = n;
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->d_bad, &h, sizeof h, hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, samk::check_csc(n, (int)nnz, cp, ri, ctx->d_bad, s));
-    HIP_TRY(ctx, hipMemcpyAsync(&h, ctx->d_bad, sizeof h, hipMemcpyDeviceToHost, s));
+    samk::CheckArgs a{};
+    a.n = n;
+    a.count = count;
+    for (int i = 0; i < count; ++i) a.m[i] = refs[i];
+    a.facts = ctx->d_facts;
+    a.total = ctx->d_total;
+    HIP_TRY(ctx, samk::check_structures(a, s));
+    return SAM_OK;
+}
+
+// The facts (and the gathered total) of the last structure_facts: one copy.
+sam_status read_facts(sam_ctx* ctx, int n, StructureFacts* out, hipStream_t s) {
+    if (n == 0) return SAM_OK;
+    static_assert(sizeof(StructureFacts) == kFactsBytes, "the status block's layout");
+    HIP_TRY(ctx, hipMemcpyAsync(out, ctx->d_facts, sizeof *out, hipMemcpyDeviceToHost, s));
     HIP_TRY(ctx, hipStreamSynchronize(s));
-    if (h != n)
-        return fail(ctx, SAM_ERR_UNSORTED,
-                    "%s: invalid CSC structure at column %d (colptr not monotone or not ending at nnz, or rows "
-                    "outside [0, n), unsorted or repeated)", name, h);
+    return SAM_OK;
+}
+
+sam_status bad_structure(sam_ctx* ctx, int column, const char* name) {
+    return fail(ctx, SAM_ERR_UNSORTED,
+                "%s: invalid CSC structure at column %d (colptr not monotone or not ending at nnz, or rows "
+                "outside [0, n), unsorted or repeated)", name, column);
+}
+
+sam_status validate_csc(sam_ctx* ctx, int n, int64_t nnz, const int32_t* cp, const int32_t* ri, const char* name,
+                        hipStream_t s, samk::CscFacts* facts) {
+    if (n == 0) return SAM_OK;
+    const samk::CscRef ref{(int)nnz, cp, ri, nullptr, nullptr};
+    StructureFacts f;
+    sam_status st;
+    if ((st = structure_facts(ctx, n, &ref, 1, &f, s)) || (st = read_facts(ctx, n, &f, s))) return st;
+    if (f.m[0].bad != n) return bad_structure(ctx, f.m[0].bad, name);
+    if (facts) *facts = f.m[0];
     return SAM_OK;
 }
 
@@ -136,7 +169,7 @@ void pattern_ws_layout(Carve& cv, int n, int nnzA, int longest, int power, Patte
     t.D = cv.take<double>((size_t)n);
     t.B_cp = cv.take<int>((size_t)n + 1);
     t.B_ri = cv.take<int>((size_t)nnzA + (size_t)n);
-    t.flags = cv.take<int>(4);
+    t.flags = cv.take<int>(8);
     const int mids = power >= 3 ? std::min(power - 2, 2) : 0;
     t.Lcap = power >= 3 ? level_bound(n, longest, power - 1) : 0;
     for (int i = 0; i < mids; ++i) {
@@ -151,7 +184,7 @@ void pattern_ws_layout(Carve& cv, int n, int nnzA, int longest, int power, Patte
 // level <- expand(level, B).  Intermediate levels are stored in the
 // workspace; the last is counted only.
 sam_status compute_pattern(sam_ctx* ctx, const sam_csc* Ak, const sam_pattern_spec* spec, const PatternWs& w,
-                           PatternResult* res, hipStream_t s, PatternLevels* levels) {
+                           const samk::CscFacts& facts, PatternResult* res, hipStream_t s, PatternLevels* levels) {
     const int n = Ak->n;
     const int p = spec->power;
     const size_t cp_bytes = (size_t)(n + 1) * 4;
@@ -166,8 +199,10 @@ sam_status compute_pattern(sam_ctx* ctx, const sam_csc* Ak, const sam_pattern_sp
     };
     *res = PatternResult{};
     samk::SparsifySpec sp = to_sp(spec);
-    const int init[3] = {0, n, 0};
-    HIP_TRY(ctx, hipMemcpyAsync(w.flags, init, sizeof init, hipMemcpyHostToDevice, s));
+    // flags: overflow, earliest bad column, longest column of the level just
+    // scanned; its total follows them
+    int64_t* d_total = (int64_t*)(w.flags + 4);
+    HIP_TRY(ctx, samk::set4_i32(w.flags, 0, n, 0, 0, s));
     if (n == 0) {
         HIP_TRY(ctx, samk::fill_i32(w.B_cp, 1, 0, s));
         HIP_TRY(ctx, samk::fill_i32(w.S_cp, 1, 0, s));
@@ -177,65 +212,65 @@ sam_status compute_pattern(sam_ctx* ctx, const sam_csc* Ak, const sam_pattern_sp
         HIP_TRY(ctx, hipStreamSynchronize(s));
         return SAM_OK;
     }
-    // total and longest column of the level just scanned
-    auto level_facts = [&](int64_t* tot, int* maxc) {
-        hipError_t e = hipMemcpyAsync(tot, w.off + n, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(maxc, w.flags + 2, sizeof(int), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        return e;
+    struct { int flags[4]; int64_t total; } host{};
+    auto level_facts = [&]() {   // one copy
+        hipError_t e = hipMemcpyAsync(&host, w.flags, sizeof host, hipMemcpyDeviceToHost, s);
+        return e == hipSuccess ? hipStreamSynchronize(s) : e;
     };
     HIP_TRY(ctx, samk::sparsify_count(n, Ak->colptr, Ak->rowind, Ak->val, sp, w.D, w.counts, s));
-    HIP_TRY(ctx, samk::scan_counts(w.counts, n, w.off, w.B_cp, w.flags, w.stemp, s, w.flags + 2));
+    HIP_TRY(ctx, samk::scan_counts(w.counts, n, w.off, w.B_cp, w.flags, w.stemp, s, nullptr, d_total));
     HIP_TRY(ctx, samk::sparsify_fill(n, Ak->colptr, Ak->rowind, Ak->val, sp, w.D, w.B_cp, w.B_ri, s));
     HIP_TRY(ctx, keep_level(0, w.B_cp));
-    int64_t nnzB = 0;
-    int maxB = 0;
-    HIP_TRY(ctx, level_facts(&nnzB, &maxB));
-    if (levels) {
-        levels->nnz.push_back(nnzB);
+    // B's longest column is at most A_k's, one more where a diagonal is added
+    // (it picks what the expansion holds in registers)
+    const int maxB = facts.longest + (facts.missing > 0 ? 1 : 0);
+    if (levels) {   // structural patterns (no rule): B is A_k's structure and the missing diagonals
+        levels->nnz.push_back((int64_t)Ak->nnz + facts.missing);
         levels->maxcol.push_back(maxB);
     }
     const int* cur_cp = w.B_cp;
     const int* cur_ri = w.B_ri;
     int cur_max = maxB;
-    int64_t last_nnz = nnzB;
     for (int lev = 1; lev < p; ++lev) {
         HIP_TRY(ctx, samk::expand_count(n, cur_cp, cur_ri, w.B_cp, w.B_ri, w.counts, w.flags + 1, cur_max, s));
         HIP_TRY(ctx, samk::fill_i32(w.flags + 2, 1, 0, s));
         const bool last = lev == p - 1;
         int* dst_cp = last ? w.S_cp : w.L_cp[(lev - 1) & 1];
-        HIP_TRY(ctx, samk::scan_counts(w.counts, n, w.off, dst_cp, w.flags, w.stemp, s, w.flags + 2));
-        int64_t tot = 0;
-        int tmax = 0;
-        HIP_TRY(ctx, level_facts(&tot, &tmax));
-        if (tot > INT_MAX)
-            return fail(ctx, SAM_ERR_OVERFLOW, "pattern level %d has %lld entries (>= 2^31)", lev + 1, (long long)tot);
+        HIP_TRY(ctx, samk::scan_counts(w.counts, n, w.off, dst_cp, w.flags, w.stemp, s, w.flags + 2, d_total));
         HIP_TRY(ctx, keep_level(lev, dst_cp));
-        if (levels) {
-            levels->nnz.push_back(tot);
-            levels->maxcol.push_back(tmax);
-        }
         if (last) {
             res->last_cp = cur_cp;
             res->last_ri = cur_ri;
             res->last_max = cur_max;
-            last_nnz = tot;
-        } else {
-            if (tot > w.Lcap)   // cannot happen: the bound holds for every pattern of this structure
-                return fail(ctx, SAM_ERR_OVERFLOW, "pattern level %d exceeds its workspace bound", lev + 1);
-            int* dst_ri = w.L_ri[(lev - 1) & 1];
-            HIP_TRY(ctx, samk::expand_fill(n, cur_cp, cur_ri, w.B_cp, w.B_ri, dst_cp, dst_ri, cur_max, maxB, s));
-            cur_cp = dst_cp;
-            cur_ri = dst_ri;
-            cur_max = tmax;
+            break;
         }
+        HIP_TRY(ctx, level_facts());
+        if (host.total > INT_MAX)
+            return fail(ctx, SAM_ERR_OVERFLOW, "pattern level %d has %lld entries (>= 2^31)", lev + 1,
+                        (long long)host.total);
+        if (levels) {
+            levels->nnz.push_back(host.total);
+            levels->maxcol.push_back(host.flags[2]);
+        }
+        if (host.total > w.Lcap)   // cannot happen: the bound holds for every pattern of this structure
+            return fail(ctx, SAM_ERR_OVERFLOW, "pattern level %d exceeds its workspace bound", lev + 1);
+        int* dst_ri = w.L_ri[(lev - 1) & 1];
+        HIP_TRY(ctx, samk::expand_fill(n, cur_cp, cur_ri, w.B_cp, w.B_ri, dst_cp, dst_ri, cur_max, maxB, s));
+        cur_cp = dst_cp;
+        cur_ri = dst_ri;
+        cur_max = host.flags[2];
     }
-    int hflags[2] = {0, n};
-    HIP_TRY(ctx, hipMemcpyAsync(hflags, w.flags, sizeof hflags, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
-    if (hflags[1] != n) return fail(ctx, SAM_ERR_UNSORTED, "column %d references a column index outside [0, n)", hflags[1]);
-    if (hflags[0]) return fail(ctx, SAM_ERR_OVERFLOW, "pattern size does not fit in int32");
-    res->nnz = last_nnz;
+    HIP_TRY(ctx, level_facts());
+    if (p > 1 && host.total > INT_MAX)
+        return fail(ctx, SAM_ERR_OVERFLOW, "pattern level %d has %lld entries (>= 2^31)", p, (long long)host.total);
+    if (host.flags[1] != n)
+        return fail(ctx, SAM_ERR_UNSORTED, "column %d references a column index outside [0, n)", host.flags[1]);
+    if (host.flags[0]) return fail(ctx, SAM_ERR_OVERFLOW, "pattern size does not fit in int32");
+    if (levels && p > 1) {
+        levels->nnz.push_back(host.total);
+        levels->maxcol.push_back(host.flags[2]);
+    }
+    res->nnz = host.total;
     res->B_cp = w.B_cp;
     res->B_ri = w.B_ri;
     res->maxB = maxB;
@@ -284,31 +319,32 @@ BucketTable table_of(const std::vector<const NumericVariant*>& vars, int weighte
     return tab;
 }
 
-sam_status plan_combo(sam_plan* pl, int prec, int weighted, hipStream_t s) {
-    std::vector<const NumericVariant*> vars;
-    menu_table(prec, weighted, &vars);
-    return plan_combo_with(pl, prec, weighted, vars, s);
+// Columns of every class of a table, from the plan's shapes; returns the
+// columns that fit none.
+int class_counts(const sam_plan* pl, const BucketTable& tab, std::vector<int>* counts) {
+    counts->assign((size_t)tab.nb, 0);
+    int unfit = pl->shapes.empty() ? 0 : pl->shapes[samk::kShapeCells - 1];   // beyond every class
+    for (int r = 0; r <= samk::kShapeRows; ++r)
+        for (int c = 0; c <= samk::kShapeCols; ++c) {
+            const int cnt = pl->shapes.empty() ? 0 : pl->shapes[(size_t)r * (samk::kShapeCols + 1) + c];
+            if (!cnt) continue;
+            const int rows = tab.penalty_rows ? std::max(r, 2 * c) : r;
+            int b = 0;
+            while (b < tab.nb && !(rows <= tab.max_rows[b] && c <= tab.max_cols[b])) ++b;
+            if (b < tab.nb) (*counts)[(size_t)b] += cnt;
+            else unfit += cnt;
+        }
+    return unfit;
 }
 
-sam_status plan_combo_with(sam_plan* pl, int prec, int weighted, const std::vector<const NumericVariant*>& vars,
-                           hipStream_t s) {
-    sam_ctx* ctx = pl->ctx;
+void plan_combo_with(sam_plan* pl, int prec, int weighted, const std::vector<const NumericVariant*>& vars) {
     Combo& cb = pl->combo[prec][weighted];
     cb.variants = vars;
     if (cb.variants.size() > (size_t)samk::kMaxBuckets) cb.variants.resize(samk::kMaxBuckets);
-    BucketTable tab = table_of(cb.variants, weighted);
-    cb.tab = tab;
-    int* unfit_d = pl->flags;
-    HIP_TRY(ctx, samk::fill_i32(unfit_d, 1, 0, s));
-    HIP_TRY(ctx, samk::bucket_sort(pl->n, pl->S_cp, pl->nI, tab, cb.queue, cb.bstart, unfit_d, nullptr, pl->btemp, s));
-    std::vector<int> hb(tab.nb + 1, 0);
-    int unfit = 0;
-    HIP_TRY(ctx, hipMemcpyAsync(hb.data(), cb.bstart, sizeof(int) * (tab.nb + 1), hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipMemcpyAsync(&unfit, unfit_d, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
-    cb.counts.resize(tab.nb);
-    for (int b = 0; b < tab.nb; ++b) cb.counts[b] = hb[b + 1] - hb[b];
+    cb.tab = table_of(cb.variants, weighted);
+    const int unfit = class_counts(pl, cb.tab, &cb.counts);
     cb.ok = unfit == 0;
+    cb.why.clear();
     if (!cb.ok) {
         char buf[256];
         snprintf(buf, sizeof buf,
@@ -316,6 +352,30 @@ sam_status plan_combo_with(sam_plan* pl, int prec, int weighted, const std::vect
                  prec ? "FP32+refine" : "FP64", weighted ? " weighted" : "", pl->max_rows, pl->max_cols);
         cb.why = buf;
     }
+}
+
+sam_status plan_sort(sam_plan* pl, Combo* const* combos, int count, hipStream_t s) {
+    sam_ctx* ctx = pl->ctx;
+    samk::BucketJobs jobs{};
+    for (int i = 0; i < count; ++i) {
+        Combo& cb = *combos[i];
+        if (!cb.ok) continue;
+        // classes that receive no column change no column's first fitting
+        // class: the sort runs over the others
+        cb.slot.assign(cb.counts.size(), -1);
+        BucketTable tab{};
+        tab.penalty_rows = cb.tab.penalty_rows;
+        for (size_t b = 0; b < cb.counts.size(); ++b) {
+            if (cb.counts[b] <= 0) continue;
+            cb.slot[b] = tab.nb;
+            tab.max_rows[tab.nb] = cb.tab.max_rows[b];
+            tab.max_cols[tab.nb] = cb.tab.max_cols[b];
+            tab.nb++;
+        }
+        if (tab.nb == 1) HIP_TRY(ctx, samk::identity_queue(pl->n, nullptr, cb.bstart, s));
+        else if (tab.nb > 1) jobs.job[jobs.count++] = samk::BucketJob{tab, cb.queue, cb.bstart};
+    }
+    HIP_TRY(ctx, samk::bucket_sort(pl->n, pl->S_cp, pl->nI, jobs, nullptr, pl->btemp, s));
     return SAM_OK;
 }
 
@@ -339,16 +399,20 @@ namespace {
 
 struct PlanTemps {
     int* counts;
-    int64_t* off;
+    int* hist;      // shapes of the column problems
     void* stemp;
 };
 
-void plan_temp_layout(Carve& cv, int n, PlanTemps* t) {
+// The temporaries, then the offsets of the gathered entries, which are
+// written before their number (and with it the rest of the layout) is known.
+void plan_temp_layout(Carve& cv, int n, PlanTemps* t, sam_plan* pl) {
     PlanTemps x;
     x.counts = cv.take<int>((size_t)n);
-    x.off = cv.take<int64_t>((size_t)n + 1);
+    x.hist = cv.take<int>(samk::kShapeCells);
     x.stemp = cv.take<char>(samk::scan_temp_bytes(n));
+    int64_t* eoff = cv.take<int64_t>((size_t)n + 1);
     if (t) *t = x;
+    if (pl) pl->eoff = eoff;
 }
 
 // The plan's arrays (pl == null: measure only).
@@ -356,7 +420,6 @@ void plan_array_layout(Carve& cv, int n, int64_t E, int nnzA0, int partcap, sam_
     sam_plan dummy;
     sam_plan* p = pl ? pl : &dummy;
     p->nI = cv.take<int>((size_t)n);
-    p->eoff = cv.take<int64_t>((size_t)n + 1);
     p->posA = cv.take<unsigned char>((size_t)E);
     p->posB = cv.take<unsigned char>((size_t)nnzA0);
     for (int a = 0; a < 2; ++a)
@@ -368,33 +431,49 @@ void plan_array_layout(Carve& cv, int n, int64_t E, int nnzA0, int partcap, sam_
     p->partcap = partcap;
     p->partbuf = cv.take<double>((size_t)partcap);
     p->rtemp = cv.take<char>(samk::reduce_temp_bytes(std::max(n, partcap)));
-    p->btemp = cv.take<char>(samk::bucket_temp_bytes(n));
-    p->flags = cv.take<int>(4);
+    p->btemp = cv.take<char>(samk::bucket_temp_bytes(4));
 }
 
 }  // namespace
 
 size_t plan_bytes(int n, int64_t E, int nnzA0, int partcap) {
     Carve cv(nullptr);
-    plan_temp_layout(cv, n, nullptr);
+    plan_temp_layout(cv, n, nullptr, nullptr);
     plan_array_layout(cv, n, E, nnzA0, partcap, nullptr);
     return cv.off;
 }
 
-sam_status gathered_total(sam_ctx* ctx, int n, const int32_t* S_cp, const int32_t* S_ri, const int32_t* Ak_cp,
-                          int64_t* E, hipStream_t s) {
-    *E = 0;
-    if (n == 0) return SAM_OK;
-    unsigned long long h = 0;
-    HIP_TRY(ctx, hipMemcpyAsync(ctx->d_total, &h, sizeof h, hipMemcpyHostToDevice, s));
-    HIP_TRY(ctx, samk::plan_gather_total(n, S_cp, S_ri, Ak_cp, ctx->d_total, s));
-    HIP_TRY(ctx, read_back(ctx->d_total, &h, s));
-    *E = (int64_t)h;
-    return SAM_OK;
+// Flop counts and largest block from the shapes.
+void plan_shape_stats(sam_plan* pl) {
+    auto add = [&](double cnt, int ri, int ci) {
+        const double r = ri, c = ci;
+        pl->max_rows = std::max(pl->max_rows, ri);
+        pl->max_cols = std::max(pl->max_cols, ci);
+        // Householder QR of the r x c block (2 r c^2 - 2/3 c^3), Q^T b
+        // (4 r c) and three triangular solves (3 c^2: the solution and
+        // the refinement's two)
+        pl->fl_qr32 += cnt * (2.0 * r * c * c - 2.0 / 3.0 * c * c * c + 4.0 * r * c + 3.0 * c * c);
+        pl->fl_ref64 += cnt * (6.0 * r * c + 2.0 * r);   // r = b - Am, A^T r, final residual
+        // FP64 mode: QR, Q^T b, one triangular solve, explicit residual
+        pl->fl_f64 += cnt * (2.0 * r * c * c - 2.0 / 3.0 * c * c * c + 4.0 * r * c + c * c + 2.0 * r * c + 2.0 * r);
+        pl->m_rc2 += cnt * r * c * c;
+        pl->m_c3 += cnt * c * c * c;
+        pl->m_rc += cnt * r * c;
+        pl->m_c2 += cnt * c * c;
+        pl->m_r += cnt * r;
+    };
+    if (pl->large.empty()) {
+        for (int r = 0; r <= samk::kShapeRows; ++r)
+            for (int c = 0; c <= samk::kShapeCols; ++c)
+                if (const int cnt = pl->shapes[(size_t)r * (samk::kShapeCols + 1) + c]) add(cnt, r, c);
+    } else {   // some block is beyond every class: the shapes column by column
+        for (const auto& rc : pl->large) add(1.0, rc.first, rc.second);
+    }
 }
 
 sam_status plan_init(sam_ctx* ctx, sam_plan* pl, const sam_csc* Ak, const sam_csc* A0, const int32_t* S_colptr,
-                     const int32_t* S_rowind, int64_t nnz_S, void* mem, size_t mem_bytes, hipStream_t s) {
+                     const int32_t* S_rowind, int64_t nnz_S, void* mem, size_t mem_bytes, int only_prec,
+                     hipStream_t s) {
     const int n = Ak->n;
     pl->ctx = ctx;
     pl->n = n;
@@ -411,22 +490,29 @@ sam_status plan_init(sam_ctx* ctx, sam_plan* pl, const sam_csc* Ak, const sam_cs
     pl->mem_bytes = mem_bytes;
     Carve cv(mem);
     PlanTemps t;
-    plan_temp_layout(cv, n, &t);
-    const size_t temps = cv.off;
-    if (mem_bytes < temps) return fail(ctx, SAM_ERR_ARG, "plan memory: %zu bytes given, more needed", mem_bytes);
-
-    std::vector<int> hcp;
-    int longest = 0;
+    plan_temp_layout(cv, n, &t, pl);
     sam_status st;
-    if ((st = host_colptr(ctx, Ak->colptr, n, Ak->nnz, "Ak", &pl->max_len_A, s))) return st;
-    if ((st = host_colptr(ctx, S_colptr, n, nnz_S, "S", &longest, s, &hcp))) return st;
-    // pass 1: gathered entries per column -> eoff
-    int64_t E = 0;
-    if (n > 0) {
-        HIP_TRY(ctx, samk::plan_gather_count(n, S_colptr, S_rowind, Ak->colptr, t.counts, s));
-        HIP_TRY(ctx, samk::scan_counts(t.counts, n, t.off, nullptr, nullptr, t.stemp, s));
-        HIP_TRY(ctx, read_back(t.off + n, &E, s));
-    }
+    // the three structures' checks, their longest columns, and the gathered
+    // entries per column (where the memory holds their count), scanned
+    const bool room = cv.off <= mem_bytes;
+    const samk::CscRef refs[3] = {{Ak->nnz, Ak->colptr, Ak->rowind, nullptr, nullptr},
+                                  {A0->nnz, A0->colptr, A0->rowind, nullptr, nullptr},
+                                  {(int)nnz_S, S_colptr, S_rowind, Ak->colptr, room ? t.counts : nullptr}};
+    StructureFacts f;
+    if ((st = structure_facts(ctx, n, refs, 3, &f, s))) return st;
+    if (n > 0 && room)
+        HIP_TRY(ctx, samk::scan_counts(t.counts, n, pl->eoff, nullptr, nullptr, t.stemp, s));
+    if ((st = read_facts(ctx, n, &f, s))) return st;
+    const char* names[3] = {"Ak", "A0", "S"};
+    for (int i = 0; n > 0 && i < 3; ++i)
+        if (f.m[i].bad != n) return bad_structure(ctx, f.m[i].bad, names[i]);
+    if (n == 0)   // nothing on the device to check against: the pointers alone
+        if ((st = colptr_error(ctx, Ak->colptr, n, Ak->nnz, "Ak", s)) ||
+            (st = colptr_error(ctx, S_colptr, n, nnz_S, "S", s)))
+            return st;
+    if (!room) return fail(ctx, SAM_ERR_ARG, "plan memory: %zu bytes given, more needed", mem_bytes);
+    const int64_t E = (int64_t)f.total;
+    pl->max_len_A = f.m[0].longest;
     pl->E = E;
     // the numeric kernels address A_k, A_0 and the gathered positions with
     // 32-bit byte offsets
@@ -441,33 +527,33 @@ sam_status plan_init(sam_ctx* ctx, sam_plan* pl, const sam_csc* Ak, const sam_cs
         return fail(ctx, SAM_ERR_ARG, "plan memory: %zu bytes given, %zu needed", mem_bytes, cv.off);
 
     if (n > 0) {
-        std::vector<int> hnI(n);
-        HIP_TRY(ctx, hipMemcpyAsync(pl->eoff, t.off, (size_t)(n + 1) * 8, hipMemcpyDeviceToDevice, s));
         HIP_TRY(ctx, samk::plan_positions(n, S_colptr, S_rowind, Ak->colptr, Ak->rowind, A0->colptr, A0->rowind,
-                                          pl->eoff, pl->nI, pl->posA, pl->posB, longest, pl->max_len_A, s));
-        HIP_TRY(ctx, hipMemcpyAsync(hnI.data(), pl->nI, (size_t)n * 4, hipMemcpyDeviceToHost, s));
+                                          pl->eoff, pl->nI, pl->posA, pl->posB, f.m[2].longest, pl->max_len_A, s));
+        HIP_TRY(ctx, samk::shape_histogram(n, S_colptr, pl->nI, t.hist, s));
+        pl->shapes.assign(samk::kShapeCells, 0);
+        HIP_TRY(ctx, hipMemcpyAsync(pl->shapes.data(), t.hist, samk::kShapeCells * sizeof(int),
+                                    hipMemcpyDeviceToHost, s));
         HIP_TRY(ctx, hipStreamSynchronize(s));
-        for (int j = 0; j < n; ++j) {
-            pl->max_rows = std::max(pl->max_rows, hnI[j]);
-            const int cj = hcp[(size_t)j + 1] - hcp[(size_t)j];
-            pl->max_cols = std::max(pl->max_cols, cj);
-            const double r = hnI[j], c = cj;
-            // Householder QR of the r x c block (2 r c^2 - 2/3 c^3), Q^T b
-            // (4 r c) and three triangular solves (3 c^2: the solution and
-            // the refinement's two)
-            pl->fl_qr32 += 2.0 * r * c * c - 2.0 / 3.0 * c * c * c + 4.0 * r * c + 3.0 * c * c;
-            pl->fl_ref64 += 6.0 * r * c + 2.0 * r;   // r = b - Am, A^T r, final residual
-            // FP64 mode: QR, Q^T b, one triangular solve, explicit residual
-            pl->fl_f64 += 2.0 * r * c * c - 2.0 / 3.0 * c * c * c + 4.0 * r * c + c * c + 2.0 * r * c + 2.0 * r;
-            pl->m_rc2 += r * c * c;
-            pl->m_c3 += c * c * c;
-            pl->m_rc += r * c;
-            pl->m_c2 += c * c;
-            pl->m_r += r;
+        if (pl->shapes[samk::kShapeCells - 1] > 0) {
+            std::vector<int> hnI(n), hcp((size_t)n + 1);
+            HIP_TRY(ctx, hipMemcpyAsync(hnI.data(), pl->nI, (size_t)n * 4, hipMemcpyDeviceToHost, s));
+            HIP_TRY(ctx, hipMemcpyAsync(hcp.data(), S_colptr, hcp.size() * 4, hipMemcpyDeviceToHost, s));
+            HIP_TRY(ctx, hipStreamSynchronize(s));
+            for (int j = 0; j < n; ++j) pl->large.emplace_back(hnI[j], hcp[(size_t)j + 1] - hcp[(size_t)j]);
         }
+        plan_shape_stats(pl);
+        pl->large = {};
+        Combo* combos[4];
+        int count = 0;
         for (int p = 0; p < 2; ++p)
-            for (int w = 0; w < 2; ++w)
-                if ((st = plan_combo(pl, p, w, s))) return st;
+            for (int w = 0; w < 2; ++w) {
+                if (only_prec >= 0 && (p != only_prec || w != 0)) continue;
+                std::vector<const NumericVariant*> vars;
+                menu_table(p, w, &vars);
+                plan_combo_with(pl, p, w, vars);
+                combos[count++] = &pl->combo[p][w];
+            }
+        if ((st = plan_sort(pl, combos, count, s))) return st;
     }
     return SAM_OK;
 }
@@ -510,7 +596,7 @@ sam_status run_numeric(sam_plan* pl, const double* Ak_val, const double* A0_val,
         const int cnt = cb.counts[b];
         if (cnt <= 0) continue;
         const NumericVariant* v = cb.variants[b];
-        a.bucket = (int)b;
+        a.bucket = cb.slot.empty() ? (int)b : cb.slot[b];
         int groups = (cnt + v->per_wave() - 1) / v->per_wave();
         // one round of resident blocks for the plain maps; the weighted
         // forms run faster over two rounds (as the adjoint's launch)
@@ -616,8 +702,8 @@ sam_status sam_create(sam_ctx** out, int device) {
         // failure is kept and reported by that call, which alone needs it)
         (void)scratch_setup(device);
         ctx->d_status = (unsigned long long*)ctx->block;
-        ctx->d_bad = (int*)((char*)ctx->block + 64);
-        ctx->d_total = (unsigned long long*)((char*)ctx->block + 128);
+        ctx->d_facts = (samk::CscFacts*)((char*)ctx->block + 64);
+        ctx->d_total = (unsigned long long*)((char*)ctx->block + 64 + 3 * sizeof(samk::CscFacts));
         unsigned long long clear = kStatusClear;
         if (hipMemcpy(ctx->d_status, &clear, sizeof clear, hipMemcpyHostToDevice) != hipSuccess) {
             (void)hipFree(ctx->block);
@@ -682,7 +768,7 @@ sam_status sam_pattern_workspace_size(sam_ctx* ctx, const sam_csc* Ak, const sam
     if (!bytes) return fail(ctx, SAM_ERR_ARG, "bytes is NULL");
     if ((st = need_device(ctx))) return st;
     int longest = 0;
-    if ((st = host_colptr(ctx, Ak->colptr, Ak->n, Ak->nnz, "Ak", &longest, S(stream)))) return st;
+    if ((st = check_colptr(ctx, Ak->colptr, Ak->n, Ak->nnz, "Ak", &longest, S(stream)))) return st;
     Carve cv(nullptr);
     pattern_ws_layout(cv, Ak->n, Ak->nnz, longest, spec->power, nullptr);
     *bytes = cv.off;
@@ -699,15 +785,19 @@ sam_status sam_pattern_count(sam_ctx* ctx, const sam_csc* Ak, const sam_pattern_
     if ((st = need_device(ctx))) return st;
     hipStream_t s = S(stream);
     ctx->pat.valid = false;
-    int longest = 0;
-    if ((st = host_colptr(ctx, Ak->colptr, Ak->n, Ak->nnz, "Ak", &longest, s))) return st;
+    StructureFacts f;
+    const samk::CscRef ref{Ak->nnz, Ak->colptr, Ak->rowind, nullptr, nullptr};
+    if ((st = structure_facts(ctx, Ak->n, &ref, 1, &f, s)) || (st = read_facts(ctx, Ak->n, &f, s))) return st;
+    if ((Ak->n == 0 || f.m[0].bad_cp != Ak->n) &&
+        (st = colptr_error(ctx, Ak->colptr, Ak->n, Ak->nnz, "Ak", s)))
+        return st;
     Carve cv(ws);
     PatternWs w;
-    pattern_ws_layout(cv, Ak->n, Ak->nnz, longest, spec->power, &w);
+    pattern_ws_layout(cv, Ak->n, Ak->nnz, f.m[0].longest, spec->power, &w);
     if ((st = check_ws(ctx, ws, ws_bytes, cv.off, "pattern workspace"))) return st;
-    if ((st = validate_csc(ctx, Ak->n, Ak->nnz, Ak->colptr, Ak->rowind, "Ak", s))) return st;
+    if (Ak->n > 0 && f.m[0].bad != Ak->n) return bad_structure(ctx, f.m[0].bad, "Ak");
     PatternResult res;
-    if ((st = compute_pattern(ctx, Ak, spec, w, &res, s))) return st;
+    if ((st = compute_pattern(ctx, Ak, spec, w, f.m[0], &res, s))) return st;
     PatternState& ps = ctx->pat;
     ps.valid = true;
     ps.ws = ws;
@@ -758,17 +848,21 @@ sam_status sam_plan_size(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0, con
     if ((st = need_device(ctx))) return st;
     hipStream_t s = S(stream);
     const int n = Ak->n;
-    if ((st = validate_csc(ctx, n, Ak->nnz, Ak->colptr, Ak->rowind, "Ak", s))) return st;
-    if ((st = validate_csc(ctx, n, nnz_S, S_colptr, S_rowind, "S", s))) return st;
-    int64_t E = 0;
-    if ((st = gathered_total(ctx, n, S_colptr, S_rowind, Ak->colptr, &E, s))) return st;
-    *bytes = plan_bytes(n, E, A0->nnz, partial_capacity(ctx));
+    const samk::CscRef refs[2] = {{Ak->nnz, Ak->colptr, Ak->rowind, nullptr, nullptr},
+                                  {(int)nnz_S, S_colptr, S_rowind, Ak->colptr, nullptr}};
+    StructureFacts f;
+    if ((st = structure_facts(ctx, n, refs, 2, &f, s)) || (st = read_facts(ctx, n, &f, s))) return st;
+    if (n > 0 && f.m[0].bad != n) return bad_structure(ctx, f.m[0].bad, "Ak");
+    if (n > 0 && f.m[1].bad != n) return bad_structure(ctx, f.m[1].bad, "S");
+    *bytes = plan_bytes(n, (int64_t)f.total, A0->nnz, partial_capacity(ctx));
     return SAM_OK;
 }
 
-sam_status sam_plan_create(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0, const int32_t* S_colptr,
-                           const int32_t* S_rowind, int64_t nnz_S, void* mem, size_t mem_bytes, sam_plan** plan,
-                           sam_stream_t stream) {
+// sam_plan_create with every combination of precision and weighting, or
+// (only_prec >= 0, the one-shot build) the plain maps of one precision alone.
+static sam_status create_plan(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0, const int32_t* S_colptr,
+                              const int32_t* S_rowind, int64_t nnz_S, void* mem, size_t mem_bytes, int only_prec,
+                              sam_plan** plan, sam_stream_t stream) {
     if (check_ctx(ctx)) return SAM_ERR_ARG;
     sam_status st;
     if (!plan) return fail(ctx, SAM_ERR_ARG, "plan is NULL");
@@ -784,18 +878,20 @@ sam_status sam_plan_create(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0, c
     if ((st = check_ws(ctx, mem, mem_bytes, 1, "plan memory"))) return st;
     if ((st = need_device(ctx))) return st;
     hipStream_t s = S(stream);
-    const int n = Ak->n;
-    if ((st = validate_csc(ctx, n, Ak->nnz, Ak->colptr, Ak->rowind, "Ak", s))) return st;
-    if ((st = validate_csc(ctx, n, A0->nnz, A0->colptr, A0->rowind, "A0", s))) return st;
-    if ((st = validate_csc(ctx, n, nnz_S, S_colptr, S_rowind, "S", s))) return st;
     sam_plan* pl = new (std::nothrow) sam_plan();
     if (!pl) return fail(ctx, SAM_ERR_NOMEM, "host allocation failed");
-    if ((st = plan_init(ctx, pl, Ak, A0, S_colptr, S_rowind, nnz_S, mem, mem_bytes, s))) {
+    if ((st = plan_init(ctx, pl, Ak, A0, S_colptr, S_rowind, nnz_S, mem, mem_bytes, only_prec, s))) {
         delete pl;
         return st;
     }
     *plan = pl;
     return SAM_OK;
+}
+
+sam_status sam_plan_create(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0, const int32_t* S_colptr,
+                           const int32_t* S_rowind, int64_t nnz_S, void* mem, size_t mem_bytes, sam_plan** plan,
+                           sam_stream_t stream) {
+    return create_plan(ctx, Ak, A0, S_colptr, S_rowind, nnz_S, mem, mem_bytes, -1, plan, stream);
 }
 
 sam_status sam_plan_destroy(sam_plan* plan) {
@@ -899,7 +995,9 @@ sam_status sam_build(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0, const i
     if (!prec_ok(prec)) return fail(ctx, SAM_ERR_ARG, "unknown precision %d", (int)prec);
     if (nnz_S > 0 && !M_val) return fail(ctx, SAM_ERR_ARG, "M_val is NULL");
     sam_plan* pl = nullptr;
-    if ((st = sam_plan_create(ctx, Ak, A0, S_colptr, S_rowind, nnz_S, ws, ws_bytes, &pl, stream))) return st;
+    if ((st = create_plan(ctx, Ak, A0, S_colptr, S_rowind, nnz_S, ws, ws_bytes,
+                          prec == SAM_PREC_F32_REFINE ? 1 : 0, &pl, stream)))
+        return st;
     st = sam_build_planned(pl, Ak->val, A0->val, prec, M_val, col_res2, res2, stream);
     delete pl;   // host record only: the launches hold their arguments by value
     return st;
@@ -1038,15 +1136,17 @@ std::vector<const NumericVariant*> menu_subset(int prec, int weighted, const int
 sam_status plan_select(sam_plan* pl, int prec, const std::vector<const NumericVariant*>& vars, hipStream_t s) {
     sam_ctx* ctx = pl->ctx;
     Combo& cb = pl->combo[prec][0];
-    const std::vector<const NumericVariant*> previous = cb.variants;
-    sam_status st = plan_combo_with(pl, prec, 0, vars, s);
-    if (st) return st;
-    if (!cb.ok) {
+    const Combo previous = cb;
+    plan_combo_with(pl, prec, 0, vars);
+    if (!cb.ok) {   // nothing was sorted yet: the previous choice stays as it is
         const std::string why = cb.why;
-        st = plan_combo_with(pl, prec, 0, previous, s);
-        if (st) return st;
+        cb = previous;
         return fail(ctx, SAM_ERR_UNSUPPORTED, "selection rejected: %s", why.c_str());
     }
+    Combo* one = &cb;
+    sam_status st = plan_sort(pl, &one, 1, s);
+    if (st) return st;
+    HIP_TRY(ctx, hipStreamSynchronize(s));
     return SAM_OK;
 }
 

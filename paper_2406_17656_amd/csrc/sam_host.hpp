@@ -99,10 +99,10 @@ struct sam_ctx {
     int device = SAM_NO_DEVICE;
     std::string err;
     // 256-byte device status block: the status word (kernels' failures), the
-    // bad-column flag of structure checks and a 64-bit accumulator
+    // facts of up to three structure checks and a 64-bit accumulator
     void* block = nullptr;
     unsigned long long* d_status = nullptr;
-    int* d_bad = nullptr;
+    samk::CscFacts* d_facts = nullptr;          // 3, then d_total (read back together)
     unsigned long long* d_total = nullptr;
     samh::PatternState pat;
     int CUs = 256;
@@ -121,6 +121,9 @@ struct Combo {
     int* queue = nullptr;   // device n
     int* bstart = nullptr;  // device nb+1
     std::vector<int> counts;
+    // place of each class in bstart (empty: its own number): classes without
+    // columns are left out of the sort
+    std::vector<int> slot;
     // replanned sequences: one live bucket, so the queue is the identity and
     // bstart = {0, n}, written once instead of sorting every run
     bool identity = false;
@@ -145,9 +148,11 @@ struct sam_plan {
     double* partbuf = nullptr;  // per-block partial sums of the column residuals
     int partcap = 0;
     void* btemp = nullptr;      // bucket-sort temporary (selection)
-    int* flags = nullptr;       // device ints for the bucket sort
     int64_t E = 0;
     int max_rows = 0, max_cols = 0;
+    // columns per shape (samk::shape_histogram), host copy
+    std::vector<int> shapes;
+    std::vector<std::pair<int, int>> large;   // (rows, columns) of every column, during creation only
     // algorithmic flop counts of one build (dense column blocks), and the
     // shape moments sum_j r c^2, c^3, r c, c^2, r (r = |I_j|, c = |J_j|) the
     // weighted and adjoint counts follow from
@@ -195,40 +200,55 @@ hipError_t read_back(const T* dptr, T* host, hipStream_t s) {
     return hipStreamSynchronize(s);
 }
 
-// Column pointers read to the host (synchronising): checks colptr[0] = 0,
+// Facts of up to three structures and the gathered total, as the device holds
+// them in the status block.
+struct StructureFacts {
+    samk::CscFacts m[3];
+    unsigned long long total;
+};
+constexpr size_t kFactsBytes = 3 * sizeof(samk::CscFacts) + 8;
+static_assert(64 + kFactsBytes <= kCtxBlockBytes, "the facts fit the status block");
+// Enqueue the checks, and read their results back (synchronising).  Nothing
+// is enqueued for n = 0.
+sam_status structure_facts(sam_ctx* ctx, int n, const samk::CscRef* refs, int count, StructureFacts* out,
+                           hipStream_t s);
+sam_status read_facts(sam_ctx* ctx, int n, StructureFacts* out, hipStream_t s);
+sam_status bad_structure(sam_ctx* ctx, int column, const char* name);
+// Column pointers checked on the device (synchronising): colptr[0] = 0,
 // monotone, colptr[n] = nnz; *longest receives the longest column.
-sam_status host_colptr(sam_ctx* ctx, const int32_t* cp, int n, int64_t nnz, const char* name, int* longest,
-                       hipStream_t s, std::vector<int>* keep = nullptr);
+sam_status check_colptr(sam_ctx* ctx, const int32_t* cp, int n, int64_t nnz, const char* name, int* longest,
+                        hipStream_t s);
+// The error of column pointers that the device found bad (SAM_OK if they are
+// not), from a copy of them.
+sam_status colptr_error(sam_ctx* ctx, const int32_t* cp, int n, int64_t nnz, const char* name, hipStream_t s);
 // Full structure check on the device before any other kernel reads the
 // indices (synchronising): SAM_ERR_UNSORTED names the first bad column.
 sam_status validate_csc(sam_ctx* ctx, int n, int64_t nnz, const int32_t* cp, const int32_t* ri, const char* name,
-                        hipStream_t s);
+                        hipStream_t s, samk::CscFacts* facts = nullptr);
 
 // Pattern S((I + B)^p) counted in a pattern workspace: every level but the
 // last is stored there, the last is counted (column pointers in w.S_cp);
-// pattern_fill writes it to the caller's arrays.
+// pattern_fill writes it to the caller's arrays.  facts: A_k's.
 sam_status compute_pattern(sam_ctx* ctx, const sam_csc* Ak, const sam_pattern_spec* spec, const PatternWs& w,
-                           PatternResult* res, hipStream_t s, PatternLevels* levels = nullptr);
+                           const samk::CscFacts& facts, PatternResult* res, hipStream_t s, PatternLevels* levels = nullptr);
 sam_status pattern_fill(sam_ctx* ctx, int n, const PatternResult& res, int* S_cp, int* S_ri, hipStream_t s);
 
 // Plan memory: creation temporaries (sized by n), then the plan's arrays
 // (sized by n, the gathered entries E, nnz(A_0) and the partial-sum
 // capacity).
 size_t plan_bytes(int n, int64_t E, int nnzA0, int partcap);
-// A plan in caller memory `mem` (>= plan_bytes); structures validated by the
-// caller.  E_known >= 0 skips nothing but is checked against the count.
+// A plan in caller memory `mem` (>= plan_bytes).  Checks the three structures.
+// only_prec >= 0: the classes of that precision's plain maps alone.
 sam_status plan_init(sam_ctx* ctx, sam_plan* pl, const sam_csc* Ak, const sam_csc* A0, const int32_t* S_colptr,
-                     const int32_t* S_rowind, int64_t nnz_S, void* mem, size_t mem_bytes, hipStream_t s);
-// sum_j sum_{l in S(:,j)} nnz(A_k(:,l)) (synchronising; S validated).
-sam_status gathered_total(sam_ctx* ctx, int n, const int32_t* S_cp, const int32_t* S_ri, const int32_t* Ak_cp,
-                          int64_t* E, hipStream_t s);
+                     const int32_t* S_rowind, int64_t nnz_S, void* mem, size_t mem_bytes, int only_prec,
+                     hipStream_t s);
 
 // The bucket table of one (precision, weighted) combination of the menu.
 samk::BucketTable menu_table(int prec, int weighted, std::vector<const samk::NumericVariant*>* variants);
-sam_status plan_combo(sam_plan* pl, int prec, int weighted, hipStream_t s);
-// Bucket the plan's columns over an explicit ordered list of variants.
-sam_status plan_combo_with(sam_plan* pl, int prec, int weighted, const std::vector<const samk::NumericVariant*>& vars,
-                           hipStream_t s);
+// Classes of the plan's columns over an ordered list of variants (host only),
+// and the device queues of up to four combinations.
+void plan_combo_with(sam_plan* pl, int prec, int weighted, const std::vector<const samk::NumericVariant*>& vars);
+sam_status plan_sort(sam_plan* pl, Combo* const* combos, int count, hipStream_t s);
 samk::BucketTable table_of(const std::vector<const samk::NumericVariant*>& vars, int weighted);
 // Variants of sam_menu(prec, weighted) in the given order (nullptr entries when out of range).
 std::vector<const samk::NumericVariant*> menu_subset(int prec, int weighted, const int32_t* order, int32_t count,

@@ -12,18 +12,36 @@ namespace samk {
 // ----------------------------------------------------------------- scans
 // Exclusive prefix sum of n int32 counts into int64 offsets (n+1 entries,
 // off[n] = total).  Optionally also writes the int32 copy (n+1), raises
-// *overflow (device int) when the total does not fit in int32, and raises
-// *maxcount (device int, preset by the caller) to the largest count.  Needs
+// *overflow (device int) when the total does not fit in int32, raises
+// *maxcount (device int, preset by the caller) to the largest count and writes
+// the total to *total.  Needs
 // scan_temp_bytes(n) bytes of temporary device memory (any contents).  Two
 // launches (tile sums, then the scan) up to 2^21 counts.
 size_t scan_temp_bytes(int64_t n);
 hipError_t scan_counts(const int* counts, int64_t n, int64_t* off, int* off32, int* overflow,
-                       void* temp, hipStream_t s, int* maxcount = nullptr);
+                       void* temp, hipStream_t s, int* maxcount = nullptr, int64_t* total = nullptr);
 
 // ------------------------------------------------------------- structure
-// Checks of a CSC structure; writes the earliest bad column to *bad
-// (device int, must be preset to n by the caller; stays n when valid).
-hipError_t check_csc(int n, int nnz, const int* cp, const int* ri, int* bad, hipStream_t s);
+struct CscFacts {
+    int bad;                 // first column whose pointers or rows are invalid (n: none)
+    int bad_cp;              // first column at which the pointers alone are (n: none)
+    int longest;             // longest column
+    int missing;             // columns without their diagonal entry
+};
+struct CscRef {
+    int nnz;
+    const int *cp, *ri;      // ri null: the column pointers alone
+    const int* gather_cp;    // not null: sum nnz of these columns over the entries (checked indices)
+    int* gather_counts;      // per column of that sum (may be null)
+};
+struct CheckArgs {
+    int n, count;
+    CscRef m[3];
+    CscFacts* facts;         // device, count
+    unsigned long long* total;   // device: sum of the gathered entries
+};
+// All checks and facts of up to three structures of order n in one pass.
+hipError_t check_structures(const CheckArgs& a, hipStream_t s);
 
 // ------------------------------------------------------------- patterns
 struct SparsifySpec {
@@ -59,12 +77,6 @@ hipError_t expand_slots(int n, const int* P_cp, const int* P_cnt, const int* P_r
                         int max_lists, int max_len, hipStream_t s);
 
 // ------------------------------------------------------------------ plan
-// Per column j: E_j = sum_{l in J_j} nnz(A_k(:,l)).
-hipError_t plan_gather_count(int n, const int* S_cp, const int* S_ri, const int* Ak_cp,
-                             int* counts, hipStream_t s);
-// *total (device, preset by the caller) += sum_j E_j.
-hipError_t plan_gather_total(int n, const int* S_cp, const int* S_ri, const int* Ak_cp,
-                             unsigned long long* total, hipStream_t s);
 // Per column j: nI[j] = |I_j|, positions of the gathered A_k entries (posA,
 // at eoff[j]) and of the A_0(:,j) entries (posB aligned with A_0's entries,
 // 0xFF outside I_j).  Columns with |I_j| > 255 get nI = |I_j| and no
@@ -88,13 +100,26 @@ struct BucketTable {
     int max_rows[kMaxBuckets];
     int max_cols[kMaxBuckets];
 };
-// Stable counting sort of the columns by bucket: queue[] lists the columns
-// of bucket 0, then bucket 1, ...; bstart[b] (device, nb+1) are the bucket
-// offsets.  Columns that fit no bucket are counted in *unfit (device int,
-// may be null) and reported in the status word (may be null).
-size_t bucket_temp_bytes(int n);
-hipError_t bucket_sort(int n, const int* S_cp, const int* nI, BucketTable tab, int* queue,
-                       int* bstart, int* unfit, unsigned long long* status, void* temp, hipStream_t s);
+constexpr int kShapeRows = 128, kShapeCols = 32;   // the largest kernel class
+constexpr int kShapeCells = (kShapeRows + 1) * (kShapeCols + 1) + 1;
+// hist[|I_j| (kShapeCols + 1) + |J_j|] over the columns, larger blocks in the
+// last cell (cleared here).
+hipError_t shape_histogram(int n, const int* S_cp, const int* nI, int* hist, hipStream_t s);
+// Stable counting sort of the columns by bucket, for up to four tables at
+// once: queue[] lists the columns of bucket 0, then bucket 1, ...; bstart[b]
+// (device, nb+1) are the bucket offsets.  Columns that fit no bucket are
+// reported in the status word (may be null).
+struct BucketJob {
+    BucketTable tab;
+    int *queue, *bstart;
+};
+struct BucketJobs {
+    int count;
+    BucketJob job[4];
+};
+size_t bucket_temp_bytes(int jobs);
+hipError_t bucket_sort(int n, const int* S_cp, const int* nI, const BucketJobs& jobs, unsigned long long* status,
+                       void* temp, hipStream_t s);
 
 // --------------------------------------------------------------- numeric
 // NumericArgs, NumericVariant and the menu: sam_numeric_args.hpp.
@@ -117,7 +142,11 @@ hipError_t residual_columns(int n, int64_t nnzA, int64_t nnzM, const int* Ak_cp,
 // ----------------------------------------------------------------- apply
 // p[0 .. count) = v (a kernel, so that graph captures record no memset node)
 hipError_t fill_i32(int* p, int64_t count, int v, hipStream_t s);
-// queue = 0..n-1 and bstart = {0, n}: every column in bucket 0
+// p[0 .. 4) = {a, b, c, d} (p 16-byte aligned)
+hipError_t set4_i32(int* p, int a, int b, int c, int d, hipStream_t s);
+// queue = 0..n-1 and bstart = {0, n}: every column in bucket 0 (queue null:
+// bstart alone, which is all the numeric kernels read of a bucket that holds
+// every column)
 hipError_t identity_queue(int n, int* queue, int* bstart, hipStream_t s);
 hipError_t transpose_count(int n, const int* cp, const int* ri, int64_t nnz, int* rowcount,
                            hipStream_t s);

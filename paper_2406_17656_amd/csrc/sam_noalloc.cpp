@@ -75,9 +75,10 @@ sam_status sam_build_noalloc(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0,
         return fail(ctx, SAM_ERR_UNSUPPORTED,
                     "sam_build_noalloc: the plan of this problem needs %zu bytes, the fixed scratch holds %zu "
                     "(use sam_build with a workspace)", need, kScratchBytes);
-    if ((st = validate_csc(ctx, A0->n, A0->nnz, A0->colptr, A0->rowind, "A0", s))) return st;
     sam_plan pl;
-    if ((st = plan_init(ctx, &pl, Ak, A0, S_colptr, S_rowind, nnz_S, base, kScratchBytes, s))) return st;
+    if ((st = plan_init(ctx, &pl, Ak, A0, S_colptr, S_rowind, nnz_S, base, kScratchBytes,
+                        prec == SAM_PREC_F32_REFINE ? 1 : 0, s)))
+        return st;
     return run_numeric(&pl, Ak->val, A0->val, nullptr, 0.0, prec == SAM_PREC_F32_REFINE ? 1 : 0, 0, M_val, col_res2,
                        res2, s);
 }

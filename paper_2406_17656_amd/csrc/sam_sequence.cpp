@@ -175,8 +175,8 @@ sam_status enqueue_symbolic(sam_seq* q, int k, sam_seq::Scratch& R, const double
                                             q->plan->max_cols, q->plan->max_len_A, s));
     Combo& cb = pl->combo[q->prec][0];
     if (!cb.identity)
-        HIP_TRY(ctx, samk::bucket_sort(n, Scp, pl->nI, cb.tab, cb.queue, cb.bstart, nullptr, ctx->d_status, R.btemp,
-                                       s));
+        HIP_TRY(ctx, samk::bucket_sort(n, Scp, pl->nI, samk::BucketJobs{1, {{cb.tab, cb.queue, cb.bstart}}},
+                                       ctx->d_status, R.btemp, s));
     return SAM_OK;
 }
 
@@ -229,6 +229,7 @@ struct SeqDims {
     bool replan = false;
     int64_t nnzS = 0, Ebound = 0;
     std::vector<int64_t> lev_nnz;
+    samk::CscFacts facts{};   // of A_k's structure
 };
 
 // Layout of a sequence's memory (q == null: measure only): the structural
@@ -267,7 +268,7 @@ size_t seq_layout(Carve& cv, const SeqDims& d, sam_seq* q, PatternWs* pw, void**
         sam_seq::Scratch& R = q ? q->part[b] : dummy;
         R.off = cv.take<int64_t>((size_t)n + 1);
         R.stemp = cv.take<char>(samk::scan_temp_bytes(n));
-        R.btemp = cv.take<char>(samk::bucket_temp_bytes(n));
+        R.btemp = cv.take<char>(samk::bucket_temp_bytes(1));
         R.D = cv.take<double>((size_t)n);
         R.B_ri = cv.take<int>((size_t)lev_nnz(0));
         R.B_cnt = cv.take<int>((size_t)n);
@@ -316,12 +317,13 @@ sam_status seq_count(sam_ctx* ctx, const sam_csc* A0, const sam_csc* Ak_struct, 
     sam_status st;
     const int n = A0->n;
     if ((st = validate_csc(ctx, n, A0->nnz, A0->colptr, A0->rowind, "A0", s))) return st;
-    if ((st = validate_csc(ctx, n, Ak_struct->nnz, Ak_struct->colptr, Ak_struct->rowind, "Ak_struct", s))) return st;
+    if ((st = validate_csc(ctx, n, Ak_struct->nnz, Ak_struct->colptr, Ak_struct->rowind, "Ak_struct", s, &d->facts)))
+        return st;
     sam_pattern_spec structural = *spec;
     structural.kind = SAM_SPARSIFY_NONE;
     sam_csc skel = *Ak_struct;
     skel.val = nullptr;
-    if ((st = compute_pattern(ctx, &skel, &structural, w, res, s, levels))) return st;
+    if ((st = compute_pattern(ctx, &skel, &structural, w, d->facts, res, s, levels))) return st;
     d->nnzS = res->nnz;
     d->lev_nnz = levels->nnz;
     d->Ebound = std::max<int64_t>(d->nnzS * (int64_t)d->longest, 1);
@@ -337,7 +339,7 @@ sam_status seq_dims_base(sam_ctx* ctx, const sam_csc* A0, const sam_csc* Ak_stru
     d->nnzA = Ak_struct->nnz;
     d->nnzA0 = A0->nnz;
     d->partcap = partial_capacity(ctx);
-    return host_colptr(ctx, Ak_struct->colptr, d->n, Ak_struct->nnz, "Ak_struct", &d->longest, s);
+    return check_colptr(ctx, Ak_struct->colptr, d->n, Ak_struct->nnz, "Ak_struct", &d->longest, s);
 }
 
 }  // namespace
@@ -426,7 +428,7 @@ sam_status sam_sequence_create(sam_ctx* ctx, const sam_csc* A0, const sam_csc* A
         structural.kind = SAM_SPARSIFY_NONE;
         sam_csc skel = *Ak_struct;
         skel.val = nullptr;
-        if ((st = compute_pattern(ctx, &skel, &structural, w, &res, s, &q->levels))) return bail(st);
+        if ((st = compute_pattern(ctx, &skel, &structural, w, d.facts, &res, s, &q->levels))) return bail(st);
         if (res.nnz != d.nnzS) return bail(fail(ctx, SAM_ERR_HIP, "structural pattern changed between two counts"));
         if ((st = pattern_fill(ctx, n, res, q->S_cp, q->S_ri, s))) return bail(st);
         q->nnzS = res.nnz;
@@ -442,7 +444,7 @@ sam_status sam_sequence_create(sam_ctx* ctx, const sam_csc* A0, const sam_csc* A
         sam_plan* pl = new (std::nothrow) sam_plan();
         if (!pl) return bail(fail(ctx, SAM_ERR_NOMEM, "host allocation failed"));
         q->plan = pl;
-        if ((st = plan_init(ctx, pl, &skel, A0, q->S_cp, q->S_ri, q->nnzS, plan_mem, plan_sz, s))) return bail(st);
+        if ((st = plan_init(ctx, pl, &skel, A0, q->S_cp, q->S_ri, q->nnzS, plan_mem, plan_sz, -1, s))) return bail(st);
         if (pl->E > d.Ebound) return bail(fail(ctx, SAM_ERR_HIP, "gathered entries exceed their bound"));
     }
     if (!q->plan->combo[q->prec][0].ok)

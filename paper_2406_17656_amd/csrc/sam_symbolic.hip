@@ -79,7 +79,7 @@ k_scan_tiles(const Tin* src, int64_t n_in, int64_t* tile_sum, int* maxval) {
 template <typename Tin>
 __global__ void __launch_bounds__(kScanThreads)
 k_scan_apply(const Tin* src, int64_t n_in, int64_t N, const int64_t* tile_sum, const int64_t* tile_off,
-             int64_t* out, int* out32, int* overflow) {
+             int64_t* out, int* out32, int* overflow, int64_t* total) {
     __shared__ int64_t sh[kScanThreads / 64];
     __shared__ int64_t wsum[kScanThreads / 64];
     const int lane = wave_lane();
@@ -115,6 +115,7 @@ k_scan_apply(const Tin* src, int64_t n_in, int64_t N, const int64_t* tile_sum, c
         if (idx < N) {
             out[idx] = run;
             if (out32) out32[idx] = (int)run;
+            if (total && idx == N - 1) *total = run;
             big |= run > INT_MAX;
         }
         run += v[i];
@@ -142,7 +143,7 @@ size_t scan_temp_bytes(int64_t n) { return scan_temp_rec(n + 1) + 256; }
 // survives between calls, so the temporary memory may hold anything.
 template <typename Tin>
 static hipError_t scan_any(const Tin* src, int64_t n_in, int64_t N, int64_t* out, int* out32, int* overflow,
-                           int* maxval, void* temp, hipStream_t s) {
+                           int* maxval, int64_t* total, void* temp, hipStream_t s) {
     const int64_t nt = scan_tiles(N);
     char* p = (char*)temp;
     int64_t* tile_sum = (int64_t*)p;
@@ -152,43 +153,128 @@ static hipError_t scan_any(const Tin* src, int64_t n_in, int64_t N, int64_t* out
     if (nt > kDirectTiles) {
         tile_off = (int64_t*)p;
         p += (((nt + 1) * 8 + 255) / 256) * 256;
-        hipError_t e = scan_any<int64_t>(tile_sum, nt, nt, tile_off, nullptr, nullptr, nullptr, p, s);
+        hipError_t e = scan_any<int64_t>(tile_sum, nt, nt, tile_off, nullptr, nullptr, nullptr, nullptr, p, s);
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(k_scan_apply<Tin>, dim3((unsigned)nt), dim3(kScanThreads), 0, s, src, n_in, N, tile_sum,
-                       tile_off, out, out32, overflow);
+                       tile_off, out, out32, overflow, total);
     return hipGetLastError();
 }
 
 hipError_t scan_counts(const int* counts, int64_t n, int64_t* off, int* off32, int* overflow,
-                       void* temp, hipStream_t s, int* maxcount) {
-    return scan_any<int>(counts, n, n + 1, off, off32, overflow, maxcount, temp, s);
+                       void* temp, hipStream_t s, int* maxcount, int64_t* total) {
+    return scan_any<int>(counts, n, n + 1, off, off32, overflow, maxcount, total, temp, s);
 }
 
 // ----------------------------------------------------------------- checks
 
-__global__ void k_check_csc(int n, int nnz, const int* cp, const int* ri, int* bad) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    const int a = cp[j], b = cp[j + 1];
-    bool ok = a >= 0 && a <= b && b <= nnz;
-    if (j == 0 && a != 0) ok = false;
-    if (j == n - 1 && b != nnz) ok = false;
-    if (ok) {
-        int prev = -1;
-        for (int e = a; e < b; ++e) {
-            int r = ri[e];
-            if (r <= prev || r >= n) { ok = false; break; }
-            prev = r;
+// Every fact about a structure that the host needs before other kernels may
+// read it, in one pass (up to three structures by blockIdx.y, one block of
+// results): the first bad column, the longest column, the columns that lack
+// their diagonal entry; and, for a pattern S, the gathered entries
+// sum_l nnz(A_k(:, l)) of each column (A_k's column pointers are only read,
+// never followed, so they need not have been checked yet).
+//
+// Eight lanes per column take its entries as one contiguous run, each
+// comparing its row with the one before: a thread per column read them one
+// dependent cache line after the other.  Device-wide atomics on one line cost
+// about 20 ns each: one per wave took 59 us for the gathered total of
+// n = 262144 alone, four per block of 256 threads 56 us, so blocks are large,
+// stride over the columns, and report only what the results do not hold yet.
+// A check takes 22 us at that size (mean over the four of a one-shot map),
+// 32 us with a thread per column.
+constexpr int kCheckThreads = 1024;
+constexpr int kCheckLanes = 8;
+constexpr int kCheckCols = kCheckThreads / kCheckLanes;
+constexpr int kCheckBlocks = 256;
+
+__global__ void __launch_bounds__(kCheckThreads)
+k_check(CheckArgs a) {
+    __shared__ int sh_i[4][kCheckThreads / 64];
+    __shared__ long long sh_e[kCheckThreads / 64];
+    const CscRef m = a.m[blockIdx.y];
+    const int n = a.n;
+    const int g = threadIdx.x % kCheckLanes;
+    int bad = n, bad_cp = n, longest = 0, missing = 0;
+    long long gathered = 0;
+    for (int64_t jj = (int64_t)blockIdx.x * kCheckCols + threadIdx.x / kCheckLanes; jj < n;
+         jj += (int64_t)gridDim.x * kCheckCols) {   // whole groups of lanes
+        const int j = (int)jj;
+        const int lo = m.cp[j], hi = m.cp[j + 1];
+        bool ok = lo <= hi && !(j == 0 && lo != 0) && !(j == n - 1 && hi != m.nnz);
+        if (!ok) bad_cp = min(bad_cp, j);
+        ok &= lo >= 0 && hi <= m.nnz;
+        int e_j = 0, diag = 0;
+        if (ok && m.ri) {
+            for (int64_t e = (int64_t)lo + g; e < hi; e += kCheckLanes) {
+                const int r = m.ri[e], prev = e > lo ? m.ri[e - 1] : -1;
+                ok &= r > prev && r < n;
+                diag |= r == j;
+                if (m.gather_cp && r >= 0 && r < n) e_j += m.gather_cp[r + 1] - m.gather_cp[r];
+            }
+        }
+        if (!ok) bad = min(bad, j);
+        diag = grp_max<kCheckLanes>(diag);
+        if (m.gather_cp) e_j = grp_sum<kCheckLanes>(e_j);
+        if (g == 0) {
+            const int len = hi - lo;
+            longest = max(longest, len);
+            missing += 1 - diag;
+            gathered += e_j;
+            if (m.gather_counts) m.gather_counts[j] = e_j;
         }
     }
-    if (!ok) atomicMin(bad, j);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        bad = min(bad, __shfl_xor(bad, d));
+        bad_cp = min(bad_cp, __shfl_xor(bad_cp, d));
+        longest = max(longest, __shfl_xor(longest, d));
+        missing += __shfl_xor(missing, d);
+        gathered += __shfl_xor(gathered, d);
+    }
+    CscFacts* f = a.facts + blockIdx.y;
+    const int wv = threadIdx.x >> 6;
+    if (wave_lane() == 0) {
+        sh_i[0][wv] = bad;
+        sh_i[1][wv] = bad_cp;
+        sh_i[2][wv] = longest;
+        sh_i[3][wv] = missing;
+        sh_e[wv] = gathered;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kCheckThreads / 64; ++w) {
+            bad = min(bad, sh_i[0][w]);
+            bad_cp = min(bad_cp, sh_i[1][w]);
+            longest = max(longest, sh_i[2][w]);
+            missing += sh_i[3][w];
+            gathered += sh_e[w];
+        }
+        if (bad < n) atomicMin(&f->bad, bad);
+        if (bad_cp < n) atomicMin(&f->bad_cp, bad_cp);
+        // k_check_init put a column's length here, so most blocks have nothing
+        // longer (a stale read is at most too small: an atomic for nothing)
+        if (longest > __hip_atomic_load(&f->longest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+            atomicMax(&f->longest, longest);
+        if (missing) atomicAdd(&f->missing, missing);
+        if (m.gather_cp && gathered != 0) atomicAdd(a.total, (unsigned long long)gathered);
+    }
 }
 
-hipError_t check_csc(int n, int nnz, const int* cp, const int* ri, int* bad, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_check_csc, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, n, nnz, cp, ri,
-                       bad);
+__global__ void k_check_init(CheckArgs a) {
+    const int i = threadIdx.x;
+    if (i < a.count) {
+        const int mid = a.n / 2;   // < n
+        a.facts[i] = CscFacts{a.n, a.n, max(a.m[i].cp[mid + 1] - a.m[i].cp[mid], 0), 0};
+    }
+    if (i == 0) *a.total = 0;
+}
+
+hipError_t check_structures(const CheckArgs& a, hipStream_t s) {
+    if (a.n <= 0 || a.count <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_check_init, dim3(1), dim3(64), 0, s, a);
+    const unsigned nb = (unsigned)std::min<int64_t>(ceil_div(a.n, kCheckCols), kCheckBlocks);
+    hipLaunchKernelGGL(k_check, dim3(nb, (unsigned)a.count), dim3(kCheckThreads), 0, s, a);
     return hipGetLastError();
 }
 
@@ -653,49 +739,6 @@ hipError_t expand_slots(int n, const int* P_cp, const int* P_cnt, const int* P_r
 
 // ------------------------------------------------------------------ plan
 
-__global__ void k_gather_count(int n, const int* S_cp, const int* S_ri, const int* Ak_cp, int* counts) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    int s = 0;
-    for (int e = S_cp[j]; e < S_cp[j + 1]; ++e) {
-        int l = S_ri[e];
-        if (l >= 0 && l < n) s += Ak_cp[l + 1] - Ak_cp[l];
-    }
-    counts[j] = s;
-}
-
-hipError_t plan_gather_count(int n, const int* S_cp, const int* S_ri, const int* Ak_cp, int* counts,
-                             hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather_count, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, n, S_cp, S_ri,
-                       Ak_cp, counts);
-    return hipGetLastError();
-}
-
-// *total += sum_j sum_{l in S(:,j)} nnz(A_k(:,l)): a column per thread, the
-// wave's sum added once (integer, so the order does not matter).
-__global__ void k_gather_total(int n, const int* S_cp, const int* S_ri, const int* Ak_cp,
-                               unsigned long long* total) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    long long s = 0;
-    if (j < n) {
-        for (int e = S_cp[j]; e < S_cp[j + 1]; ++e) {
-            const int l = S_ri[e];
-            if (l >= 0 && l < n) s += Ak_cp[l + 1] - Ak_cp[l];
-        }
-    }
-    for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d);
-    if ((threadIdx.x & 63) == 0 && s != 0) atomicAdd(total, (unsigned long long)s);
-}
-
-hipError_t plan_gather_total(int n, const int* S_cp, const int* S_ri, const int* Ak_cp, unsigned long long* total,
-                             hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gather_total, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, s, n, S_cp, S_ri, Ak_cp,
-                       total);
-    return hipGetLastError();
-}
-
 // Row set I_j of every column as a bitmap sweep; every gathered A_k entry (in
 // the order: entries of A_k(:, J_j[0]), then of A_k(:, J_j[1]), ...) gets its
 // rank inside I_j, and so does every entry of A_0(:, j) (0xFF when its row is
@@ -718,6 +761,49 @@ hipError_t plan_positions_slots(int n, const int* S_cp, const int* S_cnt, const 
     a.counts = nI; a.eoff = eoff; a.posA = posA; a.A0_cp = A0_cp; a.A0_ri = A0_ri; a.posB = posB;
     a.cP_cp = cS_cp; a.cP_ri = cS_ri;
     return launch_union<kModePositions>(a, max_lists, max_len, s);
+}
+
+// Shapes of the column problems: hist[r * (kShapeCols + 1) + c] counts the
+// columns with |I_j| = r <= kShapeRows and |J_j| = c <= kShapeCols, the cell
+// after the last one the larger ones.  Everything the host decides on (bucket
+// sizes under any table, the largest block, the flop counts) follows from
+// these counts, so 17 KB come back instead of two n-sized arrays.
+constexpr int kShapeThreads = 256;
+
+__global__ void __launch_bounds__(kShapeThreads)
+k_shapes(int n, const int* S_cp, const int* nI, int* hist) {
+    __shared__ int h[kShapeCells];
+    for (int i = threadIdx.x; i < kShapeCells; i += kShapeThreads) h[i] = 0;
+    __syncthreads();
+    const int64_t stride = (int64_t)gridDim.x * kShapeThreads;
+    for (int64_t c0 = (int64_t)blockIdx.x * kShapeThreads; c0 < n; c0 += stride) {   // the same trips for a wave
+        const int64_t jj = c0 + threadIdx.x;
+        int cell = -1;
+        if (jj < n) {
+            const int j = (int)jj;
+            const int r = nI[j], c = S_cp[j + 1] - S_cp[j];
+            cell = r <= kShapeRows && c <= kShapeCols ? r * (kShapeCols + 1) + c : kShapeCells - 1;
+        }
+        // one LDS atomic per distinct shape of the wave (most columns share one)
+        unsigned long long left = __ballot(cell >= 0);
+        while (left) {
+            const int lead = __shfl(cell, __ffsll((unsigned long long)left) - 1);
+            const unsigned long long same = __ballot(cell == lead);
+            if (wave_lane() == __ffsll((unsigned long long)same) - 1) atomicAdd(&h[lead], __popcll(same));
+            left &= ~same;
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kShapeCells; i += kShapeThreads)
+        if (h[i]) atomicAdd(&hist[i], h[i]);
+}
+
+hipError_t shape_histogram(int n, const int* S_cp, const int* nI, int* hist, hipStream_t s) {
+    hipError_t e = fill_i32(hist, kShapeCells, 0, s);
+    if (e != hipSuccess || n <= 0) return e;
+    const unsigned nb = (unsigned)std::min<int64_t>(ceil_div(n, kShapeThreads), 256);
+    hipLaunchKernelGGL(k_shapes, dim3(nb), dim3(kShapeThreads), 0, s, n, S_cp, nI, hist);
+    return hipGetLastError();
 }
 
 // --------------------------------------------------------------- buckets
@@ -747,8 +833,10 @@ static int64_t range_len(int n, int nb) {
 }
 
 __global__ void __launch_bounds__(kBucketThreads)
-k_bucket_hist(int n, int64_t len, const int* S_cp, const int* nI, BucketTable tab, int* hist, int* unfit,
+k_bucket_hist(int n, int64_t len, const int* S_cp, const int* nI, BucketJobs jobs, int* hist_all,
               unsigned long long* status) {
+    const BucketTable& tab = jobs.job[blockIdx.y].tab;
+    int* hist = hist_all + (size_t)blockIdx.y * kBucketBlocks * kMaxBuckets;
     __shared__ int h[kMaxBuckets];
     if (threadIdx.x < kMaxBuckets) h[threadIdx.x] = 0;
     __syncthreads();
@@ -760,10 +848,7 @@ k_bucket_hist(int n, int64_t len, const int* S_cp, const int* nI, BucketTable ta
         if (jj < j1) {
             const int j = (int)jj;
             b = bucket_of(nI[j], S_cp[j + 1] - S_cp[j], tab);
-            if (b < 0) {
-                if (unfit) atomicAdd(unfit, 1);
-                if (status) report(status, j, kStUnsupported);
-            }
+            if (b < 0 && status) report(status, j, kStUnsupported);
         }
         // per-wave counts (one LDS atomic per wave and bucket, not per column)
         for (int k = 0; k < tab.nb; ++k) {
@@ -776,8 +861,11 @@ k_bucket_hist(int n, int64_t len, const int* S_cp, const int* nI, BucketTable ta
 }
 
 __global__ void __launch_bounds__(kBucketThreads)
-k_bucket_scatter(int n, int64_t len, const int* S_cp, const int* nI, BucketTable tab, const int* hist,
-                 int* queue, int* bstart) {
+k_bucket_scatter(int n, int64_t len, const int* S_cp, const int* nI, BucketJobs jobs, const int* hist_all) {
+    const BucketTable& tab = jobs.job[blockIdx.y].tab;
+    int* queue = jobs.job[blockIdx.y].queue;
+    int* bstart = jobs.job[blockIdx.y].bstart;
+    const int* hist = hist_all + (size_t)blockIdx.y * kBucketBlocks * kMaxBuckets;
     __shared__ int tot[kMaxBuckets], pre[kMaxBuckets], base[kMaxBuckets + 1];
     __shared__ int wcount[kBucketThreads / 64][kMaxBuckets];
     const int nblk = gridDim.x;
@@ -844,20 +932,18 @@ k_bucket_scatter(int n, int64_t len, const int* S_cp, const int* nI, BucketTable
 }
 
 
-size_t bucket_temp_bytes(int n) {
-    return (size_t)kBucketBlocks * kMaxBuckets * sizeof(int) + 512;
-}
+size_t bucket_temp_bytes(int jobs) { return (size_t)jobs * kBucketBlocks * kMaxBuckets * sizeof(int) + 512; }
 
-hipError_t bucket_sort(int n, const int* S_cp, const int* nI, BucketTable tab, int* queue, int* bstart,
-                       int* unfit, unsigned long long* status, void* temp, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const int64_t len = range_len(n, tab.nb);
-    const int nblk = (int)ceil_div(n, len);
+hipError_t bucket_sort(int n, const int* S_cp, const int* nI, const BucketJobs& jobs, unsigned long long* status,
+                       void* temp, hipStream_t s) {
+    if (n <= 0 || jobs.count <= 0) return hipSuccess;
+    int nb = 0;
+    for (int k = 0; k < jobs.count; ++k) nb = std::max(nb, jobs.job[k].tab.nb);
+    const int64_t len = range_len(n, nb);
+    const dim3 grid((unsigned)ceil_div(n, len), (unsigned)jobs.count);
     int* hist = (int*)temp;
-    hipLaunchKernelGGL(k_bucket_hist, dim3(nblk), dim3(kBucketThreads), 0, s, n, len, S_cp, nI, tab, hist, unfit,
-                       status);
-    hipLaunchKernelGGL(k_bucket_scatter, dim3(nblk), dim3(kBucketThreads), 0, s, n, len, S_cp, nI, tab, hist,
-                       queue, bstart);
+    hipLaunchKernelGGL(k_bucket_hist, grid, dim3(kBucketThreads), 0, s, n, len, S_cp, nI, jobs, hist, status);
+    hipLaunchKernelGGL(k_bucket_scatter, grid, dim3(kBucketThreads), 0, s, n, len, S_cp, nI, jobs, hist);
     return hipGetLastError();
 }
 

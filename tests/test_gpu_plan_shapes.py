@@ -1,0 +1,104 @@
+"""What a plan knows of its column problems (device counts, host decisions)
+against numpy: gathered entries, largest block, columns per class and flop
+counts, at sizes around the blocks of the counting kernels, on ragged patterns
+with one class and with many, and on blocks beyond every class."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import pde_inputs as P
+from parity_util import TOL, colmax_rel
+
+pytestmark = pytest.mark.gpu
+
+
+def banded(n, rng, widths):
+    """Column j holds its diagonal and widths[j] - 1 other rows nearby."""
+    rows, cp = [], np.zeros(n + 1, dtype=np.int32)
+    for j in range(n):
+        lo, hi = max(0, j - 12), min(n, j + 13)
+        others = np.setdiff1d(np.arange(lo, hi), [j])
+        r = np.sort(np.append(rng.choice(others, size=min(widths[j] - 1, others.size), replace=False), j))
+        rows.append(r)
+        cp[j + 1] = cp[j] + r.size
+    ri = np.concatenate(rows).astype(np.int32)
+    val = rng.standard_normal(ri.size) + 6.0 * (ri == np.repeat(np.arange(n), np.diff(cp)))
+    return P.CSC(n, cp, ri, val)
+
+
+def shapes(A, S_cp, S_ri):
+    r, c, e = [], [], 0
+    for j in range(A.n):
+        J = S_ri[S_cp[j]:S_cp[j + 1]]
+        runs = [A.rowind[A.colptr[l]:A.colptr[l + 1]] for l in J]
+        r.append(np.unique(np.concatenate(runs)).size if runs else 0)
+        c.append(J.size)
+        e += sum(x.size for x in runs)
+    return np.array(r), np.array(c), e
+
+
+@pytest.mark.parametrize("n,widest", [(1, 1), (255, 2), (256, 4), (257, 5), (2049, 6), (700, 1)])
+def test_plan_facts(n, widest):
+    from paper_2406_17656_amd import Context, DeviceCSC, autotune
+    rng = np.random.default_rng(n)
+    Ak = banded(n, rng, rng.integers(1, widest + 1, n))
+    A0 = banded(n, rng, rng.integers(1, 4, n))
+    S = banded(n, rng, rng.integers(1, 2 * widest + 1, n))
+    ctx = Context(0)
+    dAk, dA0 = DeviceCSC.from_host(Ak), DeviceCSC.from_host(A0)
+    cp, ri = torch.as_tensor(S.colptr).cuda(), torch.as_tensor(S.rowind).cuda()
+    plan = ctx.plan(dAk, dA0, cp, ri)
+    r, c, e = shapes(Ak, S.colptr, S.rowind)
+    info = plan.info()
+    assert (info["max_rows"], info["max_cols"], info["gathered"]) == (r.max(), c.max(), e)
+    assert sum(info["bucket_cols"]) == n
+    order = list(range(len(autotune.menu("f32"))))
+    for select in (order, order[::-1]):
+        plan.select(select, "f32")
+        left = np.ones(n, dtype=bool)
+        want = []
+        for v in (autotune.menu("f32")[i] for i in select):
+            fits = left & (r <= v["max_rows"]) & (c <= v["NC"])
+            want.append(int(fits.sum()))
+            left &= ~fits
+        assert plan.info()["bucket_cols"][:len(want)] == want
+        M, _, _ = plan.build(dAk.val, dA0.val, "f32")
+        ctx.sync_status()
+        Mo, _, _, _ = O.sam_build(Ak, A0, O.Pattern(n, S.colptr, S.rowind))
+        assert colmax_rel(M.cpu().numpy().astype(np.float64), Mo, S.colptr)[0] <= TOL["f32"]
+    rf, cf = r.astype(float), c.astype(float)
+    qr = 2 * rf * cf ** 2 - 2 / 3 * cf ** 3 + 4 * rf * cf
+    cost = plan.cost("f32")
+    np.testing.assert_allclose([cost["flops32"], cost["flops64"]],
+                               [(qr + 3 * cf ** 2).sum(), (6 * rf * cf + 2 * rf).sum()], rtol=1e-12)
+    np.testing.assert_allclose(plan.cost("f64")["flops64"], (qr + cf ** 2 + 2 * rf * cf + 2 * rf).sum(), rtol=1e-12)
+    plan.close()
+    ctx.close()
+
+
+def test_blocks_beyond_every_class():
+    """A dense column of S: the plan is made, says how large the block is, and
+    refuses to build with the class limit in the message."""
+    from paper_2406_17656_amd import Context, DeviceCSC, SamError
+    n = 300
+    A0h, Ash = P.config2(m=20, nmat=2)
+    n = A0h.n
+    cp = np.arange(n + 1, dtype=np.int32)
+    cp[11:] += n - 1
+    ri = np.concatenate([np.arange(10), np.arange(n), np.arange(11, n)]).astype(np.int32)
+    ctx = Context(0)
+    dAk, dA0 = DeviceCSC.from_host(Ash[0]), DeviceCSC.from_host(A0h)
+    plan = ctx.plan(dAk, dA0, torch.as_tensor(cp).cuda(), torch.as_tensor(ri).cuda())
+    info = plan.info()
+    assert info["max_rows"] == n and info["max_cols"] == n
+    r, c, e = shapes(Ash[0], cp, ri)
+    rf, cf = r.astype(float), c.astype(float)
+    np.testing.assert_allclose(plan.cost("f32")["flops64"], (6 * rf * cf + 2 * rf).sum(), rtol=1e-12)
+    for prec in ("f32", "f64"):
+        with pytest.raises(SamError, match=f"1 columns exceed .*max .I_j. = {n}, max .J_j. = {n}"):
+            plan.build(dAk.val, dA0.val, prec)
+    with pytest.raises(SamError, match="selection rejected"):
+        plan.select([0, 1, 2], "f32")
+    plan.close()
+    ctx.close()
