@@ -1064,7 +1064,11 @@ const NumericVariant kMenu[] = {
     SAM_VARIANT(double, 0, 2, 8, 8, 4, 3, false),
     SAM_VARIANT(double, 0, 4, 7, 13, 2, 2, false),
     SAM_VARIANT(double, 0, 8, 4, 16, 2, 1, false),
-    SAM_VARIANT(double, 0, 32, 2, 25, 1, 1, false),
+    // 64 x 25 on 16 lanes: one wave per SIMD (its block is 200 VGPRs, the rest
+    // in AGPRs), as on 32 lanes, but a group of four problems takes the time
+    // of a group of two there (an FP64 sum over 32 lanes is some 18
+    // instructions beside four FMAs per column): 64^3 level 2, 3.77 -> 1.86 ms
+    SAM_VARIANT(double, 0, 16, 4, 25, 1, 1, false),
     SAM_VARIANT(double, 0, 64, 2, 32, 1, 1, false),
     SAM_VARIANT(double, 0, 1, 13, 5, 1, 5, false),
     SAM_VARIANT(double, 0, 8, 4, 13, 2, 1, false),
