@@ -236,7 +236,8 @@ sam_status sam_plan_destroy(sam_plan* plan);
 
 /* Shape statistics of a plan (host outputs, any may be NULL): number of
  * columns, max |I_j|, max |J_j|, total gathered entries sum_j nnz(A_k(:,J_j)),
- * and the column count of each of up to 16 buckets (bucket_cols[16]). */
+ * and the column count of each of up to 16 buckets (bucket_cols[16]: the FP32
+ * plain classes in use, in their order). */
 sam_status sam_plan_info(const sam_plan* plan, int32_t* n, int32_t* max_rows, int32_t* max_cols,
                          int64_t* gathered, int32_t* nbuckets, int32_t* bucket_cols);
 
@@ -261,7 +262,10 @@ sam_status sam_plan_cost_weighted(const sam_plan* plan, int32_t prec, int32_t ba
                                   double* flops64);
 
 /* The numeric kernel variants compiled for `prec` (weighted = 0: plain maps,
- * 1: soft-weighted), in their default order.  Each serves column blocks of
+ * 1: soft-weighted).  Until sam_plan_select chooses others, a plan's plain
+ * builds use the variants that its shapes make cheapest together; weighted
+ * builds and sequences with a sparsification rule take a column's first
+ * fitting one in this order.  Each serves column blocks of
  * at most G*R rows (G*R - |J_j| penalty rows aside when weighted) and NC
  * columns; G lanes of a wave64 own one column problem, TC columns are staged
  * per LDS pass.  Host outputs of `capacity` entries (any may be NULL);

@@ -222,10 +222,8 @@ hipError_t residual_columns(int n, int64_t nnzA, int64_t nnzM, const int* Ak_cp,
     // 4057 / 1962.
     const bool narrow = nnzA <= (int64_t)7 * n && nnzM <= (int64_t)14 * n;
     const int cols = narrow ? 8 : 4;
-    // up to 12 one-wave blocks per CU are resident; a multiple of 8 blocks, so
-    // that neighbouring ranges share an XCD
-    int grid = (int)std::min<int64_t>(((int64_t)n + cols - 1) / cols, 256 * 12);
-    if (grid >= 64) grid = grid / 8 * 8;
+    // up to 12 one-wave blocks per CU are resident
+    const int grid = launch_grid(((int64_t)n + cols - 1) / cols, 256 * 12);
     if (narrow)
         hipLaunchKernelGGL((k_residual_columns<8, 16>), dim3(grid), dim3(64), 0, s, n, Ak_cp, Ak_ri, Ak_v, A0_cp,
                            A0_ri, A0_v, M_cp, M_ri, M_v, m_is_f32, col_out, status);

@@ -127,9 +127,8 @@ sam_status sam_backward(sam_plan* plan, const double* Ak_val, const double* A0_v
         if (cnt <= 0) continue;
         const samk::NumericVariant* v = cb.variants[k];
         a.bucket = cb.slot.empty() ? (int)k : cb.slot[k];
-        int groups = (cnt + v->per_wave() - 1) / v->per_wave();
-        int grid = std::min(groups, ctx->CUs * 16);
-        if (grid >= 64) grid = grid / 8 * 8;
+        const int groups = (cnt + v->per_wave() - 1) / v->per_wave();
+        const int grid = samk::launch_grid(groups, ctx->CUs * 16);
         HIP_TRY(ctx, v->launch_backward(a, grid, s));
     }
     HIP_TRY(ctx, samk::backward_scatter(plan->n, plan->Ak_cp, b.ST_rowptr, b.ST_perm, b.segoff, b.contrib, gAk, s));

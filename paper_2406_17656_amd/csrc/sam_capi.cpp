@@ -337,6 +337,71 @@ int class_counts(const sam_plan* pl, const BucketTable& tab, std::vector<int>* c
     return unfit;
 }
 
+// The classes that serve the plan's columns at the least modelled time, the
+// cheapest per column first.  A launch costs a round of its class however few
+// columns it has, and the launches of a build run one after another, so a
+// class earns its place only if its columns cost more in the next wider one:
+// all the 5-point boundary columns in classes of their own took 147 us of
+// launches for the 512^2 level-2 map, 104 us in the interior's class; the 64^2
+// nine-point map took eleven launches and 227 us, now 26 us in one.  Starting
+// from every class, the one whose loss helps most is left out until none
+// does.  Columns fall into few distinct sets of fitting classes, so this is
+// some thousand operations.  Empty: some column fits no class.
+std::vector<const NumericVariant*> fitted_order(const sam_plan* pl, int prec) {
+    constexpr double kLaunchUs = 2.0;   // from one launch's end to the next one's start
+    std::vector<const NumericVariant*> all;
+    menu_table(prec, 0, &all);
+    std::stable_sort(all.begin(), all.end(),
+                     [](const NumericVariant* a, const NumericVariant* b) { return a->col_ns < b->col_ns; });
+    if (pl->shapes.empty() || pl->shapes[samk::kShapeCells - 1] > 0) return {};
+    std::vector<std::pair<unsigned, int>> sets;   // fitting classes (bits), columns
+    for (int r = 0; r <= samk::kShapeRows; ++r)
+        for (int c = 0; c <= samk::kShapeCols; ++c) {
+            const int cnt = pl->shapes[(size_t)r * (samk::kShapeCols + 1) + c];
+            if (!cnt) continue;
+            unsigned fits = 0;
+            for (size_t v = 0; v < all.size(); ++v)
+                if (r <= all[v]->max_rows() && c <= all[v]->NC) fits |= 1u << v;
+            if (!fits) return {};
+            auto it = std::find_if(sets.begin(), sets.end(), [&](const auto& p) { return p.first == fits; });
+            if (it == sets.end()) sets.emplace_back(fits, cnt);
+            else it->second += cnt;
+        }
+    std::vector<int> counts(all.size());
+    auto cost = [&](unsigned use) {   // us, or -1 where a column fits none
+        std::fill(counts.begin(), counts.end(), 0);
+        for (const auto& p : sets) {
+            if (!(p.first & use)) return -1.0;
+            counts[(size_t)__builtin_ctz(p.first & use)] += p.second;
+        }
+        double t = 0.0;
+        for (size_t v = 0; v < all.size(); ++v)
+            if (counts[v]) t += kLaunchUs + std::max<double>(all[v]->round_us, 1e-3 * all[v]->col_ns * counts[v]);
+        return t;
+    };
+    unsigned use = (1u << all.size()) - 1u;
+    double now = cost(use);
+    for (bool better = true; better;) {
+        better = false;
+        unsigned best = use;
+        for (size_t v = 0; v < all.size(); ++v) {
+            if (!(use >> v & 1u)) continue;
+            const double t = cost(use & ~(1u << v));
+            if (t >= 0.0 && t < now) {
+                now = t;
+                best = use & ~(1u << v);
+                better = true;
+            }
+        }
+        use = best;
+    }
+    cost(use);
+    std::vector<const NumericVariant*> order;
+    for (size_t v = 0; v < all.size(); ++v)
+        if (counts[v]) order.push_back(all[v]);
+    return order;
+}
+
 void plan_combo_with(sam_plan* pl, int prec, int weighted, const std::vector<const NumericVariant*>& vars) {
     Combo& cb = pl->combo[prec][weighted];
     cb.variants = vars;
@@ -473,7 +538,7 @@ void plan_shape_stats(sam_plan* pl) {
 
 sam_status plan_init(sam_ctx* ctx, sam_plan* pl, const sam_csc* Ak, const sam_csc* A0, const int32_t* S_colptr,
                      const int32_t* S_rowind, int64_t nnz_S, void* mem, size_t mem_bytes, int only_prec,
-                     hipStream_t s) {
+                     bool fitted, hipStream_t s) {
     const int n = Ak->n;
     pl->ctx = ctx;
     pl->n = n;
@@ -549,7 +614,8 @@ sam_status plan_init(sam_ctx* ctx, sam_plan* pl, const sam_csc* Ak, const sam_cs
             for (int w = 0; w < 2; ++w) {
                 if (only_prec >= 0 && (p != only_prec || w != 0)) continue;
                 std::vector<const NumericVariant*> vars;
-                menu_table(p, w, &vars);
+                if (fitted && w == 0) vars = fitted_order(pl, p);
+                if (vars.empty()) menu_table(p, w, &vars);
                 plan_combo_with(pl, p, w, vars);
                 combos[count++] = &pl->combo[p][w];
             }
@@ -597,12 +663,11 @@ sam_status run_numeric(sam_plan* pl, const double* Ak_val, const double* A0_val,
         if (cnt <= 0) continue;
         const NumericVariant* v = cb.variants[b];
         a.bucket = cb.slot.empty() ? (int)b : cb.slot[b];
-        int groups = (cnt + v->per_wave() - 1) / v->per_wave();
+        const int groups = (cnt + v->per_wave() - 1) / v->per_wave();
         // one round of resident blocks for the plain maps; the weighted
         // forms run faster over two rounds (as the adjoint's launch)
         const int per_cu = weighted ? std::min(16, 2 * resident_blocks(ctx, v)) : resident_blocks(ctx, v);
-        int grid = std::min(groups, ctx->CUs * per_cu);
-        if (grid >= 64) grid = grid / 8 * 8;
+        const int grid = samk::launch_grid(groups, ctx->CUs * per_cu);
         if (res2 && parts + grid > pl->partcap)
             return fail(ctx, SAM_ERR_HIP, "partial-sum buffer too small (%d blocks)", parts + grid);
         a.part_base = parts;
@@ -880,7 +945,7 @@ static sam_status create_plan(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0
     hipStream_t s = S(stream);
     sam_plan* pl = new (std::nothrow) sam_plan();
     if (!pl) return fail(ctx, SAM_ERR_NOMEM, "host allocation failed");
-    if ((st = plan_init(ctx, pl, Ak, A0, S_colptr, S_rowind, nnz_S, mem, mem_bytes, only_prec, s))) {
+    if ((st = plan_init(ctx, pl, Ak, A0, S_colptr, S_rowind, nnz_S, mem, mem_bytes, only_prec, true, s))) {
         delete pl;
         return st;
     }

@@ -1028,58 +1028,60 @@ constexpr LaunchFn backward_launcher() {
     else return nullptr;
 }
 
-#define SAM_VARIANT(TQ, PREC, G, R, NC, TC, LPL, W)                                                \
+#define SAM_VARIANT(TQ, PREC, G, R, NC, TC, LPL, W, ROUND_US, COL_NS)                              \
     NumericVariant{PREC, G, R, NC, W, TC, LPL, &launch_numeric<TQ, G, R, NC, TC, LPL, W ? 1 : 0>, \
                    backward_launcher<TQ, G, R, NC, TC, LPL, W>(),                             \
-                   &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, W ? 1 : 0>}
+                   &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, W ? 1 : 0>, ROUND_US, COL_NS}
 
 // Menu per precision, cheapest first.  Shapes of the workloads: 2D 5-point
 // level 1 (13 x 5), level 2 (25 x 13); 3D 7-point level 2 (63 x 25); 2D
 // 9-point level 2 with thresholds (ragged, mostly 20..45 x 5..20, at most
-// 49 x 24); weighted 3D (63 x 25 with 25 penalty rows: 64 rows in two stages).  The first fitting entry of a (precision,
-// weighting) group serves a column by default; later entries of the same
-// shape class are alternatives the autotuner can put in front
-// (sam_plan_select).  The FP32 classes between 36 x 10 and 48 x 24 follow the
-// ragged 9-point distribution: each halves the padded work of the columns
-// it takes from the next wider class.
+// 49 x 24); weighted 3D (63 x 25 with 25 penalty rows: 64 rows in two stages).
+// An explicit order (sam_plan_select, the autotuner) serves a column by its
+// first fitting entry; a plan of known shapes otherwise takes the entries that
+// cost least together (fitted_order), by the last two figures: the time of a
+// launch of 1024 columns, and per column of 262144 (64^3 and 512^2 maps).
+// The FP32 classes between 36 x 10 and 48 x 24 follow the ragged 9-point
+// distribution: each halves the padded work of the columns it takes from the
+// next wider class.
 const NumericVariant kMenu[] = {
     // FP32 + refinement
-    SAM_VARIANT(float, 1, 2, 8, 5, 4, 3, false),
-    SAM_VARIANT(float, 1, 2, 8, 8, 4, 3, false),
-    SAM_VARIANT(float, 1, 4, 9, 10, 1, 2, false),   // ragged 9-point / thresholded blocks
-    SAM_VARIANT(float, 1, 4, 9, 12, 1, 2, false),
-    SAM_VARIANT(float, 1, 4, 7, 13, 1, 2, false),
-    SAM_VARIANT(float, 1, 4, 8, 16, 2, 2, false),
-    SAM_VARIANT(float, 1, 8, 5, 14, 1, 2, false),
-    SAM_VARIANT(float, 1, 8, 6, 16, 1, 2, false),
-    SAM_VARIANT(float, 1, 8, 5, 20, 1, 2, false),
-    SAM_VARIANT(float, 1, 8, 6, 24, 1, 2, false),
-    SAM_VARIANT(float, 1, 16, 4, 25, 1, 1, false),
-    SAM_VARIANT(float, 1, 32, 4, 32, 1, 1, false),
-    SAM_VARIANT(float, 1, 1, 13, 5, 1, 5, false),   // one problem per lane, no reductions
-    SAM_VARIANT(float, 1, 8, 4, 13, 2, 1, false),
-    SAM_VARIANT(float, 1, 32, 2, 25, 1, 1, false),
+    SAM_VARIANT(float, 1, 2, 8, 5, 4, 3, false, 7.f, 0.123f),
+    SAM_VARIANT(float, 1, 2, 8, 8, 4, 3, false, 8.2f, 0.154f),
+    SAM_VARIANT(float, 1, 4, 9, 10, 1, 2, false, 9.9f, 0.32f),   // ragged 9-point / thresholded blocks
+    SAM_VARIANT(float, 1, 4, 9, 12, 1, 2, false, 11.3f, 0.39f),
+    SAM_VARIANT(float, 1, 4, 7, 13, 1, 2, false, 11.3f, 0.39f),
+    SAM_VARIANT(float, 1, 4, 8, 16, 2, 2, false, 15.5f, 0.634f),
+    SAM_VARIANT(float, 1, 8, 5, 14, 1, 2, false, 13.1f, 0.843f),
+    SAM_VARIANT(float, 1, 8, 6, 16, 1, 2, false, 15.5f, 1.05f),
+    SAM_VARIANT(float, 1, 8, 5, 20, 1, 2, false, 18.5f, 1.48f),
+    SAM_VARIANT(float, 1, 8, 6, 24, 1, 2, false, 24.6f, 2.03f),
+    SAM_VARIANT(float, 1, 16, 4, 25, 1, 1, false, 23.3f, 3.26f),
+    SAM_VARIANT(float, 1, 32, 4, 32, 1, 1, false, 49.8f, 13.5f),
+    SAM_VARIANT(float, 1, 1, 13, 5, 1, 5, false, 7.2f, 0.077f),   // one problem per lane, no reductions
+    SAM_VARIANT(float, 1, 8, 4, 13, 2, 1, false, 10.1f, 0.572f),
+    SAM_VARIANT(float, 1, 32, 2, 25, 1, 1, false, 32.3f, 6.4f),
     // FP64
-    SAM_VARIANT(double, 0, 2, 8, 5, 4, 3, false),
-    SAM_VARIANT(double, 0, 2, 8, 8, 4, 3, false),
-    SAM_VARIANT(double, 0, 4, 7, 13, 2, 2, false),
-    SAM_VARIANT(double, 0, 8, 4, 16, 2, 1, false),
+    SAM_VARIANT(double, 0, 2, 8, 5, 4, 3, false, 6.6f, 0.161f),
+    SAM_VARIANT(double, 0, 2, 8, 8, 4, 3, false, 8.1f, 0.245f),
+    SAM_VARIANT(double, 0, 4, 7, 13, 2, 2, false, 11.8f, 0.62f),
+    SAM_VARIANT(double, 0, 8, 4, 16, 2, 1, false, 13.1f, 1.42f),
     // 64 x 25 on 16 lanes: one wave per SIMD (its block is 200 VGPRs, the rest
     // in AGPRs), as on 32 lanes, but a group of four problems takes the time
     // of a group of two there (an FP64 sum over 32 lanes is some 18
     // instructions beside four FMAs per column): 64^3 level 2, 3.77 -> 1.86 ms
-    SAM_VARIANT(double, 0, 16, 4, 25, 1, 1, false),
-    SAM_VARIANT(double, 0, 64, 2, 32, 1, 1, false),
-    SAM_VARIANT(double, 0, 1, 13, 5, 1, 5, false),
-    SAM_VARIANT(double, 0, 8, 4, 13, 2, 1, false),
+    SAM_VARIANT(double, 0, 16, 4, 25, 1, 1, false, 29.f, 6.77f),
+    SAM_VARIANT(double, 0, 64, 2, 32, 1, 1, false, 60.6f, 54.8f),
+    SAM_VARIANT(double, 0, 1, 13, 5, 1, 5, false, 6.7f, 0.103f),
+    SAM_VARIANT(double, 0, 8, 4, 13, 2, 1, false, 11.1f, 0.843f),
     // soft-weighted (stacked penalty rows)
-    SAM_VARIANT(float, 1, 4, 7, 13, 2, 2, true),
-    SAM_VARIANT(float, 1, 16, 4, 25, 1, 1, true),
-    SAM_VARIANT(float, 1, 32, 3, 25, 1, 1, true),
-    SAM_VARIANT(float, 1, 64, 2, 32, 1, 1, true),
-    SAM_VARIANT(double, 0, 4, 8, 13, 2, 2, true),
-    SAM_VARIANT(double, 0, 64, 2, 25, 1, 1, true),
-    SAM_VARIANT(double, 0, 64, 2, 32, 1, 1, true),
+    SAM_VARIANT(float, 1, 4, 7, 13, 2, 2, true, 0, 0),
+    SAM_VARIANT(float, 1, 16, 4, 25, 1, 1, true, 0, 0),
+    SAM_VARIANT(float, 1, 32, 3, 25, 1, 1, true, 0, 0),
+    SAM_VARIANT(float, 1, 64, 2, 32, 1, 1, true, 0, 0),
+    SAM_VARIANT(double, 0, 4, 8, 13, 2, 2, true, 0, 0),
+    SAM_VARIANT(double, 0, 64, 2, 25, 1, 1, true, 0, 0),
+    SAM_VARIANT(double, 0, 64, 2, 32, 1, 1, true, 0, 0),
 };
 
 }  // namespace

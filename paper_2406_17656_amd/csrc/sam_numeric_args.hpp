@@ -57,11 +57,24 @@ struct NumericVariant {
     hipError_t (*launch)(const NumericArgs&, int grid, hipStream_t);
     hipError_t (*launch_backward)(const NumericArgs&, int grid, hipStream_t);  // weighted only
     int (*blocks_per_cu)();  // resident one-wave blocks per CU of the forward kernel (0: unknown)
+    // measured cost of a plain launch (0: not measured): one round of blocks
+    // (us), and a column once the GPU is full (ns)
+    float round_us, col_ns;
     int max_rows() const { return G * R; }
     int per_wave() const { return 64 / G; }
 };
 // The compiled menu, ordered from the cheapest per column to the most
 // general for each precision.
 const NumericVariant* numeric_menu(int* count);
+
+// Blocks of a launch over `groups` groups, at most `cap` (a multiple of 8):
+// from 64 on a multiple of 8, as the XCD-aware block order wants, rounded up
+// (a block without a group ends at once).  Rounded down, a launch of 125
+// groups ran 120 blocks, five of them for two rounds: 1000 columns took 23.5
+// us where 1024 took 13.1.
+inline int launch_grid(int64_t groups, int cap) {
+    const int64_t up = groups >= 64 ? (groups + 7) / 8 * 8 : groups;
+    return (int)(up < cap ? up : cap);
+}
 
 }  // namespace samk

@@ -38,6 +38,14 @@ def shapes(A, S_cp, S_ri):
     return np.array(r), np.array(c), e
 
 
+def build_matches_oracle(ctx, plan, dAk, dA0, Ak, A0, S):
+    Mo, _, _, _ = O.sam_build(Ak, A0, O.Pattern(Ak.n, S.colptr, S.rowind))
+    for prec in ("f32", "f64"):
+        M, _, _ = plan.build(dAk.val, dA0.val, prec)
+        ctx.sync_status()
+        assert colmax_rel(M.cpu().numpy().astype(np.float64), Mo, S.colptr)[0] <= TOL[prec]
+
+
 @pytest.mark.parametrize("n,widest", [(1, 1), (255, 2), (256, 4), (257, 5), (2049, 6), (700, 1)])
 def test_plan_facts(n, widest):
     from paper_2406_17656_amd import Context, DeviceCSC, autotune
@@ -54,7 +62,11 @@ def test_plan_facts(n, widest):
     assert (info["max_rows"], info["max_cols"], info["gathered"]) == (r.max(), c.max(), e)
     assert sum(info["bucket_cols"]) == n
     order = list(range(len(autotune.menu("f32"))))
-    for select in (order, order[::-1]):
+    for select in (None, order, order[::-1]):   # None: the classes the plan picked itself
+        if select is None:
+            assert 0 not in info["bucket_cols"]
+            build_matches_oracle(ctx, plan, dAk, dA0, Ak, A0, S)
+            continue
         plan.select(select, "f32")
         left = np.ones(n, dtype=bool)
         want = []
@@ -63,10 +75,7 @@ def test_plan_facts(n, widest):
             want.append(int(fits.sum()))
             left &= ~fits
         assert plan.info()["bucket_cols"][:len(want)] == want
-        M, _, _ = plan.build(dAk.val, dA0.val, "f32")
-        ctx.sync_status()
-        Mo, _, _, _ = O.sam_build(Ak, A0, O.Pattern(n, S.colptr, S.rowind))
-        assert colmax_rel(M.cpu().numpy().astype(np.float64), Mo, S.colptr)[0] <= TOL["f32"]
+        build_matches_oracle(ctx, plan, dAk, dA0, Ak, A0, S)
     rf, cf = r.astype(float), c.astype(float)
     qr = 2 * rf * cf ** 2 - 2 / 3 * cf ** 3 + 4 * rf * cf
     cost = plan.cost("f32")
