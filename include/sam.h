@@ -514,6 +514,14 @@ sam_status sam_backward(sam_plan* plan, const double* Ak_val, const double* A0_v
                         double* gAk, double* gA0, double* gw, double* loss,
                         void* ws, size_t ws_bytes, sam_stream_t stream);
 
+/* sam_backward with the scale dL read from the device when the kernels run
+ * (a device scalar), so that a gradient that arrives as a device value needs
+ * no copy to the host.  Otherwise as sam_backward. */
+sam_status sam_backward_scaled(sam_plan* plan, const double* Ak_val, const double* A0_val,
+                               const double* w, double mu, const double* dL, int32_t prec,
+                               double* gAk, double* gA0, double* gw, double* loss,
+                               void* ws, size_t ws_bytes, sam_stream_t stream);
+
 /* ------------------------------------------------------ adaptive patterns */
 
 /* The paper leaves adaptive patterns as future work (end of Section 2;

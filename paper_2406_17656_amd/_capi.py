@@ -99,6 +99,7 @@ SIGNATURES = {
     "sam_backward_workspace_size": (c_int32, [P, SZ]),
     "sam_backward_prepare": (c_int32, [P, P, c_size_t, P]),
     "sam_backward": (c_int32, [P, P, P, P, c_double, c_double, c_int32, P, P, P, P, P, c_size_t, P]),
+    "sam_backward_scaled": (c_int32, [P, P, P, P, c_double, P, c_int32, P, P, P, P, P, c_size_t, P]),
     "sam_candidate_weights": (c_int32, [P, c_int32, P, P, c_int64, P, P, c_int64, c_double, c_double, P, P]),
     "sam_topk_workspace_size": (c_int32, [c_int32, SZ]),
     "sam_pattern_topk": (c_int32, [P, c_int32, P, P, c_int64, P, P, c_int32, P, P, ctypes.POINTER(c_int64),

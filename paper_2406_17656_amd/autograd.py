@@ -23,5 +23,5 @@ class SamResidualLoss(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dL):
         Ak_val, A0_val, w = ctx.saved_tensors
-        gAk, gA0, gw, _ = ctx.plan.backward(Ak_val, A0_val, w, ctx.mu, dL=float(dL), prec=ctx.prec)
+        gAk, gA0, gw, _ = ctx.plan.backward(Ak_val, A0_val, w, ctx.mu, dL=dL, prec=ctx.prec)
         return None, gAk, gA0, gw, None, None

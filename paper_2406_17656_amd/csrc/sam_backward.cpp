@@ -71,9 +71,9 @@ sam_status sam_backward_prepare(sam_plan* plan, void* ws, size_t ws_bytes, sam_s
     return SAM_OK;
 }
 
-sam_status sam_backward(sam_plan* plan, const double* Ak_val, const double* A0_val, const double* w, double mu,
-                        double dL, int32_t prec, double* gAk, double* gA0, double* gw, double* loss, void* ws,
-                        size_t ws_bytes, sam_stream_t stream) {
+static sam_status run_backward(sam_plan* plan, const double* Ak_val, const double* A0_val, const double* w, double mu,
+                               double dL, const double* dL_dev, int32_t prec, double* gAk, double* gA0, double* gw,
+                               double* loss, void* ws, size_t ws_bytes, sam_stream_t stream) {
     if (!plan || !plan->ctx) return SAM_ERR_ARG;
     sam_ctx* ctx = plan->ctx;
     check_ctx(ctx);
@@ -118,6 +118,7 @@ sam_status sam_backward(sam_plan* plan, const double* Ak_val, const double* A0_v
     a.w = w;
     a.mu = mu;
     a.dL = dL;
+    a.dL_dev = dL_dev;
     a.contrib = b.contrib;
     a.segoff = b.segoff;
     a.gA0 = gA0;
@@ -134,6 +135,21 @@ sam_status sam_backward(sam_plan* plan, const double* Ak_val, const double* A0_v
     HIP_TRY(ctx, samk::backward_scatter(plan->n, plan->Ak_cp, b.ST_rowptr, b.ST_perm, b.segoff, b.contrib, gAk, s));
     if (loss && plan->n > 0) HIP_TRY(ctx, samk::reduce_sum(plan->colbuf, plan->n, loss, plan->rtemp, s));
     return SAM_OK;
+}
+
+sam_status sam_backward(sam_plan* plan, const double* Ak_val, const double* A0_val, const double* w, double mu,
+                        double dL, int32_t prec, double* gAk, double* gA0, double* gw, double* loss, void* ws,
+                        size_t ws_bytes, sam_stream_t stream) {
+    return run_backward(plan, Ak_val, A0_val, w, mu, dL, nullptr, prec, gAk, gA0, gw, loss, ws, ws_bytes, stream);
+}
+
+sam_status sam_backward_scaled(sam_plan* plan, const double* Ak_val, const double* A0_val, const double* w, double mu,
+                               const double* dL, int32_t prec, double* gAk, double* gA0, double* gw, double* loss,
+                               void* ws, size_t ws_bytes, sam_stream_t stream) {
+    if (!plan || !plan->ctx) return SAM_ERR_ARG;
+    check_ctx(plan->ctx);
+    if (!dL) return fail(plan->ctx, SAM_ERR_ARG, "dL is NULL");
+    return run_backward(plan, Ak_val, A0_val, w, mu, 0.0, dL, prec, gAk, gA0, gw, loss, ws, ws_bytes, stream);
 }
 
 }  // extern "C"

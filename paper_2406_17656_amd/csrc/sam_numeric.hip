@@ -916,7 +916,7 @@ k_numeric(NumericArgs a) {
             wave_sync();
             scatter_v(al, lsh, 1.0);
             // dL/dA at the gathered entries: 2 r m^T - r lambda^T - (A lambda) m^T
-            const double dL = a.dL;
+            const double dL = a.dL_dev ? *a.dL_dev : a.dL;
             double* cj = a.contrib + eo;
 #pragma unroll
             for (int c = 0; c < NC; ++c) {

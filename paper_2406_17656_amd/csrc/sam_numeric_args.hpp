@@ -38,6 +38,7 @@ struct NumericArgs {
     double mu;
     // adjoint outputs (backward launches only)
     double dL;
+    const double* dL_dev; // the scale on the device instead (may be null)
     double* contrib;      // per gathered entry, at eoff[j] + offset in the block
     int64_t* segoff;      // per S entry: where its column's contributions start
     double* gA0;          // nnz(A_0)

@@ -364,9 +364,15 @@ class Plan:
             self.ctx.check(self.ctx.lib.sam_backward_prepare(self.h, _ptr(ws), nb.value, self.ctx.stream()))
             self._bwd = (ws, nb.value)
         ws, nb = self._bwd
-        self.ctx.check(self.ctx.lib.sam_backward(self.h, _ptr(Ak_val), _ptr(A0_val), _ptr(w), float(mu),
-                                                 float(dL), p, _ptr(gAk), _ptr(gA0), _ptr(gw), _ptr(loss),
-                                                 _ptr(ws), nb, self.ctx.stream()))
+        if isinstance(dL, torch.Tensor) and dL.device == Ak_val.device and dL.is_cuda \
+                and dL.dtype == torch.float64 and dL.numel() == 1:
+            # read on the device by this stream's kernels: no wait for its value here
+            dL.record_stream(torch.cuda.current_stream(dL.device))
+            call, scale = self.ctx.lib.sam_backward_scaled, _ptr(dL)
+        else:
+            call, scale = self.ctx.lib.sam_backward, float(dL)
+        self.ctx.check(call(self.h, _ptr(Ak_val), _ptr(A0_val), _ptr(w), float(mu), scale, p, _ptr(gAk), _ptr(gA0),
+                            _ptr(gw), _ptr(loss), _ptr(ws), nb, self.ctx.stream()))
         return gAk, gA0, (gw[:self.nnz_S] if gw is not None else None), loss
 
 
