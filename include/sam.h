@@ -263,9 +263,9 @@ sam_status sam_plan_cost_weighted(const sam_plan* plan, int32_t prec, int32_t ba
 
 /* The numeric kernel variants compiled for `prec` (weighted = 0: plain maps,
  * 1: soft-weighted).  Until sam_plan_select chooses others, a plan's plain
- * builds use the variants that its shapes make cheapest together; weighted
- * builds and sequences with a sparsification rule take a column's first
- * fitting one in this order.  Each serves column blocks of
+ * builds use the variants that its shapes make cheapest together (a sequence
+ * with a sparsification rule: shapes spread below its structural ones);
+ * weighted builds take a column's first fitting one in this order.  Each serves column blocks of
  * at most G*R rows (G*R - |J_j| penalty rows aside when weighted) and NC
  * columns; G lanes of a wave64 own one column problem, TC columns are staged
  * per LDS pass.  Host outputs of `capacity` entries (any may be NULL);

@@ -34,6 +34,11 @@ CFLAGS = [
     "-I", INCLUDE, "-I", CSRC,
 ]
 
+# The Householder loop of the widest FP32 class (25 steps over 200 registers)
+# is unrolled by a pragma whose size limit it exceeds by default; left rolled,
+# the block would be indexed at run time and live in scratch memory.
+EXTRA = {"sam_numeric.hip": ["-mllvm", "-pragma-unroll-threshold=1000000"]}
+
 
 def _stale(obj: str, src: str) -> bool:
     if not os.path.exists(obj):
@@ -68,7 +73,7 @@ def _compile(src: str, force: bool) -> str:
     path = os.path.join(CSRC, src)
     obj = os.path.join(OBJDIR, os.path.splitext(src)[0] + ".o")
     if force or _stale(obj, path):
-        cmd = [HIPCC] + CFLAGS + ["-Rpass-analysis=kernel-resource-usage", "-x", "hip", "-c", path,
+        cmd = [HIPCC] + CFLAGS + EXTRA.get(src, []) + ["-Rpass-analysis=kernel-resource-usage", "-x", "hip", "-c", path,
                                   "-o", obj + ".tmp"]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:

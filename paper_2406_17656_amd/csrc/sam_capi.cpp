@@ -4,6 +4,7 @@
 #include "sam_host.hpp"
 
 #include <climits>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -344,61 +345,97 @@ int class_counts(const sam_plan* pl, const BucketTable& tab, std::vector<int>* c
 // all the 5-point boundary columns in classes of their own took 147 us of
 // launches for the 512^2 level-2 map, 104 us in the interior's class; the 64^2
 // nine-point map took eleven launches and 227 us, now 26 us in one.  Starting
-// from every class, the one whose loss helps most is left out until none
-// does.  Columns fall into few distinct sets of fitting classes, so this is
-// some thousand operations.  Empty: some column fits no class.
-std::vector<const NumericVariant*> fitted_order(const sam_plan* pl, int prec) {
-    constexpr double kLaunchUs = 2.0;   // from one launch's end to the next one's start
+// from every column's cheapest class, a class is given up, or exchanged for
+// one not in use, while that helps.  Columns fall into few distinct sets of
+// fitting classes, so this is some ten thousand operations.
+// shrinks: the shapes are the largest each column can have (a sequence with
+// a sparsification rule).  What its sources leave is not known, so eighths of
+// the columns are taken at each eighth f of the width, with the rows at f^0.8
+// (a smaller stencil of the same kind), f^0.5 and f^0.3 (a thresholded column
+// keeps most of its rows), and the classes that pay off for that are used:
+// few at small n, where a launch costs more than its columns save.  A launch
+// counts more here, for a class may turn out to get hardly any columns.
+// Empty: some column fits no class.
+std::vector<const NumericVariant*> fitted_order(const sam_plan* pl, int prec, bool shrinks) {
+    const double launch_us = shrinks ? 8.0 : 2.0;   // beyond the class's own time
     std::vector<const NumericVariant*> all;
     menu_table(prec, 0, &all);
+    auto is_long = [&](const NumericVariant* v) { return v->long_columns(pl->n, pl->nnzA, pl->max_len_A); };
+    auto col_ns = [&](const NumericVariant* v) { return is_long(v) ? v->col_ns_long : v->col_ns; };
     std::stable_sort(all.begin(), all.end(),
-                     [](const NumericVariant* a, const NumericVariant* b) { return a->col_ns < b->col_ns; });
+                     [&](const NumericVariant* a, const NumericVariant* b) { return col_ns(a) < col_ns(b); });
     if (pl->shapes.empty() || pl->shapes[samk::kShapeCells - 1] > 0) return {};
-    std::vector<std::pair<unsigned, int>> sets;   // fitting classes (bits), columns
+    std::vector<std::pair<unsigned, double>> sets;   // fitting classes (bits), columns
+    auto add = [&](int r, int c, double cnt) {
+        unsigned fits = 0;
+        for (size_t v = 0; v < all.size(); ++v)
+            if (r <= all[v]->max_rows() && c <= all[v]->NC) fits |= 1u << v;
+        if (!fits) return false;
+        auto it = std::find_if(sets.begin(), sets.end(), [&](const auto& p) { return p.first == fits; });
+        if (it == sets.end()) sets.emplace_back(fits, cnt);
+        else it->second += cnt;
+        return true;
+    };
     for (int r = 0; r <= samk::kShapeRows; ++r)
         for (int c = 0; c <= samk::kShapeCols; ++c) {
             const int cnt = pl->shapes[(size_t)r * (samk::kShapeCols + 1) + c];
             if (!cnt) continue;
-            unsigned fits = 0;
-            for (size_t v = 0; v < all.size(); ++v)
-                if (r <= all[v]->max_rows() && c <= all[v]->NC) fits |= 1u << v;
-            if (!fits) return {};
-            auto it = std::find_if(sets.begin(), sets.end(), [&](const auto& p) { return p.first == fits; });
-            if (it == sets.end()) sets.emplace_back(fits, cnt);
-            else it->second += cnt;
+            if (!shrinks) {
+                if (!add(r, c, cnt)) return {};
+                continue;
+            }
+            for (int e = 1; e <= 8; ++e) {
+                const double f = e / 8.0;
+                const int ce = (int)std::ceil(c * f);
+                for (double x : {0.8, 0.5, 0.3})
+                    if (!add((int)std::ceil(r * std::pow(f, x)), ce, cnt / 24.0)) return {};
+            }
         }
-    std::vector<int> counts(all.size());
+    std::vector<double> counts(all.size());
     auto cost = [&](unsigned use) {   // us, or -1 where a column fits none
-        std::fill(counts.begin(), counts.end(), 0);
+        std::fill(counts.begin(), counts.end(), 0.0);
         for (const auto& p : sets) {
             if (!(p.first & use)) return -1.0;
             counts[(size_t)__builtin_ctz(p.first & use)] += p.second;
         }
         double t = 0.0;
         for (size_t v = 0; v < all.size(); ++v)
-            if (counts[v]) t += kLaunchUs + std::max<double>(all[v]->round_us, 1e-3 * all[v]->col_ns * counts[v]);
+            if (counts[v] > 0.0)
+                t += launch_us + std::max<double>(is_long(all[v]) ? all[v]->round_us_long : all[v]->round_us,
+                                                  1e-3 * col_ns(all[v]) * counts[v]);
         return t;
     };
-    unsigned use = (1u << all.size()) - 1u;
+    auto in_use = [&](unsigned use) {   // without the classes that get no column
+        (void)cost(use);
+        unsigned u = 0;
+        for (size_t v = 0; v < all.size(); ++v)
+            if (counts[v] > 0.0) u |= 1u << v;
+        return u;
+    };
+    unsigned use = in_use((1u << all.size()) - 1u);
     double now = cost(use);
     for (bool better = true; better;) {
         better = false;
         unsigned best = use;
-        for (size_t v = 0; v < all.size(); ++v) {
-            if (!(use >> v & 1u)) continue;
-            const double t = cost(use & ~(1u << v));
+        auto consider = [&](unsigned cand) {
+            const double t = cost(cand);
             if (t >= 0.0 && t < now) {
                 now = t;
-                best = use & ~(1u << v);
+                best = cand;
                 better = true;
             }
+        };
+        for (size_t v = 0; v < all.size(); ++v) {
+            if (!(use >> v & 1u)) continue;
+            consider(use & ~(1u << v));
+            for (size_t u = 0; u < all.size(); ++u)
+                if (!(use >> u & 1u)) consider((use & ~(1u << v)) | 1u << u);
         }
-        use = best;
+        use = in_use(best);
     }
-    cost(use);
     std::vector<const NumericVariant*> order;
     for (size_t v = 0; v < all.size(); ++v)
-        if (counts[v]) order.push_back(all[v]);
+        if (use >> v & 1u) order.push_back(all[v]);
     return order;
 }
 
@@ -446,17 +483,19 @@ sam_status plan_sort(sam_plan* pl, Combo* const* combos, int count, hipStream_t 
 
 // Blocks of a numeric variant the GPU holds at once per CU (16 when the
 // occupancy query failed).
-int resident_blocks(const sam_ctx* ctx, const NumericVariant* v) {
+int resident_blocks(const sam_ctx* ctx, const NumericVariant* v, bool lng = false) {
     int cnt = 0;
     const NumericVariant* menu = samk::numeric_menu(&cnt);
     const ptrdiff_t i = v - menu;
-    if (i >= 0 && i < (ptrdiff_t)ctx->resident.size() && ctx->resident[i] > 0) return ctx->resident[i];
+    const std::vector<int>& r = lng ? ctx->resident_long : ctx->resident;
+    if (i >= 0 && i < (ptrdiff_t)r.size() && r[i] > 0) return r[i];
     return 16;
 }
 
 int partial_capacity(const sam_ctx* ctx) {
     int most = 16;
     for (int r : ctx->resident) most = std::max(most, r);
+    for (int r : ctx->resident_long) most = std::max(most, r);
     return samk::kMaxBuckets * ctx->CUs * most;
 }
 
@@ -538,7 +577,7 @@ void plan_shape_stats(sam_plan* pl) {
 
 sam_status plan_init(sam_ctx* ctx, sam_plan* pl, const sam_csc* Ak, const sam_csc* A0, const int32_t* S_colptr,
                      const int32_t* S_rowind, int64_t nnz_S, void* mem, size_t mem_bytes, int only_prec,
-                     bool fitted, hipStream_t s) {
+                     bool shrinks, hipStream_t s) {
     const int n = Ak->n;
     pl->ctx = ctx;
     pl->n = n;
@@ -614,7 +653,7 @@ sam_status plan_init(sam_ctx* ctx, sam_plan* pl, const sam_csc* Ak, const sam_cs
             for (int w = 0; w < 2; ++w) {
                 if (only_prec >= 0 && (p != only_prec || w != 0)) continue;
                 std::vector<const NumericVariant*> vars;
-                if (fitted && w == 0) vars = fitted_order(pl, p);
+                if (w == 0) vars = fitted_order(pl, p, shrinks);
                 if (vars.empty()) menu_table(p, w, &vars);
                 plan_combo_with(pl, p, w, vars);
                 combos[count++] = &pl->combo[p][w];
@@ -666,12 +705,13 @@ sam_status run_numeric(sam_plan* pl, const double* Ak_val, const double* A0_val,
         const int groups = (cnt + v->per_wave() - 1) / v->per_wave();
         // one round of resident blocks for the plain maps; the weighted
         // forms run faster over two rounds (as the adjoint's launch)
-        const int per_cu = weighted ? std::min(16, 2 * resident_blocks(ctx, v)) : resident_blocks(ctx, v);
+        const bool lng = v->launch_long && v->long_columns(pl->n, pl->nnzA, pl->max_len_A);
+        const int per_cu = weighted ? std::min(16, 2 * resident_blocks(ctx, v)) : resident_blocks(ctx, v, lng);
         const int grid = samk::launch_grid(groups, ctx->CUs * per_cu);
         if (res2 && parts + grid > pl->partcap)
             return fail(ctx, SAM_ERR_HIP, "partial-sum buffer too small (%d blocks)", parts + grid);
         a.part_base = parts;
-        HIP_TRY(ctx, v->launch(a, grid, s));
+        HIP_TRY(ctx, (lng ? v->launch_long : v->launch)(a, grid, s));
         parts += grid;
     }
     if (res2 && parts > 0) HIP_TRY(ctx, samk::reduce_sum(pl->partbuf, parts, res2, pl->rtemp, s));
@@ -755,7 +795,11 @@ sam_status sam_create(sam_ctx** out, int device) {
             int cnt = 0;
             const samk::NumericVariant* menu = samk::numeric_menu(&cnt);
             ctx->resident.assign(cnt, 0);
-            for (int i = 0; i < cnt; ++i) ctx->resident[i] = menu[i].blocks_per_cu();
+            ctx->resident_long.assign(cnt, 0);
+            for (int i = 0; i < cnt; ++i) {
+                ctx->resident[i] = menu[i].blocks_per_cu();
+                if (menu[i].blocks_per_cu_long) ctx->resident_long[i] = menu[i].blocks_per_cu_long();
+            }
         }
         // the context's status block: the only device memory the library
         // allocates itself
@@ -945,7 +989,7 @@ static sam_status create_plan(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0
     hipStream_t s = S(stream);
     sam_plan* pl = new (std::nothrow) sam_plan();
     if (!pl) return fail(ctx, SAM_ERR_NOMEM, "host allocation failed");
-    if ((st = plan_init(ctx, pl, Ak, A0, S_colptr, S_rowind, nnz_S, mem, mem_bytes, only_prec, true, s))) {
+    if ((st = plan_init(ctx, pl, Ak, A0, S_colptr, S_rowind, nnz_S, mem, mem_bytes, only_prec, false, s))) {
         delete pl;
         return st;
     }

@@ -107,8 +107,8 @@ struct sam_ctx {
     samh::PatternState pat;
     int CUs = 256;
     // resident blocks per CU of each numeric kernel variant (menu order),
-    // queried once on the context's device
-    std::vector<int> resident;
+    // queried once on the context's device; and of its form for long columns
+    std::vector<int> resident, resident_long;
 };
 
 // One (precision, weighted) combination of a plan: the bucket order of the
@@ -238,12 +238,12 @@ sam_status pattern_fill(sam_ctx* ctx, int n, const PatternResult& res, int* S_cp
 // capacity).
 size_t plan_bytes(int n, int64_t E, int nnzA0, int partcap);
 // A plan in caller memory `mem` (>= plan_bytes).  Checks the three structures.
-// only_prec >= 0: the classes of that precision's plain maps alone.  fitted:
-// the plain maps take the classes that suit the plan's shapes (fitted_order),
-// else the whole menu in its order.
+// only_prec >= 0: the classes of that precision's plain maps alone.  shrinks:
+// S bounds the patterns the plan's classes will serve (a sequence with a
+// sparsification rule).
 sam_status plan_init(sam_ctx* ctx, sam_plan* pl, const sam_csc* Ak, const sam_csc* A0, const int32_t* S_colptr,
                      const int32_t* S_rowind, int64_t nnz_S, void* mem, size_t mem_bytes, int only_prec,
-                     bool fitted, hipStream_t s);
+                     bool shrinks, hipStream_t s);
 
 // The bucket table of one (precision, weighted) combination of the menu.
 samk::BucketTable menu_table(int prec, int weighted, std::vector<const samk::NumericVariant*>* variants);

@@ -77,7 +77,7 @@ sam_status sam_build_noalloc(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0,
                     "(use sam_build with a workspace)", need, kScratchBytes);
     sam_plan pl;
     if ((st = plan_init(ctx, &pl, Ak, A0, S_colptr, S_rowind, nnz_S, base, kScratchBytes,
-                        prec == SAM_PREC_F32_REFINE ? 1 : 0, true, s)))
+                        prec == SAM_PREC_F32_REFINE ? 1 : 0, false, s)))
         return st;
     return run_numeric(&pl, Ak->val, A0->val, nullptr, 0.0, prec == SAM_PREC_F32_REFINE ? 1 : 0, 0, M_val, col_res2,
                        res2, s);

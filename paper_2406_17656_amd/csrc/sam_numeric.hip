@@ -71,6 +71,14 @@ __device__ inline void lds_add(double* p, double x) {
     __hip_atomic_fetch_add(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
+// x, but (HIDE) as a value the compiler knows nothing about: what is computed
+// from it is not hoisted out of the loop or held from an earlier use.
+template <bool HIDE>
+__device__ inline int fresh(int x) {
+    if constexpr (HIDE) asm volatile("" : "+v"(x));
+    return x;
+}
+
 template <typename T>
 __device__ inline T recip(T x);
 template <>
@@ -97,8 +105,10 @@ __device__ inline double root<double>(double x) { return sqrt(x); }
 // take 175 and fit two): the compiler then keeps a few loop-invariant values
 // in scratch (28 bytes per lane, reloaded a handful of times per group), and
 // the launch is about 8% faster.
+constexpr bool is_tight(bool f32, int R, int NC, int MODE) { return f32 && MODE == 0 && R * NC > 160; }
 constexpr int numeric_min_waves(bool f32, int G, int R, int NC, int MODE) {
-    return (f32 && MODE == 0 && G == 16 && R == 4 && NC == 25) ? 3 : 1;
+    if (!f32 || MODE != 0) return 1;
+    return (G == 16 && R == 4 && NC == 25) ? 3 : is_tight(f32, R, NC, MODE) ? 2 : 1;
 }
 
 template <typename TQ, int G, int R, int NC, int TC, int LPL, int MODE>
@@ -121,6 +131,12 @@ k_numeric(NumericArgs a) {
     // of the plain map (see the stages below); only they double-buffer the
     // column extents.
     constexpr bool PIPE = NC >= 8 && NC <= 13 && MODE == 0;
+    // Classes whose block alone is most of the 256 registers that two waves
+    // per SIMD leave: fewer trailing columns in flight, and what the QR does
+    // not need waits in LDS.
+    constexpr bool TIGHT = is_tight(REFINE, R, NC, MODE);
+    static_assert(!(PIPE && TIGHT), "a prefetching class rewrites its metadata during the QR");
+    constexpr int CW = 12;
     // FP64-residual refinement steps of the weighted forms (m, and the
     // adjoint's lambda)
     constexpr int kWSteps = 1;
@@ -138,6 +154,8 @@ k_numeric(NumericArgs a) {
     __shared__ int mta[P][9];             // next group: valid, j, scol, nJ, nIj, eo (2), a0, a1
     __shared__ double alsh[BACKWARD ? P * RS : 1];  // A lambda (adjoint)
     __shared__ double racc;               // the block's running sum of column residuals
+    __shared__ double out_sh[TIGHT ? P : 1];   // out_j across the QR (see `again`)
+    __shared__ int long_sh;
     __shared__ double pen_sh[WEIGHTED ? P * NC : 1];  // penalties p_c of the group's problems
     // The weighted and adjoint forms keep their length-NC FP64 vectors (m,
     // A^T r, the corrections, lambda and its right side) in LDS: one slot per
@@ -257,6 +275,8 @@ k_numeric(NumericArgs a) {
             stage5(0);
             wave_sync();
         }
+        const int lane1 = fresh<TIGHT>(lane);
+        const int g = lane1 % G, q = lane1 / G, trash = RM + g;
         int (&vbs)[P][NC] = vbs2[bi];
         int (&cln)[P][NC] = cln2[bi];
         const bool valid = mta[q][0] != 0;
@@ -277,6 +297,8 @@ k_numeric(NumericArgs a) {
             if (c < NC) mylong |= cln[q][c] > LPL * G;
         }
         const bool longc = __ballot(mylong) != 0ull;
+        if constexpr (TIGHT)
+            if (lane == 0) long_sh = longc;
         // ---- b = A_0(I_j, j) and out_j (rows outside I_j)
 #pragma unroll
         for (int t = 0; t < R; ++t) bsh[q * RS + t * G + g] = 0.0;
@@ -308,12 +330,14 @@ k_numeric(NumericArgs a) {
             bsh[q * RS + ((bp[s] >= 0 && bp[s] != 0xFF) ? bp[s] : trash)] = bv[s];
         }
         for (int e = a0 + g + LPL * G; e < a1; e += G) {  // long columns
-            const int p = a.posB[e];
-            const double v = a.A0_v[e];
+            const int p = ld_u8(rPB, (uint32_t)e);
+            const double v = ld_f64(rA0, (uint32_t)e * 8u);
             if (p != 0xFF) bsh[q * RS + p] = v;
             else outj += v * v;
         }
         outj = group_sum<G>(outj);
+        if constexpr (TIGHT)
+            if (g == 0) out_sh[q] = outj;
         wave_sync();
 
         // ---- gather: every A_k value this lane moves is loaded first (static
@@ -361,7 +385,8 @@ k_numeric(NumericArgs a) {
                     if (len > LPL * G) {  // long columns: the rest straight from memory
                         const int e0 = cst[q][c], vb = vbs[q][c];
                         for (int e = g + LPL * G; e < len; e += G)
-                            tile[(q * RS + a.posA[eo + e0 + e]) * TC + cc] = (TQ)a.Ak_v[vb + e];
+                            tile[(q * RS + ld_u8(rPA, (uint32_t)eo + (uint32_t)(e0 + e))) * TC + cc] =
+                                (TQ)ld_f64(rAv, (uint32_t)(vb + e) * 8u);
                     }
                 }
             }
@@ -497,6 +522,37 @@ k_numeric(NumericArgs a) {
                     // second stage needs below R_1; nothing else reads them)
                     if (WEIGHTED && below) A[t][k] = (TQ)0;
                 }
+                if constexpr (TIGHT) {
+                    // a few trailing columns at a time: the dot products of
+                    // all of them beside the block would not fit
+                    TQ wb = 0;
+#pragma unroll
+                    for (int t = tk; t < R; ++t) wb += v[t] * bq[t];
+                    wb = group_sum<G>(wb) * sigma;
+#pragma unroll
+                    for (int t = tk; t < R; ++t) bq[t] -= wb * v[t];
+#pragma unroll
+                    for (int c0 = k + 1; c0 < NC; c0 += CW) {
+                        TQ w[CW];
+#pragma unroll
+                        for (int u = 0; u < CW; ++u) {
+                            TQ s = 0;
+                            if (c0 + u < NC) {
+#pragma unroll
+                                for (int t = tk; t < R; ++t) s += v[t] * A[t][c0 + u];
+                                w[u] = group_sum<G>(s) * sigma;
+                            }
+                        }
+#pragma unroll
+                        for (int u = 0; u < CW; ++u)
+                            if (c0 + u < NC) {
+#pragma unroll
+                                for (int t = tk; t < R; ++t) A[t][c0 + u] -= w[u] * v[t];
+                            }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    continue;
+                }
                 TQ w[NC + 1];
 #pragma unroll
                 for (int c = k + 1; c < NC; ++c) {
@@ -541,14 +597,29 @@ k_numeric(NumericArgs a) {
             __builtin_amdgcn_sched_barrier(0);
         }
 
+        // From here on the tight classes see lane, metadata and addresses anew
+        // (the compiler cannot know that they are the same), so nothing of
+        // them is held, or spilled, across the QR.
+        {
+        const int lane2 = fresh<TIGHT>(lane);
+        const int g = lane2 % G, q = lane2 / G, trash = RM + g;
+        const int nJ2 = TIGHT ? mta[q][3] : nJ;
+        const bool valid2 = TIGHT ? mta[q][0] != 0 : valid;
+        const int j2 = TIGHT ? mta[q][1] : j;
+        const int scol2 = TIGHT ? mta[q][2] : scol;
+        const int nrows2 = TIGHT ? mta[q][4] : nrows;   // |I_j|: the tight classes are plain
+        const uint32_t eo2 = TIGHT ? (uint32_t)mta[q][5] : (uint32_t)eo;
+        const bool longc2 = TIGHT ? long_sh != 0 : longc;
+        const double outj2 = TIGHT ? out_sh[q] : outj;
+
         // ---- rank test: |R_kk| <= 10 * rows * eps * max |R_ii|
         bool bad_rank = false;
         {
             const TQ eps = std::is_same<TQ, float>::value ? (TQ)1.1920928955078125e-07
                                                           : (TQ)2.220446049250313e-16;
-            const TQ tol = (TQ)10 * (TQ)nrows * eps * dmax;
+            const TQ tol = (TQ)10 * (TQ)nrows2 * eps * dmax;
             // some live |R_kk| <= tol (or NaN), or all of them zero
-            if (nJ > 0) bad_rank = dnan || !(dmax > (TQ)0) || !(dmin > tol);
+            if (nJ2 > 0) bad_rank = dnan || !(dmax > (TQ)0) || !(dmin > tol);
         }
 
         // ||c2||^2 = rows nJ.. of Q^T b, before the back substitution consumes b
@@ -563,20 +634,21 @@ k_numeric(NumericArgs a) {
             c2sq = group_sum<G>(r2) + c2s1;
         }
 
-        // Back substitution x = R^{-1} z, column by column: z holds the right
+        // Back substitution x = R^{-1} z, column by column, put(k, x_k): z holds the right
         // side distributed like the rows (z[t]: row t*G + g) and is consumed.
         // x_k comes from the lane owning row k and is broadcast; then every
         // lane takes x_k times column k off its rows in blocks t <= k / G.
         // Rows at or below k are done by then, so the entries below the
         // diagonal (Householder vectors) only touch finished rows.
-        auto back_solve = [&](TQ (&z)[R], TQ (&x)[NC]) {
+        auto back_solve = [&](TQ (&z)[R], auto put) {
 #pragma unroll
             for (int k = NC - 1; k >= 0; --k) {
                 const int tk = k / G, gk = k % G;
-                const TQ xk = group_bcast<G>(z[tk] * RINV(k), g, gk);
-                x[k] = (k < nJ) ? xk : (TQ)0;
+                TQ xk = group_bcast<G>(z[tk] * RINV(k), g, gk);
+                xk = (k < nJ2) ? xk : (TQ)0;
+                put(k, xk);
 #pragma unroll
-                for (int t = 0; t <= tk; ++t) z[t] -= A[t][k] * x[k];
+                for (int t = 0; t <= tk; ++t) z[t] -= A[t][k] * xk;
             }
         };
         // x = R^{-1} z into an LDS vector (the weighted forms): as back_solve,
@@ -595,7 +667,7 @@ k_numeric(NumericArgs a) {
         };
         // ---- R m = c1 (the weighted forms solve it into their LDS slot below)
         TQ m[WEIGHTED ? 1 : NC];
-        if constexpr (!WEIGHTED) back_solve(bq, m);
+        if constexpr (!WEIGHTED) back_solve(bq, [&](int k, TQ xk) { m[k] = xk; });
 
         double* rsh = lds_tile + q * RS;  // residual vector (the tile is free now)
 
@@ -704,7 +776,6 @@ k_numeric(NumericArgs a) {
         // registers across the refinement and the adjoint)
         double* pen = pen_sh + q * NC;
 
-        double mfin[WEIGHTED ? 1 : NC];
         double rr;
         double* msh = vsh + q * kNV * NC;      // weighted forms: m
         if constexpr (REFINE && MODE == 0) {
@@ -715,11 +786,11 @@ k_numeric(NumericArgs a) {
             // own FP64 group reduction;  R d = y;  m += d.  The new residual
             // ||b - A(m + d)||^2 = ||r||^2 - 2 d^T A^T r + ||A d||^2, where
             // d^T A^T r and ||A d||^2 both equal ||y||^2 up to rounding.
-            // Blocks of up to 13 columns keep the entries the gather loaded
+            // Blocks of up to 13 columns and 26 slots keep the entries the gather loaded
             // (held through the QR) for both passes; wider ones reload them
             // three columns at a time (a whole block's entries would hold
             // 3 * NC * LPL registers and cost a wave slot per SIMD).
-            constexpr int CH = NC <= 13 ? NC : 3;
+            constexpr int CH = NC <= 13 && NC * LPL <= 26 ? NC : 3;
             constexpr bool ONE = CH >= NC;
             double* rv = bsh + q * RS;
             rv[trash] = 0.0;
@@ -729,7 +800,7 @@ k_numeric(NumericArgs a) {
                     const int c = c0 + cc;
                     if (c < NC) {
                         const int len = cln[q][c];
-                        const uint32_t po = (uint32_t)eo + (uint32_t)(cst[q][c] + g);
+                        const uint32_t po = eo2 + (uint32_t)(cst[q][c] + g);
                         const uint32_t vo = (uint32_t)(vbs[q][c] + g) * 8u;
 #pragma unroll
                         for (int u = 0; u < LPL; ++u) {
@@ -762,11 +833,12 @@ k_numeric(NumericArgs a) {
                         const double xc = -(double)m[c];
 #pragma unroll
                         for (int u = 0; u < LPL; ++u) lds_add(&rv[cp[cc][u]], cv[cc][u] * xc);
-                        const int len = longc ? cln[q][c] : 0;
+                        const int len = longc2 ? cln[q][c] : 0;
                         if (len > LPL * G) {  // long columns: the rest straight from memory
                             const int e0 = cst[q][c], vb = vbs[q][c];
                             for (int e = g + LPL * G; e < len; e += G)
-                                lds_add(&rv[a.posA[eo + e0 + e]], a.Ak_v[vb + e] * xc);
+                                lds_add(&rv[ld_u8(rPA, eo2 + (uint32_t)(e0 + e))],
+                                        ld_f64(rAv, (uint32_t)(vb + e) * 8u) * xc);
                         }
                     }
                 }
@@ -780,7 +852,9 @@ k_numeric(NumericArgs a) {
             }
             const double rr0 = group_sum<G>(r2);
             TQ ydist[R];
-            TQ yrep[NC];
+            // ||y||^2 is the step's decrease of the residual, (u kappa)^2 of
+            // it at most: the QR's precision is ample
+            TQ yy = 0;
 #pragma unroll
             for (int t = 0; t < R; ++t) ydist[t] = 0;
 #pragma unroll
@@ -793,10 +867,12 @@ k_numeric(NumericArgs a) {
                         double gp = 0.0;
 #pragma unroll
                         for (int u = 0; u < LPL; ++u) gp += cv[cc][u] * rv[cp[cc][u]];
-                        const int len = longc ? cln[q][c] : 0;
+                        const int len = longc2 ? cln[q][c] : 0;
                         if (len > LPL * G) {
                             const int e0 = cst[q][c], vb = vbs[q][c];
-                            for (int e = g + LPL * G; e < len; e += G) gp += a.Ak_v[vb + e] * rv[a.posA[eo + e0 + e]];
+                            for (int e = g + LPL * G; e < len; e += G)
+                                gp += ld_f64(rAv, (uint32_t)(vb + e) * 8u) *
+                                      rv[ld_u8(rPA, eo2 + (uint32_t)(e0 + e))];
                         }
                         TQ part = 0;
 #pragma unroll
@@ -804,29 +880,19 @@ k_numeric(NumericArgs a) {
                             if (t * G < c) part += A[t][c] * ydist[t];
                         const double sc = group_sum<G>(gp - (double)part);
                         TQ yc = (TQ)sc * RINV(c);
-                        yc = (c < nJ) ? yc : (TQ)0;
-                        yrep[c] = yc;
+                        yc = (c < nJ2) ? yc : (TQ)0;
+                        yy += yc * yc;
                         if (g == c % G) ydist[c / G] = yc;
                     }
                 }
             }
-            TQ dl[NC];
-            back_solve(ydist, dl);
-            // ||y||^2 is the step's decrease of the residual, (u kappa)^2 of
-            // it at most: the QR's precision is ample.  The map is stored in
-            // FP32, so m + d is formed there too (the correctly rounded sum
-            // of the two floats).
-            TQ yy = 0;
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                yy += yrep[c] * yrep[c];
-                mfin[c] = (double)(m[c] + dl[c]);
-            }
-            rr = rr0 - (double)yy + outj;
+            // The map is stored in FP32, so m + d is formed there too (the
+            // correctly rounded sum of the two floats), in place: neither d
+            // nor an FP64 copy of m is held beside the block.
+            back_solve(ydist, [&](int k, TQ xk) { m[k] += xk; });
+            rr = rr0 - (double)yy + outj2;
         } else if constexpr (!WEIGHTED) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c) mfin[c] = (double)m[c];
-            rr = c2sq + outj;   // ||c2||^2
+            rr = c2sq + outj2;   // ||c2||^2
         } else {
             // soft-weighted forms: m, A^T r, the correction and A^T r - P m
             // in the problem's LDS slots
@@ -968,9 +1034,9 @@ k_numeric(NumericArgs a) {
             nonfinite |= group_max<G>(bad) > 0.f;
         } else {
 #pragma unroll
-            for (int c = 0; c < NC; ++c) nonfinite |= (c < nJ) && !isfinite(mfin[c]);
+            for (int c = 0; c < NC; ++c) nonfinite |= (c < nJ2) && !isfinite(m[c]);
         }
-        if (valid) {
+        if (valid2) {
             if (a.M) {
                 if constexpr (WEIGHTED) {
                     for (int c = g; c < nJ; c += G) {
@@ -980,24 +1046,24 @@ k_numeric(NumericArgs a) {
                 } else {
 #pragma unroll
                     for (int c = 0; c < NC; ++c) {
-                        if (c < nJ && (c % G) == g) {
-                            if constexpr (REFINE) static_cast<float*>(a.M)[scol + c] = (float)mfin[c];
-                            else static_cast<double*>(a.M)[scol + c] = mfin[c];
+                        if (c < nJ2 && (c % G) == g) {
+                            static_cast<TQ*>(a.M)[scol2 + c] = m[c];
                         }
                     }
                 }
             }
             if (g == 0) {
-                if (a.col_res2) a.col_res2[j] = rr;
-                if (bad_rank) report(a.status, j, kStRank);
-                else if (nonfinite) report(a.status, j, kStNonfinite);
+                if (a.col_res2) a.col_res2[j2] = rr;
+                if (bad_rank) report(a.status, j2, kStRank);
+                else if (nonfinite) report(a.status, j2, kStNonfinite);
             }
         }
         if (a.part) {  // the group's residuals, summed by a fixed wave-wide tree
-            const double gs = group_sum<64>((g == 0 && valid) ? rr : 0.0);
+            const double gs = group_sum<64>((g == 0 && valid2) ? rr : 0.0);
             if (lane == 0) racc += gs;
         }
         wave_sync();  // the next group's metadata is in LDS
+        }
     }
     if (a.part && lane == 0) a.part[a.part_base + (int)blockIdx.x] = racc;
 }
@@ -1021,17 +1087,18 @@ int numeric_blocks_per_cu() {
 // columns fall back to a loop over memory), sized for 5- to 9-point stencils.
 using LaunchFn = hipError_t (*)(const NumericArgs&, int, hipStream_t);
 
-// the adjoint exists for the weighted variants only
-template <typename TQ, int G, int R, int NC, int TC, int LPL, bool W>
-constexpr LaunchFn backward_launcher() {
-    if constexpr (W) return &launch_numeric<TQ, G, R, NC, TC, LPL, 2>;
-    else return nullptr;
-}
-
-#define SAM_VARIANT(TQ, PREC, G, R, NC, TC, LPL, W, ROUND_US, COL_NS)                              \
-    NumericVariant{PREC, G, R, NC, W, TC, LPL, &launch_numeric<TQ, G, R, NC, TC, LPL, W ? 1 : 0>, \
-                   backward_launcher<TQ, G, R, NC, TC, LPL, W>(),                             \
-                   &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, W ? 1 : 0>, ROUND_US, COL_NS}
+#define SAM_PLAIN(TQ, PREC, G, R, NC, TC, LPL, ...)                                        \
+    NumericVariant{PREC, G, R, NC, 0, TC, LPL, &launch_numeric<TQ, G, R, NC, TC, LPL, 0>,  \
+                   nullptr, &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, 0>, nullptr, nullptr, __VA_ARGS__}
+#define SAM_PLAIN_LONG(TQ, PREC, G, R, NC, TC, LPL, ...)                                   \
+    NumericVariant{PREC, G, R, NC, 0, TC, LPL, &launch_numeric<TQ, G, R, NC, TC, LPL, 0>,  \
+                   nullptr, &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, 0>,              \
+                   &launch_numeric<TQ, G, R, NC, TC, LPL + 1, 0>,                          \
+                   &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL + 1, 0>, __VA_ARGS__}
+#define SAM_WEIGHTED(TQ, PREC, G, R, NC, TC, LPL)                                          \
+    NumericVariant{PREC, G, R, NC, 1, TC, LPL, &launch_numeric<TQ, G, R, NC, TC, LPL, 1>,  \
+                   &launch_numeric<TQ, G, R, NC, TC, LPL, 2>,                              \
+                   &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, 1>, nullptr, nullptr, 0, 0, 0, 0}
 
 // Menu per precision, cheapest first.  Shapes of the workloads: 2D 5-point
 // level 1 (13 x 5), level 2 (25 x 13); 3D 7-point level 2 (63 x 25); 2D
@@ -1041,47 +1108,55 @@ constexpr LaunchFn backward_launcher() {
 // first fitting entry; a plan of known shapes otherwise takes the entries that
 // cost least together (fitted_order), by the last two figures: the time of a
 // launch of 1024 columns, and per column of 262144 (64^3 and 512^2 maps).
-// The FP32 classes between 36 x 10 and 48 x 24 follow the ragged 9-point
-// distribution: each halves the padded work of the columns it takes from the
-// next wider class.
+//
+// As few lanes per problem as the registers of two waves per SIMD allow: a
+// trailing column costs a lane two FMAs per row it holds and log2(G) exchanges,
+// and its entries G lanes' slots of which a five- to nine-entry column fills
+// half or less on 8 or 16 lanes.  Per column of a full GPU, before -> now:
+// 40 x 14 on 8 lanes 0.84 -> 48 x 14 on 4 0.64 ns, 48 x 16 1.05 -> 0.76,
+// 40 x 20 1.48 -> 0.92, 48 x 24 2.03 -> 48 x 25 1.99, 64 x 25 on 16 lanes
+// 3.26 -> on 8 2.24.  The 16-lane form stays for few columns (a round of 23
+// us against 28), as does 32 x 13 on 8 lanes.  The figures after the shape
+// are the cost model's.
 const NumericVariant kMenu[] = {
     // FP32 + refinement
-    SAM_VARIANT(float, 1, 2, 8, 5, 4, 3, false, 7.f, 0.123f),
-    SAM_VARIANT(float, 1, 2, 8, 8, 4, 3, false, 8.2f, 0.154f),
-    SAM_VARIANT(float, 1, 4, 9, 10, 1, 2, false, 9.9f, 0.32f),   // ragged 9-point / thresholded blocks
-    SAM_VARIANT(float, 1, 4, 9, 12, 1, 2, false, 11.3f, 0.39f),
-    SAM_VARIANT(float, 1, 4, 7, 13, 1, 2, false, 11.3f, 0.39f),
-    SAM_VARIANT(float, 1, 4, 8, 16, 2, 2, false, 15.5f, 0.634f),
-    SAM_VARIANT(float, 1, 8, 5, 14, 1, 2, false, 13.1f, 0.843f),
-    SAM_VARIANT(float, 1, 8, 6, 16, 1, 2, false, 15.5f, 1.05f),
-    SAM_VARIANT(float, 1, 8, 5, 20, 1, 2, false, 18.5f, 1.48f),
-    SAM_VARIANT(float, 1, 8, 6, 24, 1, 2, false, 24.6f, 2.03f),
-    SAM_VARIANT(float, 1, 16, 4, 25, 1, 1, false, 23.3f, 3.26f),
-    SAM_VARIANT(float, 1, 32, 4, 32, 1, 1, false, 49.8f, 13.5f),
-    SAM_VARIANT(float, 1, 1, 13, 5, 1, 5, false, 7.2f, 0.077f),   // one problem per lane, no reductions
-    SAM_VARIANT(float, 1, 8, 4, 13, 2, 1, false, 10.1f, 0.572f),
-    SAM_VARIANT(float, 1, 32, 2, 25, 1, 1, false, 32.3f, 6.4f),
+    SAM_PLAIN(float, 1, 2, 8, 5, 4, 3, 7.f, 0.123f, 7.f, 0.123f),
+    SAM_PLAIN(float, 1, 2, 8, 8, 4, 3, 8.2f, 0.154f, 8.2f, 0.154f),
+    SAM_PLAIN_LONG(float, 1, 4, 9, 10, 1, 2, 9.5f, 0.318f, 11.2f, 0.396f),   // ragged 9-point / thresholded blocks
+    SAM_PLAIN(float, 1, 4, 9, 12, 1, 2, 10.9f, 0.39f, 15.3f, 0.546f),
+    SAM_PLAIN(float, 1, 4, 7, 13, 1, 2, 11.1f, 0.392f, 15.4f, 0.54f),
+    SAM_PLAIN(float, 1, 4, 10, 16, 1, 2, 16.6f, 0.69f, 19.8f, 0.804f),
+    SAM_PLAIN_LONG(float, 1, 4, 12, 14, 1, 2, 16.4f, 0.637f, 17.7f, 0.71f),
+    SAM_PLAIN(float, 1, 4, 12, 16, 1, 2, 18.8f, 0.76f, 22.f, 0.871f),
+    SAM_PLAIN(float, 1, 4, 10, 20, 1, 2, 22.f, 0.916f, 25.f, 1.036f),
+    SAM_PLAIN(float, 1, 8, 6, 25, 1, 1, 23.6f, 1.99f, 27.f, 2.154f),
+    SAM_PLAIN(float, 1, 8, 8, 25, 1, 1, 27.7f, 2.24f, 31.f, 2.442f),
+    SAM_PLAIN(float, 1, 32, 4, 32, 1, 1, 49.6f, 13.1f, 49.6f, 13.1f),
+    SAM_PLAIN(float, 1, 1, 13, 5, 1, 5, 7.2f, 0.077f, 7.2f, 0.077f),   // one problem per lane, no reductions
+    SAM_PLAIN(float, 1, 8, 4, 13, 2, 1, 10.1f, 0.572f, 14.7f, 0.78f),
+    SAM_PLAIN(float, 1, 16, 4, 25, 1, 1, 23.2f, 3.23f, 23.2f, 3.25f),
+    SAM_PLAIN_LONG(float, 1, 4, 7, 9, 1, 2, 8.2f, 0.263f, 9.8f, 0.326f),   // level 1 of 7- and 9-point stencils
     // FP64
-    SAM_VARIANT(double, 0, 2, 8, 5, 4, 3, false, 6.6f, 0.161f),
-    SAM_VARIANT(double, 0, 2, 8, 8, 4, 3, false, 8.1f, 0.245f),
-    SAM_VARIANT(double, 0, 4, 7, 13, 2, 2, false, 11.8f, 0.62f),
-    SAM_VARIANT(double, 0, 8, 4, 16, 2, 1, false, 13.1f, 1.42f),
+    SAM_PLAIN(double, 0, 2, 8, 5, 4, 3, 6.6f, 0.161f, 6.6f, 0.161f),
+    SAM_PLAIN(double, 0, 2, 8, 8, 4, 3, 8.1f, 0.245f, 8.1f, 0.245f),
+    SAM_PLAIN(double, 0, 4, 7, 13, 2, 2, 11.8f, 0.62f, 13.9f, 0.752f),
+    SAM_PLAIN(double, 0, 8, 4, 16, 2, 1, 13.1f, 1.42f, 15.4f, 1.68f),
     // 64 x 25 on 16 lanes: one wave per SIMD (its block is 200 VGPRs, the rest
     // in AGPRs), as on 32 lanes, but a group of four problems takes the time
     // of a group of two there (an FP64 sum over 32 lanes is some 18
     // instructions beside four FMAs per column): 64^3 level 2, 3.77 -> 1.86 ms
-    SAM_VARIANT(double, 0, 16, 4, 25, 1, 1, false, 29.f, 6.77f),
-    SAM_VARIANT(double, 0, 64, 2, 32, 1, 1, false, 60.6f, 54.8f),
-    SAM_VARIANT(double, 0, 1, 13, 5, 1, 5, false, 6.7f, 0.103f),
-    SAM_VARIANT(double, 0, 8, 4, 13, 2, 1, false, 11.1f, 0.843f),
+    SAM_PLAIN(double, 0, 16, 4, 25, 1, 1, 29.f, 6.77f, 29.f, 6.77f),
+    SAM_PLAIN(double, 0, 64, 2, 32, 1, 1, 60.6f, 54.8f, 60.6f, 54.8f),
+    SAM_PLAIN(double, 0, 1, 13, 5, 1, 5, 6.7f, 0.103f, 6.7f, 0.103f),
+    SAM_PLAIN(double, 0, 8, 4, 13, 2, 1, 11.1f, 0.843f, 12.9f, 0.958f),
     // soft-weighted (stacked penalty rows)
-    SAM_VARIANT(float, 1, 4, 7, 13, 2, 2, true, 0, 0),
-    SAM_VARIANT(float, 1, 16, 4, 25, 1, 1, true, 0, 0),
-    SAM_VARIANT(float, 1, 32, 3, 25, 1, 1, true, 0, 0),
-    SAM_VARIANT(float, 1, 64, 2, 32, 1, 1, true, 0, 0),
-    SAM_VARIANT(double, 0, 4, 8, 13, 2, 2, true, 0, 0),
-    SAM_VARIANT(double, 0, 64, 2, 25, 1, 1, true, 0, 0),
-    SAM_VARIANT(double, 0, 64, 2, 32, 1, 1, true, 0, 0),
+    SAM_WEIGHTED(float, 1, 4, 7, 13, 2, 2),
+    SAM_WEIGHTED(float, 1, 16, 4, 25, 1, 1),
+    SAM_WEIGHTED(float, 1, 32, 3, 25, 1, 1),
+    SAM_WEIGHTED(float, 1, 64, 2, 32, 1, 1),
+    SAM_WEIGHTED(double, 0, 4, 8, 13, 2, 2),
+    SAM_WEIGHTED(double, 0, 64, 2, 25, 1, 1),
+    SAM_WEIGHTED(double, 0, 64, 2, 32, 1, 1),
 };
 
 }  // namespace

@@ -58,11 +58,22 @@ struct NumericVariant {
     hipError_t (*launch)(const NumericArgs&, int grid, hipStream_t);
     hipError_t (*launch_backward)(const NumericArgs&, int grid, hipStream_t);  // weighted only
     int (*blocks_per_cu)();  // resident one-wave blocks per CU of the forward kernel (0: unknown)
+    // the plain launch for matrices most of whose columns are longer than
+    // G * LPL entries (one more entry per lane in registers; null: the same)
+    hipError_t (*launch_long)(const NumericArgs&, int grid, hipStream_t);
+    int (*blocks_per_cu_long)();
     // measured cost of a plain launch (0: not measured): one round of blocks
-    // (us), and a column once the GPU is full (ns)
-    float round_us, col_ns;
+    // (us), and a column once the GPU is full (ns); then the same on such
+    // matrices
+    float round_us, col_ns, round_us_long, col_ns_long;
     int max_rows() const { return G * R; }
     int per_wave() const { return 64 / G; }
+    // Columns longer than the lanes hold take a memory loop, a load at a time.
+    // A few of them (boundary rows, one dense column) are cheaper left to it
+    // than an entry more per lane for all: most columns have to be that long.
+    bool long_columns(int64_t n, int64_t nnzA, int longest) const {
+        return longest > G * LPL && nnzA >= (int64_t)(G * LPL - 1) * n;
+    }
 };
 // The compiled menu, ordered from the cheapest per column to the most
 // general for each precision.

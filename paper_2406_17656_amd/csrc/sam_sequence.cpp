@@ -444,10 +444,8 @@ sam_status sam_sequence_create(sam_ctx* ctx, const sam_csc* A0, const sam_csc* A
         sam_plan* pl = new (std::nothrow) sam_plan();
         if (!pl) return bail(fail(ctx, SAM_ERR_NOMEM, "host allocation failed"));
         q->plan = pl;
-        // with a rule the structural shapes are bounds only: the sources'
-        // columns may fall into any class of the menu
         if ((st = plan_init(ctx, pl, &skel, A0, q->S_cp, q->S_ri, q->nnzS, plan_mem, plan_sz, -1,
-                            spec->kind == SAM_SPARSIFY_NONE, s)))
+                            spec->kind != SAM_SPARSIFY_NONE, s)))
             return bail(st);
         if (pl->E > d.Ebound) return bail(fail(ctx, SAM_ERR_HIP, "gathered entries exceed their bound"));
     }
