@@ -10,24 +10,35 @@ using namespace samh;
 
 namespace {
 
-// Check of a column-pointer array (synchronising): cp[0] = 0, non-decreasing,
-// cp[n] = nnz.  The device checks it; a bad one is copied for its message.
-sam_status check_pointers(sam_ctx* ctx, const int32_t* cp, int n, int64_t nnz, const char* name, hipStream_t s) {
+// Checks of up to two column-pointer arrays (synchronising): cp[0] = 0,
+// non-decreasing, cp[n] = nnz.  The device checks them together; the first
+// bad one is copied for its message.
+struct Pointers {
+    const int32_t* cp;
+    int64_t nnz;
+    const char* name;
+};
+
+sam_status check_pointers(sam_ctx* ctx, int n, const Pointers* p, int count, hipStream_t s) {
+    StructureFacts f{};
+    sam_status st;
     if (n > 0) {
-        const samk::CscRef ref{(int)nnz, cp, nullptr, nullptr, nullptr};
-        StructureFacts f;
-        sam_status st;
-        if ((st = structure_facts(ctx, n, &ref, 1, &f, s)) || (st = read_facts(ctx, n, &f, s))) return st;
-        if (f.m[0].bad_cp == n) return SAM_OK;
+        samk::CscRef refs[2];
+        for (int i = 0; i < count; ++i) refs[i] = samk::CscRef{(int)p[i].nnz, p[i].cp, nullptr, nullptr, nullptr};
+        if ((st = structure_facts(ctx, n, refs, count, &f, s)) || (st = read_facts(ctx, n, &f, s))) return st;
     }
-    std::vector<int> h((size_t)n + 1);
-    HIP_TRY(ctx, hipMemcpyAsync(h.data(), cp, h.size() * 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(ctx, hipStreamSynchronize(s));
-    if (h[0] != 0 || h[(size_t)n] != nnz)
-        return fail(ctx, SAM_ERR_SHAPE, "%s[0] = %d, %s[n] = %d but nnz = %lld", name, h[0], name, h[(size_t)n],
-                    (long long)nnz);
-    for (int j = 0; j < n; ++j)
-        if (h[(size_t)j + 1] < h[(size_t)j]) return fail(ctx, SAM_ERR_UNSORTED, "%s decreases at column %d", name, j);
+    for (int i = 0; i < count; ++i) {
+        if (n > 0 && f.m[i].bad_cp == n) continue;
+        std::vector<int> h((size_t)n + 1);
+        HIP_TRY(ctx, hipMemcpyAsync(h.data(), p[i].cp, h.size() * 4, hipMemcpyDeviceToHost, s));
+        HIP_TRY(ctx, hipStreamSynchronize(s));
+        if (h[0] != 0 || h[(size_t)n] != p[i].nnz)
+            return fail(ctx, SAM_ERR_SHAPE, "%s[0] = %d, %s[n] = %d but nnz = %lld", p[i].name, h[0], p[i].name,
+                        h[(size_t)n], (long long)p[i].nnz);
+        for (int j = 0; j < n; ++j)
+            if (h[(size_t)j + 1] < h[(size_t)j])
+                return fail(ctx, SAM_ERR_UNSORTED, "%s decreases at column %d", p[i].name, j);
+    }
     return SAM_OK;
 }
 
@@ -78,8 +89,8 @@ sam_status sam_candidate_weights(sam_ctx* ctx, int32_t n, const int32_t* S_colpt
     sam_status st = need_device(ctx);
     if (st) return st;
     hipStream_t s = S(stream);
-    if ((st = check_pointers(ctx, S_colptr, n, nnz_S, "S_colptr", s))) return st;
-    if ((st = check_pointers(ctx, B_colptr, n, nnz_B, "B_colptr", s))) return st;
+    const Pointers both[2] = {{S_colptr, nnz_S, "S_colptr"}, {B_colptr, nnz_B, "B_colptr"}};
+    if ((st = check_pointers(ctx, n, both, 2, s))) return st;
     HIP_TRY(ctx, samk::candidate_weights(n, S_colptr, S_rowind, B_colptr, B_rowind, w_base, w_cand, w, s));
     return SAM_OK;
 }
@@ -100,7 +111,8 @@ sam_status sam_pattern_topk(sam_ctx* ctx, int32_t n, const int32_t* S_colptr, co
     int64_t* off = nullptr;
     void* stemp = nullptr;
     if ((st = check_ws(ctx, ws, ws_bytes, topk_layout(cv, n, &counts, &off, &stemp), "top-k workspace"))) return st;
-    if ((st = check_pointers(ctx, S_colptr, n, nnz_S, "S_colptr", s))) return st;
+    const Pointers one{S_colptr, nnz_S, "S_colptr"};
+    if ((st = check_pointers(ctx, n, &one, 1, s))) return st;
     HIP_TRY(ctx, samk::topk_count(n, S_colptr, S_rowind, w, grad, k, counts, s));
     HIP_TRY(ctx, samk::scan_counts(counts, n, off, out_colptr, nullptr, stemp, s));
     int64_t tot = 0;

@@ -181,11 +181,14 @@ hipError_t scan_counts(const int* counts, int64_t n, int64_t* off, int* off32, i
 // about 20 ns each: one per wave took 59 us for the gathered total of
 // n = 262144 alone, four per block of 256 threads 56 us, so blocks are large,
 // stride over the columns, and report only what the results do not hold yet.
-// A check takes 22 us at that size (mean over the four of a one-shot map),
-// 32 us with a thread per column.
+// Four columns a group are in flight at once, and the sums over lanes and
+// waves go through DPP rather than thirty shuffles and a serial loop: 10 us a
+// structure of 5 entries a column at that size (12 to 13 before; with a
+// thread per column 32 us), 5.5 us at n = 65536 (7.5).
 constexpr int kCheckThreads = 1024;
 constexpr int kCheckLanes = 8;
 constexpr int kCheckCols = kCheckThreads / kCheckLanes;
+constexpr int kCheckBatch = 4;   // columns per group in flight
 constexpr int kCheckBlocks = 256;
 
 __global__ void __launch_bounds__(kCheckThreads)
@@ -197,41 +200,91 @@ k_check(CheckArgs a) {
     const int g = threadIdx.x % kCheckLanes;
     int bad = n, bad_cp = n, longest = 0, missing = 0;
     long long gathered = 0;
-    for (int64_t jj = (int64_t)blockIdx.x * kCheckCols + threadIdx.x / kCheckLanes; jj < n;
-         jj += (int64_t)gridDim.x * kCheckCols) {   // whole groups of lanes
-        const int j = (int)jj;
-        const int lo = m.cp[j], hi = m.cp[j + 1];
-        bool ok = lo <= hi && !(j == 0 && lo != 0) && !(j == n - 1 && hi != m.nnz);
-        if (!ok) bad_cp = min(bad_cp, j);
-        ok &= lo >= 0 && hi <= m.nnz;
-        int e_j = 0, diag = 0;
-        if (ok && m.ri) {
-            for (int64_t e = (int64_t)lo + g; e < hi; e += kCheckLanes) {
-                const int r = m.ri[e], prev = e > lo ? m.ri[e - 1] : -1;
-                ok &= r > prev && r < n;
-                diag |= r == j;
-                if (m.gather_cp && r >= 0 && r < n) e_j += m.gather_cp[r + 1] - m.gather_cp[r];
+    // unsigned: columns and entries up to INT_MAX plus a step stay in range
+    for (unsigned j0 = blockIdx.x * (unsigned)(kCheckCols * kCheckBatch) + threadIdx.x / kCheckLanes;
+         j0 < (unsigned)n; j0 += gridDim.x * (unsigned)(kCheckCols * kCheckBatch)) {   // whole groups of lanes
+        int lo[kCheckBatch], hi[kCheckBatch], last[kCheckBatch], e_j[kCheckBatch];
+        unsigned end[kCheckBatch];
+        bool ok[kCheckBatch], diag[kCheckBatch];
+        int steps = 0;
+#pragma unroll
+        for (int u = 0; u < kCheckBatch; ++u) {
+            const unsigned j = j0 + u * kCheckCols;
+            lo[u] = j < (unsigned)n ? m.cp[j] : 0;
+            hi[u] = j < (unsigned)n ? m.cp[j + 1] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kCheckBatch; ++u) {
+            const unsigned j = j0 + u * kCheckCols;
+            ok[u] = j >= (unsigned)n ||
+                    (lo[u] <= hi[u] && !(j == 0 && lo[u] != 0) && !(j == (unsigned)n - 1 && hi[u] != m.nnz));
+            if (!ok[u]) bad_cp = min(bad_cp, (int)j);
+            ok[u] &= lo[u] >= 0 && hi[u] <= m.nnz;
+            end[u] = (unsigned)(ok[u] && m.ri ? hi[u] : lo[u]);
+            if (ok[u] && m.ri) steps = max(steps, (int)(((unsigned)(hi[u] - lo[u]) + kCheckLanes - 1) / kCheckLanes));
+            last[u] = -1;
+            e_j[u] = 0;
+            diag[u] = false;
+        }
+        for (int t = 0; t < steps; ++t) {
+            int r[kCheckBatch], c0[kCheckBatch], c1[kCheckBatch];
+            bool mine[kCheckBatch];
+#pragma unroll
+            for (int u = 0; u < kCheckBatch; ++u) {
+                const unsigned e = (unsigned)lo[u] + (unsigned)(t * kCheckLanes + g);
+                mine[u] = e < end[u];
+                r[u] = mine[u] ? m.ri[e] : INT_MAX;
+            }
+            if (m.gather_cp) {
+#pragma unroll
+                for (int u = 0; u < kCheckBatch; ++u) {
+                    const bool in = (unsigned)r[u] < (unsigned)n;
+                    c0[u] = in ? m.gather_cp[r[u]] : 0;
+                    c1[u] = in ? m.gather_cp[r[u] + 1] : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < kCheckBatch; ++u) e_j[u] += c1[u] - c0[u];
+            }
+#pragma unroll
+            for (int u = 0; u < kCheckBatch; ++u) {
+                const int before = dppi<0x111>(r[u]);   // the lane before, inside its row of 16
+                ok[u] &= !mine[u] || (r[u] > (g ? before : last[u]) && r[u] < n);
+                diag[u] |= mine[u] && r[u] == (int)(j0 + u * kCheckCols);
+                if (t + 1 < steps) last[u] = __shfl(r[u], kCheckLanes - 1, kCheckLanes);
             }
         }
-        if (!ok) bad = min(bad, j);
-        diag = grp_max<kCheckLanes>(diag);
-        if (m.gather_cp) e_j = grp_sum<kCheckLanes>(e_j);
-        if (g == 0) {
-            const int len = hi - lo;
-            longest = max(longest, len);
-            missing += 1 - diag;
-            gathered += e_j;
-            if (m.gather_counts) m.gather_counts[j] = e_j;
+#pragma unroll
+        for (int u = 0; u < kCheckBatch; ++u) {
+            const unsigned j = j0 + u * kCheckCols;
+            if (!ok[u]) bad = min(bad, (int)j);
+            const int d = grp_max<kCheckLanes>(diag[u] ? 1 : 0);
+            if (m.gather_cp) e_j[u] = grp_sum<kCheckLanes>(e_j[u]);
+            if (g == 0 && j < (unsigned)n) {
+                longest = max(longest, hi[u] - lo[u]);
+                missing += 1 - d;
+                gathered += e_j[u];
+                if (m.gather_counts) m.gather_counts[j] = e_j[u];
+            }
         }
     }
+    // rows of 16 lanes by DPP, the rest by shuffles; then the block's waves
+    static_assert(kCheckThreads / 64 == 16, "a row of lanes adds up the waves");
+    auto row16 = [&] {
+        bad = grp_min<16>(bad);
+        bad_cp = grp_min<16>(bad_cp);
+        longest = grp_max<16>(longest);
+        missing = grp_sum<16>(missing);
+    };
+    row16();
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
+    for (int d = 32; d >= 16; d >>= 1) {
         bad = min(bad, __shfl_xor(bad, d));
         bad_cp = min(bad_cp, __shfl_xor(bad_cp, d));
         longest = max(longest, __shfl_xor(longest, d));
         missing += __shfl_xor(missing, d);
-        gathered += __shfl_xor(gathered, d);
     }
+#pragma unroll
+    for (int d = 32; d >= kCheckLanes; d >>= 1) gathered += __shfl_xor(gathered, d);   // only lanes g = 0 hold any
     CscFacts* f = a.facts + blockIdx.y;
     const int wv = threadIdx.x >> 6;
     if (wave_lane() == 0) {
@@ -242,14 +295,16 @@ k_check(CheckArgs a) {
         sh_e[wv] = gathered;
     }
     __syncthreads();
+    if (threadIdx.x >= 16) return;
+    bad = sh_i[0][threadIdx.x];
+    bad_cp = sh_i[1][threadIdx.x];
+    longest = sh_i[2][threadIdx.x];
+    missing = sh_i[3][threadIdx.x];
+    gathered = sh_e[threadIdx.x];
+    row16();
+#pragma unroll
+    for (int d = 8; d >= 1; d >>= 1) gathered += __shfl_xor(gathered, d);
     if (threadIdx.x == 0) {
-        for (int w = 1; w < kCheckThreads / 64; ++w) {
-            bad = min(bad, sh_i[0][w]);
-            bad_cp = min(bad_cp, sh_i[1][w]);
-            longest = max(longest, sh_i[2][w]);
-            missing += sh_i[3][w];
-            gathered += sh_e[w];
-        }
         if (bad < n) atomicMin(&f->bad, bad);
         if (bad_cp < n) atomicMin(&f->bad_cp, bad_cp);
         // k_check_init put a column's length here, so most blocks have nothing
@@ -273,7 +328,7 @@ __global__ void k_check_init(CheckArgs a) {
 hipError_t check_structures(const CheckArgs& a, hipStream_t s) {
     if (a.n <= 0 || a.count <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_check_init, dim3(1), dim3(64), 0, s, a);
-    const unsigned nb = (unsigned)std::min<int64_t>(ceil_div(a.n, kCheckCols), kCheckBlocks);
+    const unsigned nb = (unsigned)std::min<int64_t>(ceil_div(a.n, kCheckCols * kCheckBatch), kCheckBlocks);
     hipLaunchKernelGGL(k_check, dim3(nb, (unsigned)a.count), dim3(kCheckThreads), 0, s, a);
     return hipGetLastError();
 }
