@@ -214,12 +214,13 @@ __device__ inline void wave_sync() {
 // which adds an exact zero.  Every lane takes part; rows with live = false
 // give 0.
 // PERM: the values are read through the row view's permutation (else they
-// are in the row view's order).  SCALE: x is scale .* x.
+// are in the row view's order).  SCALE: x is scale .* x.  DIV: x is x / div
+// (before the scale).
 constexpr int kSpmvLanes = 4;
 constexpr int kSpmvUnroll = 4;
-template <bool F32, bool PERM, bool SCALE>
+template <bool F32, bool PERM, bool SCALE, bool DIV = false>
 __device__ inline double row_product(bool live, int i, const int* rowptr, const int* colind, const int* perm,
-                                     const void* val, const double* x, const double* scale) {
+                                     const void* val, const double* x, const double* scale, double div = 1.0) {
     const int g = threadIdx.x % kSpmvLanes;
     double s = 0.0;
     if (live) {
@@ -235,7 +236,10 @@ __device__ inline double row_product(bool live, int i, const int* rowptr, const 
                 v[u] = F32 ? (double)static_cast<const float*>(val)[ev] : static_cast<const double*>(val)[ev];
             }
 #pragma unroll
-            for (int u = 0; u < kSpmvUnroll; ++u) xv[u] = SCALE ? scale[c[u]] * x[c[u]] : x[c[u]];
+            for (int u = 0; u < kSpmvUnroll; ++u) {
+                xv[u] = DIV ? x[c[u]] / div : x[c[u]];
+                if (SCALE) xv[u] = scale[c[u]] * xv[u];
+            }
 #pragma unroll
             for (int u = 0; u < kSpmvUnroll; ++u) s = fma(e + u * kSpmvLanes < b ? v[u] : 0.0, xv[u], s);
         }

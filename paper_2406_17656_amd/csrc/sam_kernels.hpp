@@ -176,7 +176,8 @@ struct GmresArgs {
 };
 int gmres_chunks(int n);
 hipError_t gmres_init(int restart, double beta, double* state, hipStream_t s);
-hipError_t gmres_step(const GmresArgs& a, int k, hipStream_t s);
+// Steps first .. first + count - 1 of the cycle.
+hipError_t gmres_steps(const GmresArgs& a, int first, int count, hipStream_t s);
 hipError_t gmres_solution(int n, int used, const double* y, const double* Z, double* x, hipStream_t s);
 
 // ---------------------------------------------------------------- adjoint

@@ -4,7 +4,7 @@
 //     v_{k+1} = w / ||w||,  and the Givens rotation of the new column of H.
 //
 // The orthogonalisation is classical Gram-Schmidt taken twice: all dot
-// products of a pass in one kernel, all updates in the next, so a step is five
+// products of a pass in one kernel, all updates in the next, so a step is four
 // launches whatever k is (modified Gram-Schmidt needs a reduction over the
 // whole vector per earlier vector), and the basis is orthogonal to rounding.
 //
@@ -12,9 +12,9 @@
 // pass) goes straight on to its chunk's share of the next dot products.  The
 // kernels are bound by the latency of their dependent loads, so a row has
 // four threads: four lanes of its product with A, then a quarter of the basis
-// vectors each: 27 us per step of a 128 x 128 system with a level-2 FP64 map
-// (mean over a cycle of 50), against 36 us with one thread per row and about
-// 900 us with one host-synchronised dot product per earlier vector.  Every sum
+// vectors each: 25 us per step of a 128 x 128 system with a level-2 FP64 map
+// (mean over a cycle of 50; 36 us with one thread per row, and 900 us with one
+// host-synchronised dot product per earlier vector).  Every sum
 // has a fixed order (lanes, waves, chunks), so runs are bitwise repeatable.
 //
 // The residual test runs on the device: once it holds, `done` is set and the
@@ -233,50 +233,98 @@ k_gm_update_norm(int n, int count, int chunks, const double* src, const double* 
     }
 }
 
-// v_{k+1} = w / ||w||; block 0 rotates H's column k and the right side.
+// Givens rotation of H's column k (its first k + 1 entries; hn = ||w|| below
+// them) and of the right side; one block, sh: 3 (k + 1) doubles.
+__device__ inline void rotate_column(int k, int restart, double hn, double* Hcol, double* cs, double* sn, double tol,
+                                     double* state, double* sh) {
+    double *hc = sh, *c = sh + k + 1, *d = c + k + 1;
+    for (int i = threadIdx.x; i <= k; i += kFlat) {
+        hc[i] = Hcol[i];
+        c[i] = i < k ? cs[i] : 0.0;
+        d[i] = i < k ? sn[i] : 0.0;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double* g = state + 2 + restart;
+    double a = hc[0];
+    for (int i = 0; i < k; ++i) {     // earlier rotations
+        const double b = hc[i + 1];
+        Hcol[i] = c[i] * a + d[i] * b;
+        a = -d[i] * a + c[i] * b;
+    }
+    const double den = hypot(a, hn);
+    const double ck = den == 0.0 ? 1.0 : a / den, sk = den == 0.0 ? 0.0 : hn / den;
+    cs[k] = ck;
+    sn[k] = sk;
+    Hcol[k] = ck * a + sk * hn;
+    Hcol[k + 1] = 0.0;
+    const double gk = g[k];
+    g[k + 1] = -sk * gk;
+    g[k] = ck * gk;
+    state[2 + k] = fabs(sk * gk);
+    state[0] = k + 1;
+    if (fabs(sk * gk) <= tol || hn == 0.0) state[1] = 1.0;
+}
+
+// ||w|| from the chunks' shares, the same in every thread; negative once the
+// cycle is done (block 0 of the same launch may be setting that: a block looks
+// once).
+__device__ inline double step_norm(const double* nrm, int chunks, const double* state, double* hn_sh) {
+    if (threadIdx.x < 64) {
+        const double s = wave_sum_of(nrm, chunks);
+        if (threadIdx.x == 0)
+            *hn_sh = __hip_atomic_load(state + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0.0 ? -1.0 : sqrt(s);
+    }
+    __syncthreads();
+    return *hn_sh;
+}
+
+// The last step of a batch: v_{k+1} = w / ||w||, block 0 the rotation.
 __global__ void __launch_bounds__(kFlat)
 k_gm_next(int n, int k, int restart, int chunks, const double* nrm, const double* w, double* vnext, double* Hcol,
           double* cs, double* sn, double tol, double* state) {
-    if (state[1] != 0.0) return;
     extern __shared__ double sh[];     // H column, cs, sn: 3 (k + 1)
     __shared__ double hn_sh;
-    if (threadIdx.x < 64) {
-        const double s = wave_sum_of(nrm, chunks);
-        if (threadIdx.x == 0) hn_sh = sqrt(s);
-    }
-    double *hc = sh, *c = sh + k + 1, *d = c + k + 1;
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i <= k; i += kFlat) {
-            hc[i] = Hcol[i];
-            c[i] = i < k ? cs[i] : 0.0;
-            d[i] = i < k ? sn[i] : 0.0;
-        }
-    __syncthreads();
-    const double hn = hn_sh;
+    const double hn = step_norm(nrm, chunks, state, &hn_sh);
+    if (hn < 0.0) return;
     int r0, r1;
     chunk_range(n, r0, r1);
     if (hn != 0.0)
         for (int r = r0 + (int)threadIdx.x; r < r1; r += kFlat) vnext[r] = w[r] / hn;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        double* g = state + 2 + restart;
-        double a = hc[0];
-        for (int i = 0; i < k; ++i) {     // earlier rotations
-            const double b = hc[i + 1];
-            Hcol[i] = c[i] * a + d[i] * b;
-            a = -d[i] * a + c[i] * b;
+    if (blockIdx.x == 0) rotate_column(k, restart, hn, Hcol, cs, sn, tol, state, sh);
+}
+
+// Between two steps of a batch: the rotation of column k in block 0, in the
+// others v_{k+1} = w / ||w|| and the next step's z = N (d .* v_{k+1}), which
+// divides the entries of w that it gathers itself (the same quotients) instead
+// of waiting for a launch that writes them: 3.8 us at n = 16384 with a level-2
+// FP64 map, 3.4 + 3.2 us as two launches, and one gap between launches less.
+template <bool MAP, bool F32>
+__global__ void __launch_bounds__(kFlat)
+k_gm_next_precond(int n, int k, int restart, int chunks, const double* nrm, const double* w, double* vnext,
+                  double* Hcol, double* cs, double* sn, double tol, double* state, const int* rowptr,
+                  const int* colind, const void* val, const double* d, double* z) {
+    extern __shared__ double sh[];     // H column, cs, sn: 3 (k + 1)
+    __shared__ double hn_sh;
+    const double hn = step_norm(nrm, chunks, state, &hn_sh);
+    if (hn < 0.0) return;
+    if (blockIdx.x == 0) {
+        rotate_column(k, restart, hn, Hcol, cs, sn, tol, state, sh);
+        return;
+    }
+    if (hn == 0.0) return;
+    const int64_t t = (int64_t)(blockIdx.x - 1) * kFlat + threadIdx.x;
+    if constexpr (MAP) {
+        const int i = (int)(t / kSpmvLanes);
+        const double s = row_product<F32, false, true, true>(i < n, i, rowptr, colind, nullptr, val, w, d, hn);
+        if (i < n && t % kSpmvLanes == 0) {
+            z[i] = s;
+            vnext[i] = w[i] / hn;
         }
-        const double den = hypot(a, hn);
-        const double ck = den == 0.0 ? 1.0 : a / den, sk = den == 0.0 ? 0.0 : hn / den;
-        cs[k] = ck;
-        sn[k] = sk;
-        Hcol[k] = ck * a + sk * hn;
-        Hcol[k + 1] = 0.0;
-        const double gk = g[k];
-        g[k + 1] = -sk * gk;
-        g[k] = ck * gk;
-        state[2 + k] = fabs(sk * gk);
-        state[0] = k + 1;
-        if (fabs(sk * gk) <= tol || hn == 0.0) state[1] = 1.0;
+    } else if (t < n) {
+        const double v = w[t] / hn;
+        z[t] = d[t] * v;
+        vnext[t] = v;
     }
 }
 
@@ -310,22 +358,15 @@ hipError_t gmres_init(int restart, double beta, double* state, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t gmres_step(const GmresArgs& a, int k, hipStream_t s) {
+namespace {
+
+// A step up to the chunks' shares of ||w||; z is there already.
+void enqueue_step(const GmresArgs& a, int k, hipStream_t s) {
     const int n = a.n, count = k + 1;
     const int chunks = gmres_chunks(n);
-    const dim3 block(kThreads), flat(kFlat), rows4(blocks_for((int64_t)n * kSpmvLanes)), cg((unsigned)chunks);
-    const double* v = a.V + (int64_t)k * n;
-    double* z = a.Z + (int64_t)k * n;
+    const dim3 block(kThreads), cg((unsigned)chunks);
+    const double* z = a.Z + (int64_t)k * n;
     double* Hcol = a.H + (int64_t)k * (a.restart + 1);
-    if (!a.N_rowptr)
-        hipLaunchKernelGGL((k_gm_precond<false, false>), dim3(blocks_for(n)), flat, 0, s, n, nullptr, nullptr,
-                           nullptr, a.d, v, z, a.state);
-    else if (a.N_f32)
-        hipLaunchKernelGGL((k_gm_precond<true, true>), rows4, flat, 0, s, n, a.N_rowptr, a.N_colind, a.N_val, a.d, v,
-                           z, a.state);
-    else
-        hipLaunchKernelGGL((k_gm_precond<true, false>), rows4, flat, 0, s, n, a.N_rowptr, a.N_colind, a.N_val, a.d,
-                           v, z, a.state);
     const size_t wave_sums = sizeof(double) * kRowWaves * (size_t)count, coef = sizeof(double) * (size_t)count;
     hipLaunchKernelGGL(k_gm_apply_dots, cg, block, wave_sums, s, n, a.A_rowptr, a.A_colind, a.A_val, z, a.w, count,
                        a.V, a.part, a.state);
@@ -345,8 +386,41 @@ hipError_t gmres_step(const GmresArgs& a, int k, hipStream_t s) {
         hipLaunchKernelGGL(k_gm_reduce, dim3((unsigned)count), dim3(64), 0, s, chunks, a.part2, a.h2, a.state);
     hipLaunchKernelGGL(k_gm_update_norm, cg, block, coef, s, n, count, own ? chunks : 0, own ? a.part2 : a.h2, a.V,
                        a.w, a.h1, Hcol, a.nrm, a.state);
-    hipLaunchKernelGGL(k_gm_next, cg, flat, 3 * coef, s, n, k, a.restart, chunks, a.nrm, a.w,
-                       a.V + (int64_t)(k + 1) * n, Hcol, a.cs, a.sn, a.tol, a.state);
+}
+
+}  // namespace
+
+hipError_t gmres_steps(const GmresArgs& a, int first, int count, hipStream_t s) {
+    if (count <= 0) return hipSuccess;
+    const int n = a.n, chunks = gmres_chunks(n);
+    const dim3 flat(kFlat);
+    const unsigned rows = blocks_for(a.N_rowptr ? (int64_t)n * kSpmvLanes : n);
+    for (int k = first; k < first + count; ++k) {
+        double *v = a.V + (int64_t)k * n, *z = a.Z + (int64_t)k * n;
+        if (k == first) {
+            auto run = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(rows), flat, 0, s, n, a.N_rowptr, a.N_colind, a.N_val, a.d, v, z,
+                                   a.state);
+            };
+            if (!a.N_rowptr) run(k_gm_precond<false, false>);
+            else if (a.N_f32) run(k_gm_precond<true, true>);
+            else run(k_gm_precond<true, false>);
+        } else {
+            auto run = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(rows + 1), flat, 3 * sizeof(double) * (size_t)k, s, n, k - 1,
+                                   a.restart, chunks, a.nrm, a.w, v, a.H + (int64_t)(k - 1) * (a.restart + 1), a.cs,
+                                   a.sn, a.tol, a.state, a.N_rowptr, a.N_colind, a.N_val, a.d, z);
+            };
+            if (!a.N_rowptr) run(k_gm_next_precond<false, false>);
+            else if (a.N_f32) run(k_gm_next_precond<true, true>);
+            else run(k_gm_next_precond<true, false>);
+        }
+        enqueue_step(a, k, s);
+    }
+    const int k = first + count - 1;
+    hipLaunchKernelGGL(k_gm_next, dim3((unsigned)chunks), flat, 3 * sizeof(double) * (size_t)(k + 1), s, n, k,
+                       a.restart, chunks, a.nrm, a.w, a.V + (int64_t)(k + 1) * n,
+                       a.H + (int64_t)k * (a.restart + 1), a.cs, a.sn, a.tol, a.state);
     return hipGetLastError();
 }
 

@@ -70,7 +70,7 @@ sam_status sam_gmres_steps(sam_ctx* ctx, int32_t n, const int32_t* A_rowptr, con
     a.state = state;
     a.tol = tol;
     if (first == 0) HIP_TRY(ctx, samk::gmres_init(restart, beta, state, s));
-    for (int32_t k = first; k < first + count; ++k) HIP_TRY(ctx, samk::gmres_step(a, k, s));
+    HIP_TRY(ctx, samk::gmres_steps(a, first, count, s));
     return SAM_OK;
 }
 
