@@ -17,24 +17,27 @@ __device__ inline double mval(const void* M, int e, int f32) {
 
 // Eight (or 16) lanes per column j.  The rows of column j of
 // A_k M - A_0 are the union U of rows(A_k(:, l)) for l in M(:, j) and
-// rows(A_0(:, j)); U is built as a bitmap over a window of kResRows rows (the
-// sweep jumps to the next occupied window), the rank of a row inside U
-// indexes the LDS accumulator, and contributions are added column by column
-// of M, the lanes taking the entries of one A_k column at a time: rows are
-// distinct inside it, so the lanes of one instruction never share a slot and
-// every row's sum keeps the order of M's entries (A_0 last).
+// rows(A_0(:, j)); every row of U has an LDS accumulator, and contributions
+// are added column by column of M, the lanes taking the entries of one A_k
+// column at a time: rows are distinct inside it, so the lanes of one
+// instruction never share a slot and every row's sum keeps the order of M's
+// entries (A_0 last).
 //
-// Bound: the latency of the dependent loads (column of M, its extents in
-// A_k, the entries).  One wave per column, one A_k column after the other,
-// kept five of 64 lanes busy and paid every round trip in series: 2.76 ms for
-// the 512 x 512 level-2 map.  Eight problems per wave took it to 0.18 ms with
-// each pass over the entries (bitmap, accumulation) fetching them anew in
-// batches of eight; columns whose entries fit the registers fetch them once,
-// all loads independent: 0.11 ms (63 x 25 blocks of the 64^3 seven-point map:
-// 4.26 -> 1.07 ms).
+// U is built as a bitmap over a window of kResRows rows (the sweep jumps to
+// the next occupied window), and the rank of a row inside U picks its
+// accumulator.  The TABLE forms find it in a small hash table keyed by the row
+// instead (columns whose entries fit the registers, fetched once, all loads
+// independent): its cost does not depend on where the rows lie.  More rows
+// than slots: the bitmap again.
+//
+// Bound: VALU and LDS instructions per entry, and the latency of the
+// dependent loads (column of M, its extents in A_k, the entries).  One wave
+// per column took 2.76 ms for the 512 x 512 level-2 map, eight problems per
+// wave 0.18 ms, with the entries held in registers 0.11 ms.  Windows -> table,
+// us: 64^3 seven-point level 1 238 -> 157, level 2 1070 -> 388; 512^2 level 3
+// 495 -> 388.
 constexpr int kResWPL = 16;               // bitmap words per lane
-constexpr int kResAcc = 64;               // accumulators per column and pass
-constexpr int kResAccStride = 68;         // 8 banks apart: eight columns cover the 64 banks
+constexpr int kResAcc = 64;               // accumulators per column and pass (bitmap form)
 
 struct alignas(16) ResList {  // one column of M's pattern: its run in A_k and its value
     int start, len;
@@ -43,7 +46,7 @@ struct alignas(16) ResList {  // one column of M's pattern: its run in A_k and i
 
 // kResLanes lanes per column, kResBatch columns of M per problem held in
 // registers: 8 and 16, or 16 and 32.
-template <int kResLanes, int kResBatch>
+template <int kResLanes, int kResBatch, bool TABLE>
 __global__ void __launch_bounds__(64)
 k_residual_columns(int n, const int* Ak_cp, const int* Ak_ri, const double* Ak_v, const int* A0_cp,
                    const int* A0_ri, const double* A0_v, const int* M_cp, const int* M_ri,
@@ -54,7 +57,14 @@ k_residual_columns(int n, const int* Ak_cp, const int* Ak_ri, const double* Ak_v
     // words touch 64 consecutive words
     __shared__ unsigned bm[kResWPL * 64];
     __shared__ unsigned short pre[kResWPL * 64];
+    // table slots per column: twice the rows of a level-2 column and more
+    // (25 of a five-point, 63 of a seven-point stencil)
+    constexpr int kHashBits = kResLanes == 8 ? 6 : 7;
+    constexpr int kHash = 1 << kHashBits;
+    constexpr int kResAccStride = (TABLE ? kHash : kResAcc) + 4;   // 8 banks apart: eight columns cover the 64 banks
+    static_assert(kHash >= kResAcc, "the bitmap form uses the same accumulators");
     __shared__ double accs[kResCols * kResAccStride];
+    __shared__ int keys[TABLE ? kResCols * kHash : 1];
     __shared__ ResList lists[kResCols][kResBatch];
     const int lane = wave_lane();
     const int g = lane % kResLanes, q = lane / kResLanes;
@@ -125,6 +135,69 @@ k_residual_columns(int n, const int* Ak_cp, const int* Ak_ri, const double* Ak_v
             for (int u = 0; u < kResBatch; ++u) vals[u] *= lists[q][u].m;
 #pragma unroll
             for (int u = 0; u <= kResBatch; ++u) lo = rows[u] >= 0 ? min(lo, rows[u]) : lo;
+            if constexpr (TABLE) {
+                int* key = keys + q * kHash;
+#pragma unroll
+                for (int i = 0; i < kHash / kResLanes; ++i) {
+                    key[i * kResLanes + g] = -1;
+                    acc[i * kResLanes + g] = 0.0;
+                }
+                wave_sync();
+                bool full = false;
+                constexpr int kTries = 11;   // first tries in flight together: 17 = 11 + 6, 33 = 3 * 11
+#pragma unroll
+                for (int u0 = 0; u0 <= kResBatch; u0 += kTries) {
+                    int at[kTries], seen[kTries];
+#pragma unroll
+                    for (int i = 0; i < kTries; ++i) {
+                        const int u = u0 + i;
+                        seen[i] = -1;
+                        if (u > kResBatch) continue;
+                        at[i] = (int)(((unsigned)rows[u] * 0x9E3779B1u) >> (32 - kHashBits));
+                        if (rows[u] >= 0) seen[i] = atomicCAS(&key[at[i]], -1, rows[u]);
+                    }
+                    // taken slots: the next ones, again all together
+                    bool more = true;
+                    for (int tries = 1; more; ++tries) {
+                        more = false;
+#pragma unroll
+                        for (int i = 0; i < kTries; ++i) {
+                            const int u = u0 + i;
+                            if (u > kResBatch) continue;
+                            if (seen[i] != -1 && seen[i] != rows[u]) {
+                                at[i] = (at[i] + 1) & (kHash - 1);
+                                seen[i] = atomicCAS(&key[at[i]], -1, rows[u]);
+                            }
+                        }
+#pragma unroll
+                        for (int i = 0; i < kTries; ++i)
+                            if (u0 + i <= kResBatch) more |= seen[i] != -1 && seen[i] != rows[u0 + i];
+                        if (tries == kHash) {
+                            full |= more;
+                            break;
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < kTries; ++i) {
+                        const int u = u0 + i;
+                        if (u <= kResBatch && rows[u] >= 0)
+                            __hip_atomic_fetch_add(&acc[at[i]], vals[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    }
+                }
+                wave_sync();
+                if (__ballot(full) == 0ull) {   // wave-uniform
+                    double s = 0.0;   // empty slots hold zeros
+#pragma unroll
+                    for (int i = 0; i < kHash / kResLanes; ++i) {
+                        const double x = acc[i * kResLanes + g];
+                        s += x * x;
+                    }
+                    s = group_sum<kResLanes>(s);
+                    if (valid && g == 0) col_out[j] = s;
+                    wave_sync();
+                    continue;
+                }
+            }
         } else {   // the columns are ascending, so the smallest row heads one of them
             for (int t = ma + g; t < mb; t += kResLanes) {
                 const int l = M_ri[t];
@@ -216,20 +289,25 @@ hipError_t residual_columns(int n, int64_t nnzA, int64_t nnzM, const int* Ak_cp,
     // Eight lanes per column where most columns of A_k and A_0 have at most
     // eight entries and those of M at most 16 (means of 7 and 14: stencil
     // columns are the same length but for the boundary), else 16 lanes, which
-    // hold columns of 16 entries and 32 columns of M.  Narrow / wide, us:
-    // 512^2 level 1 91 / 354, level 2 113 / 407, level 3 713 / 497; 64^3
-    // level 1 238 / 674, level 2 2275 / 1090; 1024^2 nine-point level 2
-    // 4057 / 1962.
+    // hold columns of 16 entries and 32 columns of M.  The table pays off in
+    // the 16-lane form, and in the other for columns of more than six entries
+    // (three-dimensional stencils, whose rows span planes); shorter ones have
+    // their rows in a window or two and keep the registers and LDS that it
+    // takes for more waves.  Bitmap / table, us: eight lanes 512^2 level 1
+    // 91 / 115, level 2 113 / 133, 64^3 level 1 238 / 155; sixteen lanes 512^2
+    // level 3 495 / 388, 64^3 level 2 1070 / 388, 1024^2 nine-point level 2
+    // 1955 / 1540, level 1 1418 / 1252.
     const bool narrow = nnzA <= (int64_t)7 * n && nnzM <= (int64_t)14 * n;
     const int cols = narrow ? 8 : 4;
     // up to 12 one-wave blocks per CU are resident
     const int grid = launch_grid(((int64_t)n + cols - 1) / cols, 256 * 12);
-    if (narrow)
-        hipLaunchKernelGGL((k_residual_columns<8, 16>), dim3(grid), dim3(64), 0, s, n, Ak_cp, Ak_ri, Ak_v, A0_cp,
-                           A0_ri, A0_v, M_cp, M_ri, M_v, m_is_f32, col_out, status);
-    else
-        hipLaunchKernelGGL((k_residual_columns<16, 32>), dim3(grid), dim3(64), 0, s, n, Ak_cp, Ak_ri, Ak_v, A0_cp,
-                           A0_ri, A0_v, M_cp, M_ri, M_v, m_is_f32, col_out, status);
+    auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, n, Ak_cp, Ak_ri, Ak_v, A0_cp, A0_ri, A0_v, M_cp, M_ri,
+                           M_v, m_is_f32, col_out, status);
+    };
+    if (!narrow) run(k_residual_columns<16, 32, true>);
+    else if (nnzA > (int64_t)6 * n) run(k_residual_columns<8, 16, true>);
+    else run(k_residual_columns<8, 16, false>);
     return hipGetLastError();
 }
 
