@@ -968,7 +968,8 @@ sam_status sam_plan_size(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0, con
 }
 
 // sam_plan_create with every combination of precision and weighting, or
-// (only_prec >= 0, the one-shot build) the plain maps of one precision alone.
+// (only_prec >= 0, the one-shot build) the plain maps of one precision alone,
+// whose buckets are left to the stream.
 static sam_status create_plan(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0, const int32_t* S_colptr,
                               const int32_t* S_rowind, int64_t nnz_S, void* mem, size_t mem_bytes, int only_prec,
                               sam_plan** plan, sam_stream_t stream) {
@@ -992,6 +993,12 @@ static sam_status create_plan(sam_ctx* ctx, const sam_csc* Ak, const sam_csc* A0
     if ((st = plan_init(ctx, pl, Ak, A0, S_colptr, S_rowind, nnz_S, mem, mem_bytes, only_prec, false, s))) {
         delete pl;
         return st;
+    }
+    // the one-shot build runs on this stream; a plan may be used on any: its
+    // buckets have to be there
+    if (only_prec < 0 && hipStreamSynchronize(s) != hipSuccess) {
+        delete pl;
+        return fail(ctx, SAM_ERR_HIP, "plan creation: the stream's work failed");
     }
     *plan = pl;
     return SAM_OK;

@@ -238,6 +238,7 @@ sam_status pattern_fill(sam_ctx* ctx, int n, const PatternResult& res, int* S_cp
 // capacity).
 size_t plan_bytes(int n, int64_t E, int nnzA0, int partcap);
 // A plan in caller memory `mem` (>= plan_bytes).  Checks the three structures.
+// The bucket sorts are left on the stream.
 // only_prec >= 0: the classes of that precision's plain maps alone.  shrinks:
 // S bounds the patterns the plan's classes will serve (a sequence with a
 // sparsification rule).

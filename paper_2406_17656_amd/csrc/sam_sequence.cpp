@@ -481,9 +481,12 @@ sam_status sam_sequence_create(sam_ctx* ctx, const sam_csc* A0, const sam_csc* A
     }
     if (hipStreamCreateWithFlags(&q->cap, hipStreamNonBlocking) != hipSuccess)
         return bail(fail(ctx, SAM_ERR_HIP, "stream creation failed"));
+    // runs may come on any stream: wait for the buckets (set_bounds does)
     if (q->replan) {
         sam_status st2 = set_bounds(q, s);
         if (st2) return bail(st2);
+    } else if (hipStreamSynchronize(s) != hipSuccess) {
+        return bail(fail(ctx, SAM_ERR_HIP, "sequence creation: the stream's work failed"));
     }
     *out = q;
     return SAM_OK;
