@@ -69,6 +69,16 @@ struct sam_seq {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<const void*> key;
+    // the stream of exec's last launch: no wait has followed it yet
+    bool running = false;
+    hipStream_t last = nullptr;
+    // replaced graphs whose last launch may still run, oldest first
+    struct Retired {
+        hipGraph_t graph;
+        hipGraphExec_t exec;
+        hipEvent_t end;
+    };
+    std::vector<Retired> retired;
 };
 
 namespace {
@@ -119,12 +129,62 @@ sam_status set_bounds(sam_seq* q, hipStream_t s) {
     return SAM_OK;
 }
 
-void drop_graph(sam_seq* q) {
-    if (q->exec) (void)hipGraphExecDestroy(q->exec);
-    if (q->graph) (void)hipGraphDestroy(q->graph);
+void forget_graph(sam_seq* q) {
     q->exec = nullptr;
     q->graph = nullptr;
     q->key.clear();
+    q->running = false;
+}
+
+// Only a graph that no launch runs any more is destroyed: the caller waits
+// first (settle), or leaves it to retire_graph.
+void drop_graph(sam_seq* q) {
+    if (q->exec) (void)hipGraphExecDestroy(q->exec);
+    if (q->graph) (void)hipGraphDestroy(q->graph);
+    forget_graph(q);
+}
+
+void drop_oldest(sam_seq* q) {
+    const sam_seq::Retired r = q->retired.front();
+    q->retired.erase(q->retired.begin());
+    (void)hipGraphExecDestroy(r.exec);
+    (void)hipGraphDestroy(r.graph);
+    (void)hipEventDestroy(r.end);
+}
+
+// Wait for the last run, whatever stream it is on (s is the caller's stream; the
+// run's own may be gone by now, so another one is waited for with the device).
+hipError_t settle(sam_seq* q, hipStream_t s) {
+    if (!q->running) return hipSuccess;
+    const hipError_t e = q->last == s ? hipStreamSynchronize(s) : hipDeviceSynchronize();
+    if (e == hipSuccess) q->running = false;
+    return e;
+}
+
+// Other pointers than the captured ones: the graph goes once its last launch
+// has ended.  A run on the same stream need not wait for that; at most
+// kRetired graphs are kept.
+constexpr size_t kRetired = 4;
+hipError_t retire_graph(sam_seq* q, hipStream_t s) {
+    while (!q->retired.empty()) {
+        hipError_t e = q->retired.size() < kRetired ? hipEventQuery(q->retired.front().end)
+                                                    : hipEventSynchronize(q->retired.front().end);
+        if (e == hipErrorNotReady) break;
+        if (e != hipSuccess) return e;
+        drop_oldest(q);
+    }
+    if (!q->running || q->last != s) {
+        const hipError_t e = settle(q, s);
+        if (e == hipSuccess) drop_graph(q);
+        return e;
+    }
+    hipEvent_t end = nullptr;
+    hipError_t e = hipEventCreateWithFlags(&end, hipEventDisableTiming);
+    if (e == hipSuccess && (e = hipEventRecord(end, s)) != hipSuccess) (void)hipEventDestroy(end);
+    if (e != hipSuccess) return e;
+    q->retired.push_back({q->graph, q->exec, end});
+    forget_graph(q);
+    return hipSuccess;
 }
 
 // Symbolic work for source k (replanning mode) into scratch set R: the
@@ -499,6 +559,7 @@ sam_status sam_sequence_destroy(sam_seq* q) {
         (void)hipDeviceSynchronize();
     }
     drop_graph(q);
+    while (!q->retired.empty()) drop_oldest(q);
     if (q->cap) (void)hipStreamDestroy(q->cap);
     for (hipStream_t x : q->side)
         if (x) (void)hipStreamDestroy(x);
@@ -549,6 +610,9 @@ sam_status sam_sequence_select(sam_seq* q, const int32_t* order, int32_t count, 
     if (!ok) return fail(ctx, SAM_ERR_ARG, "variant order must list 1..%d valid menu indices", samk::kMaxBuckets);
     sam_status st = need_device(ctx);
     if (st) return st;
+    // the buckets of a run still on its way, on this stream or another, must not
+    // change under it
+    HIP_TRY(ctx, settle(q, S(stream)));
     if ((st = plan_select(q->plan, q->prec, vars, S(stream)))) return st;
     if (q->replan && (st = set_bounds(q, S(stream)))) return st;
     drop_graph(q);  // the next run captures the new launches
@@ -573,7 +637,7 @@ sam_status sam_sequence_run(sam_seq* q, const double* const* Ak_vals, void* cons
     }
     key.push_back(res2);
     if (!q->exec || key != q->key) {
-        drop_graph(q);
+        HIP_TRY(ctx, retire_graph(q, S(stream)));
         HIP_TRY(ctx, hipStreamBeginCapture(q->cap, hipStreamCaptureModeThreadLocal));
         st = enqueue_run(q, Ak_vals, M_vals, res2, q->cap);
         hipGraph_t g = nullptr;
@@ -592,6 +656,8 @@ sam_status sam_sequence_run(sam_seq* q, const double* const* Ak_vals, void* cons
         q->key = key;
     }
     HIP_TRY(ctx, hipGraphLaunch(q->exec, S(stream)));
+    q->running = true;
+    q->last = S(stream);
     return SAM_OK;
 }
 

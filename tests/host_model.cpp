@@ -34,6 +34,10 @@ struct Exec {
     std::vector<Op> ops;
     int in_flight = 0;
 };
+struct Event {
+    Stream* on = nullptr;
+    int pending = 0;
+};
 std::set<Stream*> g_streams;
 Stream g_null;
 Graph* g_capture = nullptr;
@@ -94,11 +98,34 @@ hipError_t hipStreamDestroy(hipStream_t s) {
     delete (Stream*)s;
     return hipSuccess;
 }
-// events are recorded and waited for inside captures only, where the order of
-// the calls is an order of the graph
-hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
-hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+// inside a capture, events add nothing: the order of the calls is an order of
+// the graph
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+    *e = (hipEvent_t) new Event;
+    return hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t e) {
+    if (((Event*)e)->pending) wrong("event destroyed before it is reached");
+    else delete (Event*)e;
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    if (g_capture) return hipSuccess;
+    auto* x = (Event*)e;
+    x->on = of(s);
+    ++x->pending;
+    return enqueue(s, [x] { --x->pending; });
+}
+hipError_t hipEventQuery(hipEvent_t e) { return ((Event*)e)->pending ? hipErrorNotReady : hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t e) {
+    auto* x = (Event*)e;
+    while (x->pending) {
+        Op op = std::move(x->on->ops.front());
+        x->on->ops.pop_front();
+        op();
+    }
+    return hipSuccess;
+}
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) {
     g_capture = new Graph;
@@ -503,14 +530,17 @@ int main(int argc, char** argv) {
                 served(q.N, "columns of a run");
                 ++done;
             }
-    } else if (what == "outputs") {   // new outputs while the last run is still on its way
+    } else if (what == "outputs") {   // new outputs while the last runs are still on their way
         for (hipStream_t second : {s, other}) {
             Seq q(ctx, 6, 4, SAM_SPARSIFY_COLUMN, 2, 1, s);
             clear(q.A.n);
             q.run(0, s);
+            const bool waited = of(s)->ops.empty();
             q.run(1, second);
+            if (second == s && (waited || of(s)->ops.empty())) wrong("a run waited for another on its stream");
+            for (int k = 0; k < 9; ++k) q.run(k & 1, second);
             (void)hipDeviceSynchronize();
-            served(2 * q.N, "columns of two runs");
+            served(11 * q.N, "columns of the runs");
             ++done;
         }
     } else if (what == "select") {   // other classes while the last run is still on its way on another stream

@@ -35,3 +35,19 @@ def test_made_on_one_stream_used_on_another(model, made):
     """sam_plan_create and sam_sequence_create synchronise: their buckets are
     there for a build on any stream."""
     check(model, made)
+
+
+@pytest.mark.parametrize("changed", ["outputs", "select"])
+def test_sequence_changed_while_it_runs(model, changed):
+    """Other outputs, or other classes, while the last run is still on its way,
+    on the same stream or another: no graph is destroyed and no bucket is
+    rewritten under a run."""
+    check(model, changed)
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_sequence_orders(model, seed):
+    """Selections, refused ones among them, between runs on two streams with
+    other outputs: every column of every run is served once, by a class it
+    fits."""
+    check(model, "orders", str(seed))
