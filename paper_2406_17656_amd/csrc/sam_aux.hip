@@ -406,9 +406,9 @@ template <bool F32, bool PERM>
 __global__ void __launch_bounds__(256)
 k_spmv_rows(int n, const int* rowptr, const int* colind, const int* perm, const void* val, const double* x,
             double* y) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = t / kSpmvLanes;
-    const double s = row_product<F32, PERM, false>(i < n, i, rowptr, colind, perm, val, x, nullptr);
+    const int64_t t = flat_block() * blockDim.x + threadIdx.x;
+    const int64_t i = t / kSpmvLanes;
+    const double s = row_product<F32, PERM, false>(i < n, (int)i, rowptr, colind, perm, val, x, nullptr);
     if (i < n && t % kSpmvLanes == 0) y[i] = s;
 }
 
@@ -483,7 +483,7 @@ hipError_t spmv_rows(int n, const int* rowptr, const int* colind, const int* per
                      int val_f32, const double* x, double* y, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int64_t threads = (int64_t)n * kSpmvLanes;
-    const dim3 grid((unsigned)((threads + 255) / 256)), block(256);
+    const dim3 grid = flat_grid((threads + 255) / 256), block(256);
     if (val_f32 && perm) hipLaunchKernelGGL((k_spmv_rows<true, true>), grid, block, 0, s, n, rowptr, colind, perm, val, x, y);
     else if (val_f32) hipLaunchKernelGGL((k_spmv_rows<true, false>), grid, block, 0, s, n, rowptr, colind, perm, val, x, y);
     else if (perm) hipLaunchKernelGGL((k_spmv_rows<false, true>), grid, block, 0, s, n, rowptr, colind, perm, val, x, y);

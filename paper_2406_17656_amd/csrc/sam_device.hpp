@@ -193,6 +193,9 @@ __device__ inline int grp_excl_scan(int v) {
     return x - v;
 }
 
+// The number of this block in a launch over flat_grid (sam_kernels.hpp).
+__device__ inline int64_t flat_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 __device__ inline int wave_lane() { return (int)(threadIdx.x & 63); }
 
 // Wave-level barrier for LDS traffic that stays inside one wavefront.
@@ -224,15 +227,15 @@ __device__ inline double row_product(bool live, int i, const int* rowptr, const 
     const int g = threadIdx.x % kSpmvLanes;
     double s = 0.0;
     if (live) {
-        const int b = rowptr[i + 1];
-        for (int e = rowptr[i] + g; e < b; e += kSpmvLanes * kSpmvUnroll) {
+        const unsigned b = (unsigned)rowptr[i + 1];   // unsigned: steps past 2^31 - 1 entries stay in range
+        for (unsigned e = (unsigned)rowptr[i] + g; e < b; e += kSpmvLanes * kSpmvUnroll) {
             int c[kSpmvUnroll];
             double v[kSpmvUnroll], xv[kSpmvUnroll];
 #pragma unroll
             for (int u = 0; u < kSpmvUnroll; ++u) {
-                const int eu = e + u * kSpmvLanes < b ? e + u * kSpmvLanes : e;   // e < b: in the row
+                const unsigned eu = e + u * kSpmvLanes < b ? e + u * kSpmvLanes : e;   // e < b: in the row
                 c[u] = colind[eu];
-                const int ev = PERM ? perm[eu] : eu;
+                const unsigned ev = PERM ? (unsigned)perm[eu] : eu;
                 v[u] = F32 ? (double)static_cast<const float*>(val)[ev] : static_cast<const double*>(val)[ev];
             }
 #pragma unroll

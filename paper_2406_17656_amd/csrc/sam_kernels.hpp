@@ -9,6 +9,14 @@
 
 namespace samk {
 
+// A grid of at least `blocks` blocks of up to 256 threads (flat_block numbers
+// them): a dimension of a launch holds fewer than 2^32 threads, and several
+// lanes for each of 2^31 rows are more.  The blocks past the last have no work.
+inline dim3 flat_grid(int64_t blocks) {
+    const int64_t x = blocks < (1 << 22) ? blocks : 1 << 22;
+    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+}
+
 // ----------------------------------------------------------------- scans
 // Exclusive prefix sum of n int32 counts into int64 offsets (n+1 entries,
 // off[n] = total).  Optionally also writes the int32 copy (n+1), raises

@@ -33,6 +33,7 @@ namespace {
 constexpr int kRows = 256;          // rows of a chunk in flight
 constexpr int kParts = 4;           // threads per row
 constexpr int kThreads = kRows * kParts;
+static_assert(kParts == kSpmvLanes, "k_gm_apply_dots gives a row of its product the threads of a row");
 constexpr int kRowWaves = kRows / 64;
 constexpr int kFlat = 256;          // threads per block of the kernels without chunks
 constexpr int kTile = 8;            // basis vectors whose loads are in flight together
@@ -41,24 +42,25 @@ constexpr int kTile = 8;            // basis vectors whose loads are in flight t
 constexpr int kInlineChunks = 64;
 constexpr int kMaxChunks = 1024;
 
-// Rows [r0, r1) of this block's chunk.
-__device__ inline void chunk_range(int n, int& r0, int& r1) {
+// Rows [r0, r1) of this block's chunk (unsigned: a step past the last row stays
+// in range up to n = 2^31 - 1).
+__device__ inline void chunk_range(int n, unsigned& r0, unsigned& r1) {
     const int64_t c = gridDim.x, b = blockIdx.x;
-    r0 = (int)(n * b / c);
-    r1 = (int)(n * (b + 1) / c);
+    r0 = (unsigned)(n * b / c);
+    r1 = (unsigned)(n * (b + 1) / c);
 }
 
 // part[j * chunks + block] = sum over the chunk of v_j w, j in [0, count).
 // Thread part p takes the tiles p, p + 4, ... of kTile vectors.  sh:
 // kRowWaves * count doubles.
-__device__ inline void chunk_dots(int n, int r0, int r1, int count, const double* V, const double* w, double* part,
+__device__ inline void chunk_dots(int n, unsigned r0, unsigned r1, int count, const double* V, const double* w, double* part,
                                   double* sh) {
     const int row = threadIdx.x % kRows, wv = row >> 6;
     for (int j0 = threadIdx.x / kRows * kTile; j0 < count; j0 += kParts * kTile) {
         double acc[kTile];
 #pragma unroll
         for (int u = 0; u < kTile; ++u) acc[u] = 0.0;
-        for (int r = r0 + row; r < r1; r += kRows) {
+        for (unsigned r = r0 + row; r < r1; r += kRows) {
             const double x = w[r];
 #pragma unroll
             for (int u = 0; u < kTile; ++u)   // past the last vector: v_0 again, not stored
@@ -104,12 +106,12 @@ __device__ inline void load_coefficients(int count, int chunks, const double* sr
 // row, the four sums added in order.  visit(w) sees every new entry, in the
 // threads of part 0.  ps: kThreads doubles.
 template <typename F>
-__device__ inline void chunk_subtract(int n, int r0, int r1, int count, const double* V, const double* h, double* w,
+__device__ inline void chunk_subtract(int n, unsigned r0, unsigned r1, int count, const double* V, const double* h, double* w,
                                       double* ps, F visit) {
     const int row = threadIdx.x % kRows, p = threadIdx.x / kRows;
     const int ja = count * p / kParts, jb = count * (p + 1) / kParts;
-    for (int b = r0; b < r1; b += kRows) {   // the same trips for every thread
-        const int r = b + row;
+    for (unsigned b = r0; b < r1; b += kRows) {   // the same trips for every thread
+        const unsigned r = b + row;
         double x = 0.0;
         if (r < r1) {
             int j = ja;
@@ -152,14 +154,13 @@ __global__ void __launch_bounds__(kFlat)
 k_gm_precond(int n, const int* rowptr, const int* colind, const void* val, const double* d, const double* v,
              double* z, const double* state) {
     if (state[1] != 0.0) return;
+    const int64_t t = flat_block() * kFlat + threadIdx.x;
     if constexpr (MAP) {
-        const int t = blockIdx.x * kFlat + threadIdx.x;
-        const int i = t / kSpmvLanes;
-        const double s = row_product<F32, false, true>(i < n, i, rowptr, colind, nullptr, val, v, d);
+        const int64_t i = t / kSpmvLanes;
+        const double s = row_product<F32, false, true>(i < n, (int)i, rowptr, colind, nullptr, val, v, d);
         if (i < n && t % kSpmvLanes == 0) z[i] = s;
-    } else {
-        const int i = blockIdx.x * kFlat + threadIdx.x;
-        if (i < n) z[i] = d[i] * v[i];
+    } else if (t < n) {
+        z[t] = d[t] * v[t];
     }
 }
 
@@ -169,11 +170,11 @@ k_gm_apply_dots(int n, const int* rowptr, const int* colind, const double* val, 
                 const double* V, double* part, const double* state) {
     if (state[1] != 0.0) return;
     extern __shared__ double sh[];
-    int r0, r1;
+    unsigned r0, r1;
     chunk_range(n, r0, r1);
-    for (int t = threadIdx.x; t < (r1 - r0 + kRows - 1) / kRows * kThreads; t += kThreads) {   // whole blocks
-        const int i = r0 + t / kSpmvLanes;
-        const double s = row_product<false, false, false>(i < r1, i, rowptr, colind, nullptr, val, z, nullptr);
+    for (unsigned t = threadIdx.x; t < (r1 - r0 + kRows - 1) / kRows * kThreads; t += kThreads) {   // whole blocks
+        const unsigned i = r0 + t / kSpmvLanes;
+        const double s = row_product<false, false, false>(i < r1, (int)i, rowptr, colind, nullptr, val, z, nullptr);
         if (i < r1 && t % kSpmvLanes == 0) w[i] = s;
     }
     __syncthreads();
@@ -199,7 +200,7 @@ k_gm_update_dots(int n, int count, int chunks, const double* src, const double* 
     load_coefficients(count, chunks, src, h);
     if (blockIdx.x == 0)
         for (int j = threadIdx.x; j < count; j += kThreads) h1[j] = h[j];
-    int r0, r1;
+    unsigned r0, r1;
     chunk_range(n, r0, r1);
     chunk_subtract(n, r0, r1, count, V, h, w, ps, [](double) {});
     chunk_dots(n, r0, r1, count, V, w, part, sh);
@@ -216,7 +217,7 @@ k_gm_update_norm(int n, int count, int chunks, const double* src, const double* 
     load_coefficients(count, chunks, src, h);
     if (blockIdx.x == 0)
         for (int j = threadIdx.x; j < count; j += kThreads) Hcol[j] = h1[j] + h[j];
-    int r0, r1;
+    unsigned r0, r1;
     chunk_range(n, r0, r1);
     double s = 0.0;
     chunk_subtract(n, r0, r1, count, V, h, w, ps, [&](double y) { s += y * y; });
@@ -287,10 +288,10 @@ k_gm_next(int n, int k, int restart, int chunks, const double* nrm, const double
     __shared__ double hn_sh;
     const double hn = step_norm(nrm, chunks, state, &hn_sh);
     if (hn < 0.0) return;
-    int r0, r1;
+    unsigned r0, r1;
     chunk_range(n, r0, r1);
     if (hn != 0.0)
-        for (int r = r0 + (int)threadIdx.x; r < r1; r += kFlat) vnext[r] = w[r] / hn;
+        for (unsigned r = r0 + threadIdx.x; r < r1; r += kFlat) vnext[r] = w[r] / hn;
     if (blockIdx.x == 0) rotate_column(k, restart, hn, Hcol, cs, sn, tol, state, sh);
 }
 
@@ -308,12 +309,13 @@ k_gm_next_precond(int n, int k, int restart, int chunks, const double* nrm, cons
     __shared__ double hn_sh;
     const double hn = step_norm(nrm, chunks, state, &hn_sh);
     if (hn < 0.0) return;
-    if (blockIdx.x == 0) {
+    const int64_t block = flat_block();
+    if (block == 0) {
         rotate_column(k, restart, hn, Hcol, cs, sn, tol, state, sh);
         return;
     }
     if (hn == 0.0) return;
-    const int64_t t = (int64_t)(blockIdx.x - 1) * kFlat + threadIdx.x;
+    const int64_t t = (block - 1) * kFlat + threadIdx.x;
     if constexpr (MAP) {
         const int i = (int)(t / kSpmvLanes);
         const double s = row_product<F32, false, true, true>(i < n, i, rowptr, colind, nullptr, val, w, d, hn);
@@ -331,7 +333,7 @@ k_gm_next_precond(int n, int k, int restart, int chunks, const double* nrm, cons
 // x += sum_i y_i z_i, i ascending.
 __global__ void __launch_bounds__(kFlat)
 k_gm_solution(int n, int used, const double* y, const double* Z, double* x) {
-    const int r = blockIdx.x * kFlat + threadIdx.x;
+    const int64_t r = flat_block() * kFlat + threadIdx.x;
     if (r >= n) return;
     double s = x[r];
     int i = 0;
@@ -346,7 +348,7 @@ k_gm_solution(int n, int used, const double* y, const double* Z, double* x) {
     x[r] = s;
 }
 
-unsigned blocks_for(int64_t threads) { return (unsigned)((threads + kFlat - 1) / kFlat); }
+int64_t blocks_for(int64_t threads) { return (threads + kFlat - 1) / kFlat; }
 
 }  // namespace
 
@@ -394,12 +396,12 @@ hipError_t gmres_steps(const GmresArgs& a, int first, int count, hipStream_t s) 
     if (count <= 0) return hipSuccess;
     const int n = a.n, chunks = gmres_chunks(n);
     const dim3 flat(kFlat);
-    const unsigned rows = blocks_for(a.N_rowptr ? (int64_t)n * kSpmvLanes : n);
+    const int64_t rows = blocks_for(a.N_rowptr ? (int64_t)n * kSpmvLanes : n);
     for (int k = first; k < first + count; ++k) {
         double *v = a.V + (int64_t)k * n, *z = a.Z + (int64_t)k * n;
         if (k == first) {
             auto run = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3(rows), flat, 0, s, n, a.N_rowptr, a.N_colind, a.N_val, a.d, v, z,
+                hipLaunchKernelGGL(kernel, flat_grid(rows), flat, 0, s, n, a.N_rowptr, a.N_colind, a.N_val, a.d, v, z,
                                    a.state);
             };
             if (!a.N_rowptr) run(k_gm_precond<false, false>);
@@ -407,7 +409,7 @@ hipError_t gmres_steps(const GmresArgs& a, int first, int count, hipStream_t s) 
             else run(k_gm_precond<true, false>);
         } else {
             auto run = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3(rows + 1), flat, 3 * sizeof(double) * (size_t)k, s, n, k - 1,
+                hipLaunchKernelGGL(kernel, flat_grid(rows + 1), flat, 3 * sizeof(double) * (size_t)k, s, n, k - 1,
                                    a.restart, chunks, a.nrm, a.w, v, a.H + (int64_t)(k - 1) * (a.restart + 1), a.cs,
                                    a.sn, a.tol, a.state, a.N_rowptr, a.N_colind, a.N_val, a.d, z);
             };
@@ -426,7 +428,7 @@ hipError_t gmres_steps(const GmresArgs& a, int first, int count, hipStream_t s) 
 
 hipError_t gmres_solution(int n, int used, const double* y, const double* Z, double* x, hipStream_t s) {
     if (used <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gm_solution, dim3(blocks_for(n)), dim3(kFlat), 0, s, n, used, y, Z, x);
+    hipLaunchKernelGGL(k_gm_solution, flat_grid(blocks_for(n)), dim3(kFlat), 0, s, n, used, y, Z, x);
     return hipGetLastError();
 }
 
