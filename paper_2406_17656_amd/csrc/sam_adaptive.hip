@@ -59,7 +59,7 @@ k_topk(int n, const int* S_cp, const int* S_ri, const double* w, const double* g
     __shared__ double grad_sh[kGroups][kTopkStage];
     __shared__ int row_sh[kGroups][kTopkStage];   // INT_MIN: not a candidate
     const int grp = threadIdx.x / kTopkLanes, g = threadIdx.x % kTopkLanes;
-    const int64_t j = (int64_t)blockIdx.x * kGroups + grp;
+    const int64_t j = flat_block() * kGroups + grp;
     if (j >= n) return;   // whole groups; no block barrier below
     const int a = S_cp[j], b = S_cp[j + 1], len = b - a;
     const bool staged = len <= kTopkStage;
@@ -101,7 +101,7 @@ k_topk(int n, const int* S_cp, const int* S_ri, const double* w, const double* g
 
 dim3 topk_grid(int n) {
     constexpr int kGroups = kTopkThreads / kTopkLanes;
-    return dim3((unsigned)((n - 1) / kGroups + 1));
+    return flat_grid((n - 1) / kGroups + 1);
 }
 
 }  // namespace

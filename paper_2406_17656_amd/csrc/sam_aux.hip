@@ -330,7 +330,7 @@ constexpr int kTfillLanes = 8;
 
 __global__ void k_tfill(int n, const int* cp, const int* ri, const int* rowptr, int* cursor, int* colind,
                         int* perm) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = flat_block() * blockDim.x + threadIdx.x;
     const int64_t j = t / kTfillLanes;
     if (j >= n) return;
     const int end = cp[j + 1];
@@ -360,7 +360,7 @@ k_tsort(int n, const int* rowptr, int* colind, int* perm) {
     constexpr int kHeld = kTsortStage / kTsortLanes;
     __shared__ int col_sh[kGroups][kTsortStage];
     const int grp = threadIdx.x / kTsortLanes, g = threadIdx.x % kTsortLanes;
-    const int64_t i = (int64_t)blockIdx.x * kGroups + grp;
+    const int64_t i = flat_block() * kGroups + grp;
     if (i >= n) return;   // whole groups; no block barrier below
     const int a = rowptr[i], b = rowptr[i + 1], len = b - a;
     if (len > kTsortStage) {
@@ -466,7 +466,7 @@ hipError_t transpose_fill(int n, const int* cp, const int* ri, const int* rowptr
                           int* colind, int* perm, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int64_t threads = (int64_t)n * kTfillLanes;
-    hipLaunchKernelGGL(k_tfill, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, n, cp, ri, rowptr, cursor,
+    hipLaunchKernelGGL(k_tfill, flat_grid((threads + 255) / 256), dim3(256), 0, s, n, cp, ri, rowptr, cursor,
                        colind, perm);
     return hipGetLastError();
 }
@@ -474,7 +474,7 @@ hipError_t transpose_fill(int n, const int* cp, const int* ri, const int* rowptr
 hipError_t transpose_sort_rows(int n, const int* rowptr, int* colind, int* perm, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     constexpr int kRows = kTsortThreads / kTsortLanes;
-    hipLaunchKernelGGL(k_tsort, dim3((unsigned)((n - 1) / kRows + 1)), dim3(kTsortThreads), 0, s, n, rowptr, colind,
+    hipLaunchKernelGGL(k_tsort, flat_grid((n - 1) / kRows + 1), dim3(kTsortThreads), 0, s, n, rowptr, colind,
                        perm);
     return hipGetLastError();
 }

@@ -90,3 +90,28 @@ def test_product_and_gmres_steps(ctx, n, steps):
     ctx.sync_status()
     del V, Z, x, ws, rp
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n", [(1 << 28) + 33, (1 << 29) + 33, (1 << 31) - 1])
+def test_row_view_and_topk(ctx, n):
+    """One entry in each of a few columns, rows in descending order: the row
+    view turns them round, and the selection keeps the candidates that k lets
+    in."""
+    cols = rows_of(n)
+    k = len(cols)
+    cp = pointers(n, cols)
+    ri = torch.as_tensor(cols[::-1].copy()).cuda().to(torch.int32)
+    rp, ci, pm = ctx.apply_prepare(n, cp, ri)
+    assert torch.equal(rp, cp)
+    assert np.array_equal(ci.cpu().numpy(), cols[::-1])
+    assert np.array_equal(pm.cpu().numpy(), np.arange(k)[::-1])
+    del rp, ci, pm
+    w = torch.ones(k, dtype=torch.float64, device="cuda")
+    w[1::2] = 0.5
+    for top, kept in ((1, np.arange(k)), (0, np.arange(0, k, 2))):
+        got_cp, got_ri = ctx.pattern_topk(cp, ri, w, torch.arange(float(k), dtype=torch.float64, device="cuda"), top)
+        assert torch.equal(got_cp, pointers(n, cols[kept]))
+        assert np.array_equal(got_ri.cpu().numpy(), cols[::-1][kept])
+    ctx.sync_status()
+    del cp, got_cp
+    torch.cuda.empty_cache()
