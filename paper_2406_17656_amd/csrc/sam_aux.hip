@@ -38,34 +38,279 @@ __device__ inline double mval(const void* M, int e, int f32) {
 // 495 -> 388.
 constexpr int kResWPL = 16;               // bitmap words per lane
 constexpr int kResAcc = 64;               // accumulators per column and pass (bitmap form)
+constexpr int kResWords = kResWPL * 64;   // bitmap words of a block
+// Entries beyond which a column takes a whole wave: on groups of lanes the work
+// is a column's entries times its ranges of 64 rows.  Groups / wave, us:
+// 512^2 nine-point level 3 (441 entries) 3390 / 3546, 40^3 27-point level 1
+// (729) 817 / 587, with the level-2 pattern (3375) 8370 / 1499; one dense
+// column of A_0 in 20000 short ones 87000 / 300.
+constexpr int kResWide = 512;
 
 struct alignas(16) ResList {  // one column of M's pattern: its run in A_k and its value
     int start, len;
     double m;
 };
 
+struct ResArgs {
+    int n;
+    const int *Ak_cp, *Ak_ri;
+    const double* Ak_v;
+    const int *A0_cp, *A0_ri;
+    const double* A0_v;
+    const int *M_cp, *M_ri;
+    const void* M_v;
+    int f32;
+    double* col_out;
+    unsigned long long* status;
+};
+
+__device__ inline int wave_min(int v) {
+    v = grp_min<16>(v);
+#pragma unroll
+    for (int d = 16; d < 64; d <<= 1) v = min(v, __shfl_xor(v, d));
+    return v;
+}
+__device__ inline int wave_sum(int v) {
+    v = grp_sum<16>(v);
+#pragma unroll
+    for (int d = 16; d < 64; d <<= 1) v += __shfl_xor(v, d);
+    return v;
+}
+__device__ inline double readlane(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// The first of the ascending rows ri[a, b) that is at least `row` (b: none),
+// by the wave: 64 probes a round.
+__device__ inline int first_row(const int* ri, int a, int b, int row) {
+    const int lane = wave_lane();
+    while (b - a > 64) {
+        const int step = (b - a) / 64 + 1;
+        const int p = a + min(step * (lane + 1), b - a) - 1;   // the last of lane's share
+        a += step * __popcll(__ballot(p < b - 1 && ri[p] < row));
+        b = a + min(step, b - a);
+    }
+    return a + __popcll(__ballot(lane < b - a && ri[a + lane] < row));
+}
+
+// Column j by the whole wave, for columns of many entries: a window of 32768
+// rows as a bitmap, whose words are taken in ranges of at most kAcc rows.  The
+// runs of A_k and A_0 ascend, so a range reads of a long run what lies in it,
+// and of 64 runs of M's column those that reach it: the work grows with the
+// entries, not with their product with the ranges.  Bound by the latency of the
+// runs' loads (kAhead of them in flight) and of the LDS reads that place a row.
+// bm, pre: kResWords; acc: kAcc.
+template <int kAcc>
+__device__ double wave_column(const ResArgs& a, int j, unsigned* bm, unsigned short* pre, double* acc) {
+    constexpr int kShort = 64;   // entries of a run taken at once
+    constexpr int kAhead = 8;    // short runs whose loads are in flight together
+    const int lane = wave_lane();
+    const int ma = a.M_cp[j], mb = a.M_cp[j + 1], aa = a.A0_cp[j], ab = a.A0_cp[j + 1];
+    int start = 0, len = 0;      // lane's run of the 64 at hand
+    auto runs = [&](unsigned t) {
+        start = len = 0;
+        if (t >= (unsigned)mb) return;
+        const int l = a.M_ri[t];
+        if (l < 0 || l >= a.n) {
+            report(a.status, j, kStIndex);
+            return;
+        }
+        start = a.Ak_cp[l];
+        len = a.Ak_cp[l + 1] - start;
+    };
+    int lo = lane == 0 && ab > aa ? a.A0_ri[aa] : INT_MAX;
+    for (unsigned t = ma; t < (unsigned)mb; t += 64) {
+        runs(t + lane);
+        if (len > 0) lo = min(lo, a.Ak_ri[start]);
+    }
+    double colsum = 0.0;
+    for (int base = wave_min(lo); base != INT_MAX;) {
+#pragma unroll
+        for (int w = 0; w < kResWPL; ++w) bm[w * 64 + lane] = 0u;
+        wave_sync();
+        int next = INT_MAX;   // the first row past the window
+        auto mark = [&](int r) {
+            const int d = r - base;
+            if (d < kResWords * 32) atomicOr(&bm[d >> 5], 1u << (d & 31));
+            else next = min(next, r);
+            return d < kResWords * 32;
+        };
+        auto mark_run = [&](const int* ri, int e, int end) {   // by the wave
+            for (e = first_row(ri, e, end, base);; e += 64) {
+                bool in = lane < end - e;
+                if (in) in = mark(ri[e + lane]);
+                if (__ballot(!in)) break;
+            }
+        };
+        for (unsigned t = ma; t < (unsigned)mb; t += 64) {
+            runs(t + lane);
+            if (len <= kShort)
+                for (int e = start; e < start + len; ++e) {
+                    const int r = a.Ak_ri[e];
+                    if (r >= base && !mark(r)) break;
+                }
+            for (unsigned long long left = __ballot(len > kShort); left; left &= left - 1) {
+                const int b = __ffsll(left) - 1, s = __builtin_amdgcn_readlane(start, b);
+                mark_run(a.Ak_ri, s, s + __builtin_amdgcn_readlane(len, b));
+            }
+        }
+        mark_run(a.A0_ri, aa, ab);
+        wave_sync();
+        // pre[w]: the window's rows before word w
+        int mine = 0;
+#pragma unroll
+        for (int w = 0; w < kResWPL; ++w) mine += __popc(bm[lane * kResWPL + w]);
+        int run = mine;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(run, d);
+            if (lane >= d) run += y;
+        }
+        const int cnt = __builtin_amdgcn_readlane(run, 63);
+        run -= mine;
+#pragma unroll
+        for (int w = 0; w < kResWPL; ++w) {
+            pre[lane * kResWPL + w] = (unsigned short)run;
+            run += __popc(bm[lane * kResWPL + w]);
+        }
+        wave_sync();
+        for (int w0 = 0, r0 = 0; r0 < cnt;) {
+            // the words from w0 on whose rows fit the accumulators
+            int w1 = kResWords, r1 = cnt;
+            if (cnt - r0 > kAcc) {
+                int more = 0;
+#pragma unroll
+                for (int w = 0; w < kResWPL; ++w) {
+                    const int x = lane * kResWPL + w;
+                    more += x > w0 && pre[x] - r0 <= kAcc;
+                }
+                w1 = w0 + wave_sum(more);
+                r1 = pre[w1];
+            }
+            const int d0 = w0 * 32, d1 = w1 * 32;
+#pragma unroll
+            for (int i = 0; i < kAcc / 64; ++i) acc[i * 64 + lane] = 0.0;
+            wave_sync();
+            auto add = [&](int r, double v) {
+                const int d = r - base;
+                if (d < d0 || d >= d1) return;
+                const int w = d >> 5, rank = pre[w] + __popc(bm[w] & ((1u << (d & 31)) - 1u)) - r0;
+                __hip_atomic_fetch_add(&acc[rank], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            };
+            auto add_run = [&](const int* ri, const double* val, int e, int end, double m) {
+                for (e = first_row(ri, e, end, base + d0);; e += 64) {
+                    bool in = lane < end - e;
+                    if (in) {
+                        const int r = ri[e + lane];
+                        add(r, val[e + lane] * m);
+                        in = r - base < d1;
+                    }
+                    if (__ballot(!in)) break;
+                }
+            };
+            for (unsigned t = ma; t < (unsigned)mb; t += 64) {
+                runs(t + lane);
+                double m = 0.0;
+                bool touches = false;
+                if (len > 0) {
+                    m = mval(a.M_v, (int)(t + lane), a.f32);
+                    touches = a.Ak_ri[start] - base < d1 && a.Ak_ri[start + len - 1] - base >= d0;
+                }
+                for (unsigned long long left = __ballot(touches); left;) {   // in M's order
+                    int s[kAhead], l[kAhead], row[kAhead];
+                    double v[kAhead], c[kAhead];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        s[u] = l[u] = 0;
+                        c[u] = 0.0;
+                        if (!left) continue;
+                        const int b = __ffsll(left) - 1;
+                        left &= left - 1;
+                        s[u] = __builtin_amdgcn_readlane(start, b);
+                        l[u] = __builtin_amdgcn_readlane(len, b);
+                        c[u] = readlane(m, b);
+                    }
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const bool in = l[u] <= kShort && lane < l[u];
+                        row[u] = in ? a.Ak_ri[s[u] + lane] : -1;
+                        v[u] = in ? a.Ak_v[s[u] + lane] : 0.0;
+                    }
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        if (l[u] > kShort) add_run(a.Ak_ri, a.Ak_v, s[u], s[u] + l[u], c[u]);
+                        else if (row[u] >= 0) add(row[u], v[u] * c[u]);
+                    }
+                }
+            }
+            add_run(a.A0_ri, a.A0_v, aa, ab, -1.0);
+            wave_sync();
+            double s = 0.0;
+#pragma unroll
+            for (int i = 0; i < kAcc / 64; ++i) {
+                const double x = acc[i * 64 + lane];
+                s += x * x;
+            }
+            colsum += group_sum<64>(s);
+            wave_sync();
+            w0 = w1;
+            r0 = r1;
+        }
+        base = wave_min(next);
+    }
+    return colsum;
+}
+
+// Every column by a wave.
+constexpr int kWideAcc = 1024;
+__global__ void __launch_bounds__(64)
+k_residual_wide(ResArgs a) {
+    __shared__ unsigned bm[kResWords];
+    __shared__ unsigned short pre[kResWords];
+    __shared__ double acc[kWideAcc];
+    for (int64_t j = blockIdx.x; j < a.n; j += gridDim.x) {
+        const double s = wave_column<kWideAcc>(a, (int)j, bm, pre, acc);
+        if (wave_lane() == 0) a.col_out[j] = s;
+    }
+}
+
 // kResLanes lanes per column, kResBatch columns of M per problem held in
 // registers: 8 and 16, or 16 and 32.
 template <int kResLanes, int kResBatch, bool TABLE>
-__global__ void __launch_bounds__(64)
-k_residual_columns(int n, const int* Ak_cp, const int* Ak_ri, const double* Ak_v, const int* A0_cp,
-                   const int* A0_ri, const double* A0_v, const int* M_cp, const int* M_ri,
-                   const void* M_v, int f32, double* col_out, unsigned long long* status) {
+__global__ void __launch_bounds__(64, kResLanes == 8 ? 3 : 2)
+k_residual_columns(ResArgs a) {
+    const int n = a.n, f32 = a.f32;
+    const int *Ak_cp = a.Ak_cp, *Ak_ri = a.Ak_ri, *A0_cp = a.A0_cp, *A0_ri = a.A0_ri, *M_cp = a.M_cp, *M_ri = a.M_ri;
+    const double *Ak_v = a.Ak_v, *A0_v = a.A0_v;
+    const void* M_v = a.M_v;
+    double* col_out = a.col_out;
+    unsigned long long* status = a.status;
     constexpr int kResCols = 64 / kResLanes;              // columns per wave
     constexpr int kResRows = kResWPL * kResLanes * 32;    // rows per window
     // word w of a lane sits at w * 64 + lane: the passes over a lane's own
     // words touch 64 consecutive words
-    __shared__ unsigned bm[kResWPL * 64];
-    __shared__ unsigned short pre[kResWPL * 64];
+    __shared__ unsigned bm[kResWords];
+    __shared__ unsigned short pre[kResWords];
     // table slots per column: twice the rows of a level-2 column and more
     // (25 of a five-point, 63 of a seven-point stencil)
     constexpr int kHashBits = kResLanes == 8 ? 6 : 7;
     constexpr int kHash = 1 << kHashBits;
     constexpr int kResAccStride = (TABLE ? kHash : kResAcc) + 4;   // 8 banks apart: eight columns cover the 64 banks
     static_assert(kHash >= kResAcc, "the bitmap form uses the same accumulators");
-    __shared__ double accs[kResCols * kResAccStride];
-    __shared__ int keys[TABLE ? kResCols * kHash : 1];
-    __shared__ ResList lists[kResCols][kResBatch];
+    struct Groups {
+        double accs[kResCols * kResAccStride];
+        int keys[TABLE ? kResCols * kHash : 4];
+        ResList lists[kResCols][kResBatch];
+    };
+    constexpr int kWaveAcc = (int)(sizeof(Groups) / sizeof(double)) / 64 * 64;
+    __shared__ union {
+        Groups groups;
+        double wave[kWaveAcc];   // a column that takes the whole wave
+    } sh;
+    auto& lists = sh.groups.lists;
+    auto& keys = sh.groups.keys;
+    double* accs = sh.groups.accs;
     const int lane = wave_lane();
     const int g = lane % kResLanes, q = lane / kResLanes;
     double* acc = accs + q * kResAccStride;
@@ -114,6 +359,7 @@ k_residual_columns(int n, const int* Ak_cp, const int* Ak_ri, const double* Ak_v
         int rows[kResBatch + 1];              // -1: no entry
         double vals[kResBatch + 1];           // entry times coefficient
         int lo = INT_MAX;
+        unsigned long long wides = 0;         // columns that the whole wave has summed: their first lanes
         if (fast) {
 #pragma unroll
             for (int u = 0; u < kResBatch; ++u) {
@@ -199,16 +445,27 @@ k_residual_columns(int n, const int* Ak_cp, const int* Ak_ri, const double* Ak_v
                 }
             }
         } else {   // the columns are ascending, so the smallest row heads one of them
-            for (int t = ma + g; t < mb; t += kResLanes) {
+            int entries = g == 0 ? min(ab - aa, kResWide + 1) : 0;   // counted no further than needed
+            for (int t = ma + g; t < mb && entries <= kResWide; t += kResLanes) {
                 const int l = M_ri[t];
                 if (l < 0 || l >= n) {
                     report(status, j, kStIndex);
                     continue;
                 }
-                const int qa = Ak_cp[l];
-                if (Ak_cp[l + 1] > qa) lo = min(lo, Ak_ri[qa]);
+                const int qa = Ak_cp[l], len = Ak_cp[l + 1] - qa;
+                entries += min(len, kResWide + 1);
+                if (len > 0) lo = min(lo, Ak_ri[qa]);
             }
             if (ab > aa) lo = min(lo, A0_ri[aa]);
+            const bool wide = grp_sum<kResLanes>(entries) > kResWide;
+            wides = __ballot(wide && g == 0);
+            for (unsigned long long left = wides; left; left &= left - 1) {
+                const int qw = (__ffsll(left) - 1) / kResLanes;
+                const int jw = (int)((int64_t)grp * kResCols + qw);
+                const double s = wave_column<kWaveAcc>(a, jw, bm, pre, sh.wave);
+                if (lane == 0) col_out[jw] = s;
+            }
+            if (wide) lo = INT_MAX;   // no window follows
         }
         int base = grp_min<kResLanes>(lo);
         double colsum = 0.0;
@@ -275,7 +532,7 @@ k_residual_columns(int n, const int* Ak_cp, const int* Ak_ri, const double* Ak_v
             }
             base = grp_min<kResLanes>(next);
         }
-        if (valid && g == 0) col_out[j] = colsum;
+        if (valid && g == 0 && !(wides >> lane & 1)) col_out[j] = colsum;
     }
 }
 
@@ -297,14 +554,16 @@ hipError_t residual_columns(int n, int64_t nnzA, int64_t nnzM, const int* Ak_cp,
     // 91 / 115, level 2 113 / 133, 64^3 level 1 238 / 155; sixteen lanes 512^2
     // level 3 495 / 388, 64^3 level 2 1070 / 388, 1024^2 nine-point level 2
     // 1955 / 1540, level 1 1418 / 1252.
+    const ResArgs a{n, Ak_cp, Ak_ri, Ak_v, A0_cp, A0_ri, A0_v, M_cp, M_ri, M_v, m_is_f32, col_out, status};
+    if ((double)nnzA * (double)nnzM > (double)kResWide * n * n) {   // entries of a column's problem, in the mean
+        hipLaunchKernelGGL(k_residual_wide, dim3((unsigned)std::min(n, 256 * 32)), dim3(64), 0, s, a);
+        return hipGetLastError();
+    }
     const bool narrow = nnzA <= (int64_t)7 * n && nnzM <= (int64_t)14 * n;
     const int cols = narrow ? 8 : 4;
     // up to 12 one-wave blocks per CU are resident
     const int grid = launch_grid(((int64_t)n + cols - 1) / cols, 256 * 12);
-    auto run = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, n, Ak_cp, Ak_ri, Ak_v, A0_cp, A0_ri, A0_v, M_cp, M_ri,
-                           M_v, m_is_f32, col_out, status);
-    };
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, s, a); };
     if (!narrow) run(k_residual_columns<16, 32, true>);
     else if (nnzA > (int64_t)6 * n) run(k_residual_columns<8, 16, true>);
     else run(k_residual_columns<8, 16, false>);
