@@ -173,10 +173,11 @@ def solve_with_map(ctx: Context, Ak: DeviceCSC, A0: DeviceCSC, M_colptr, M_rowin
     dinv = 1.0 / jacobi_diag(A0)
     N = None if M_val is None else SparseOp(ctx, Ak.n, M_colptr, M_rowind, M_val, prec)
     m = min(restart, maxiter)
-    # the library's steps take vectors of the context's device in FP64, up to
-    # its longest cycle and a bounded basis; anything else runs on callables
-    if (b.is_cuda and b.device.index == ctx.device and b.dtype == torch.float64 and b.dim() == 1
-            and b.numel() == Ak.n and b.is_contiguous() and not b.requires_grad
+    # the library's steps take vectors of the context's device and of A_k's
+    # order in FP64, up to their longest cycle and a bounded basis; anything else
+    # runs on callables
+    if (all(v.is_cuda and v.device.index == ctx.device and v.dtype == torch.float64 and v.dim() == 1
+            and v.numel() == Ak.n >= 1 and v.is_contiguous() and not v.requires_grad for v in (b, dinv))
             and 1 <= m <= C.SAM_GMRES_MAX_RESTART and (2 * m + 1) * Ak.n * 8 <= BASIS_BYTES):
         return _gmres_device(A, N, dinv, b, tol, restart, maxiter)
     if N is None:

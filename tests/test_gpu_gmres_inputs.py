@@ -1,0 +1,55 @@
+"""solve_with_map on what the library's steps do not take: a target of another
+order or device."""
+import numpy as np
+import pytest
+import torch
+
+import pde_inputs as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2406_17656_amd import Context
+    c = Context(0)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
+def system(m, seed=0):
+    from paper_2406_17656_amd import DeviceCSC
+    A0h, Ash = P.config2(m=m, nmat=2)
+    b = torch.as_tensor(np.random.default_rng(seed).standard_normal(A0h.n)).cuda()
+    return DeviceCSC.from_host(A0h), DeviceCSC.from_host(Ash[0]), b
+
+
+def generic(ctx, Ak, dinv, b, *args):
+    from paper_2406_17656_amd.krylov import SparseOp, gmres
+    return gmres(SparseOp(ctx, Ak.n, Ak.colptr, Ak.rowind, Ak.val), lambda v: dinv * v, b, *args)
+
+
+def test_target_of_another_order(ctx):
+    """Refused, but for the order 1, whose diagonal is a number."""
+    from paper_2406_17656_amd import DeviceCSC
+    from paper_2406_17656_amd.krylov import solve_with_map
+    _, Ak, b = system(12)
+    for m in (11, 13):
+        with pytest.raises(RuntimeError):
+            solve_with_map(ctx, Ak, system(m)[0], None, None, None, b)
+    one = DeviceCSC(1, torch.tensor([0, 1], dtype=torch.int32, device="cuda"),
+                    torch.zeros(1, dtype=torch.int32, device="cuda"),
+                    torch.full((1,), 4.0, dtype=torch.float64, device="cuda"))
+    x, its, hist = solve_with_map(ctx, Ak, one, None, None, None, b, "f64", 1e-8, 20, 200)
+    xr, itsr, histr = generic(ctx, Ak, torch.full((1,), 0.25, dtype=torch.float64, device="cuda"), b, 1e-8, 20, 200)
+    assert its == itsr and hist == histr and torch.equal(x, xr)
+
+
+def test_target_on_the_host(ctx):
+    from paper_2406_17656_amd import DeviceCSC
+    from paper_2406_17656_amd.krylov import solve_with_map
+    A0, Ak, b = system(12)
+    host = DeviceCSC(A0.n, A0.colptr.cpu(), A0.rowind.cpu(), A0.val.cpu())
+    with pytest.raises(RuntimeError):
+        solve_with_map(ctx, Ak, host, None, None, None, b)
