@@ -109,13 +109,18 @@ def gmres(apply_A, apply_M, b, tol=1e-8, restart=50, maxiter=2000):
 BASIS_BYTES = 4 << 30
 
 
+def _cycle(restart, maxiter) -> int:
+    """Steps of a cycle (maxiter need not be a whole number)."""
+    return int(restart if restart <= maxiter else math.ceil(maxiter))
+
+
 def _gmres_device(A: SparseOp, N: SparseOp | None, dinv, b, tol, restart, maxiter):
     """``gmres`` with the Arnoldi steps in the library: the residual test runs
     on the device, so the host looks after 1, 2, 4, ... 16 steps instead of
     after every dot product (steps enqueued past the last one needed return
     at once)."""
     ctx, n, dev = A.ctx, b.numel(), b.device
-    m = min(restart, maxiter)
+    m, tol = _cycle(restart, maxiter), float(tol)
     x = torch.zeros_like(b)
     bnorm = float(torch.linalg.vector_norm(b))
     hist = []
@@ -135,7 +140,7 @@ def _gmres_device(A: SparseOp, N: SparseOp | None, dinv, b, tol, restart, maxite
         if beta <= tol * bnorm:
             break
         torch.div(r, beta, out=V[0])
-        left = min(m, maxiter - its)
+        left = _cycle(m, maxiter - its)
         k = 0
         while True:
             count = min(batch, left - k)
@@ -172,13 +177,13 @@ def solve_with_map(ctx: Context, Ak: DeviceCSC, A0: DeviceCSC, M_colptr, M_rowin
     A = SparseOp(ctx, Ak.n, Ak.colptr, Ak.rowind, Ak.val, "f64")
     dinv = 1.0 / jacobi_diag(A0)
     N = None if M_val is None else SparseOp(ctx, Ak.n, M_colptr, M_rowind, M_val, prec)
-    m = min(restart, maxiter)
     # the library's steps take vectors of the context's device and of A_k's
     # order in FP64, up to their longest cycle and a bounded basis; anything else
     # runs on callables
     if (all(v.is_cuda and v.device.index == ctx.device and v.dtype == torch.float64 and v.dim() == 1
             and v.numel() == Ak.n >= 1 and v.is_contiguous() and not v.requires_grad for v in (b, dinv))
-            and 1 <= m <= C.SAM_GMRES_MAX_RESTART and (2 * m + 1) * Ak.n * 8 <= BASIS_BYTES):
+            and min(restart, maxiter) >= 1 and _cycle(restart, maxiter) <= C.SAM_GMRES_MAX_RESTART
+            and (2 * _cycle(restart, maxiter) + 1) * Ak.n * 8 <= BASIS_BYTES):
         return _gmres_device(A, N, dinv, b, tol, restart, maxiter)
     if N is None:
         apply_M = lambda v: dinv * v                       # noqa: E731

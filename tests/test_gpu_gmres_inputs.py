@@ -1,5 +1,8 @@
 """solve_with_map on what the library's steps do not take: a target of another
-order or device."""
+order or device; and numbers of steps and tolerances that are no plain Python
+numbers."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -53,3 +56,22 @@ def test_target_on_the_host(ctx):
     host = DeviceCSC(A0.n, A0.colptr.cpu(), A0.rowind.cpu(), A0.val.cpu())
     with pytest.raises(RuntimeError):
         solve_with_map(ctx, Ak, host, None, None, None, b)
+
+
+@pytest.mark.parametrize("restart,maxiter,tol", [
+    (np.int64(9), np.int64(30), np.float32(1e-7)),
+    (9, 30.0, torch.tensor(1e-7, dtype=torch.float64)),   # cut in the fourth cycle
+    (9, 1e4, 1e-7),
+    (9, 25.5, 1e-7),                                       # 26 steps
+    (40, 25.5, 1e-7),
+    (9, math.inf, 1e-7),
+])
+def test_numbers(ctx, restart, maxiter, tol):
+    from paper_2406_17656_amd.krylov import jacobi_diag, solve_with_map
+    A0, Ak, b = system(16)
+    x, its, hist = solve_with_map(ctx, Ak, A0, None, None, None, b, "f64", tol, restart, maxiter)
+    xr, itsr, histr = generic(ctx, Ak, 1.0 / jacobi_diag(A0), b, float(tol), int(restart), maxiter)
+    # the same steps but for rounding at the tolerance
+    assert abs(its - itsr) <= (1 if itsr < maxiter else 0)
+    k = min(len(hist), len(histr)) - 2
+    np.testing.assert_allclose(hist[:k], histr[:k], rtol=1e-6)
