@@ -178,13 +178,16 @@ def solve_with_map(ctx: Context, Ak: DeviceCSC, A0: DeviceCSC, M_colptr, M_rowin
     dinv = 1.0 / jacobi_diag(A0)
     N = None if M_val is None else SparseOp(ctx, Ak.n, M_colptr, M_rowind, M_val, prec)
     # the library's steps take vectors of the context's device and of A_k's
-    # order in FP64, up to their longest cycle and a bounded basis; anything else
-    # runs on callables
+    # order in FP64, up to their longest cycle and a bounded basis, if the device
+    # has room for it; anything else runs on callables
     if (all(v.is_cuda and v.device.index == ctx.device and v.dtype == torch.float64 and v.dim() == 1
             and v.numel() == Ak.n >= 1 and v.is_contiguous() and not v.requires_grad for v in (b, dinv))
             and min(restart, maxiter) >= 1 and _cycle(restart, maxiter) <= C.SAM_GMRES_MAX_RESTART
             and (2 * _cycle(restart, maxiter) + 1) * Ak.n * 8 <= BASIS_BYTES):
-        return _gmres_device(A, N, dinv, b, tol, restart, maxiter)
+        try:
+            return _gmres_device(A, N, dinv, b, tol, restart, maxiter)
+        except torch.OutOfMemoryError:
+            pass   # the callables' driver holds a vector per step it takes
     if N is None:
         apply_M = lambda v: dinv * v                       # noqa: E731
     else:

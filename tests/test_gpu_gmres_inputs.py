@@ -1,6 +1,6 @@
 """solve_with_map on what the library's steps do not take: a target of another
-order or device; and numbers of steps and tolerances that are no plain Python
-numbers."""
+order or device, a basis that the device has no room for; and numbers of steps
+and tolerances that are no plain Python numbers."""
 import math
 
 import numpy as np
@@ -75,3 +75,24 @@ def test_numbers(ctx, restart, maxiter, tol):
     assert abs(its - itsr) <= (1 if itsr < maxiter else 0)
     k = min(len(hist), len(histr)) - 2
     np.testing.assert_allclose(hist[:k], histr[:k], rtol=1e-6)
+
+
+def test_basis_beyond_the_device(ctx):
+    """Room for the few steps that are taken, not for a whole cycle's basis."""
+    from paper_2406_17656_amd.krylov import BASIS_BYTES, solve_with_map
+    A0, Ak, b = system(400)
+    restart = 512
+    basis = (2 * restart + 1) * Ak.n * 8
+    assert 1 << 30 < basis <= BASIS_BYTES
+    want, its, _ = solve_with_map(ctx, Ak, A0, None, None, None, b, "f64", 0.3, restart)
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved(0) + (768 << 20)) / total)
+    try:
+        x, again, _ = solve_with_map(ctx, Ak, A0, None, None, None, b, "f64", 0.3, restart)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert abs(again - its) <= 1 < its < 200
+    # two solutions to the same tolerance, by other roundings: 8 / pi^2 n of them a step
+    if again == its:
+        assert float(torch.linalg.vector_norm(x - want)) <= 1e-7 * float(torch.linalg.vector_norm(want))
