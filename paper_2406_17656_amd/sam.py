@@ -367,6 +367,7 @@ class Plan:
         if isinstance(dL, torch.Tensor) and dL.device == Ak_val.device and dL.is_cuda \
                 and dL.dtype == torch.float64 and dL.numel() == 1:
             # read on the device by this stream's kernels: no wait for its value here
+            dL = dL.resolve_neg()   # a lazy negation is not in the memory they read
             dL.record_stream(torch.cuda.current_stream(dL.device))
             call, scale = self.ctx.lib.sam_backward_scaled, _ptr(dL)
         else:
