@@ -7,7 +7,7 @@ list that its block fits.  ``tune`` times candidate orders on the plan's own
 shape histogram -- the default order and, for every variant, the order that
 puts it first -- then refines the class boundaries of the fastest by leaving
 classes out and swapping neighbours, keeps the fastest (sam_plan_select) and
-caches the choice per device, precision and shape signature in a JSON file
+caches the choice per device, precision, menu and shape signature in a JSON file
 ($SAM_TUNE_CACHE, default ~/.cache/sam_mi355x_tune.json).
 """
 from __future__ import annotations
@@ -59,9 +59,10 @@ def complete(order, prec="f32") -> list[int]:
 def signature(plan, prec) -> str:
     info = plan.info()
     dev = torch.cuda.get_device_name(plan.ctx.device)
-    # selection-invariant shape data (the bucket split depends on the selection)
+    # selection-invariant shape data (the bucket split depends on the selection),
+    # and the menu that an order's indices refer to
     key = json.dumps([dev, prec, info["n"], info["max_rows"], info["max_cols"], info["gathered"],
-                      plan.nnz_S])
+                      plan.nnz_S, [[v["G"], v["R"], v["NC"], v["TC"]] for v in menu(prec)]])
     return hashlib.sha256(key.encode()).hexdigest()[:24]
 
 
@@ -107,9 +108,13 @@ def tune(plan, Ak_val, A0_val, prec="f32", reps=10, use_cache=True, refine=True)
     cache = _load_cache() if use_cache else {}
     if sig in cache:
         order = cache[sig]["order"]
-        plan.select(order, prec)
-        return {"order": order, "us": cache[sig]["us"], "timings": cache[sig].get("timings", {}),
-                "cached": True}
+        try:
+            plan.select(order, prec)
+        except SamError:
+            pass   # an order of another menu, or one that leaves a column out: tuned again
+        else:
+            return {"order": order, "us": cache[sig]["us"], "timings": cache[sig].get("timings", {}),
+                    "cached": True}
     n_var = len(menu(prec))
     timings = {}
 
