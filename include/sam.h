@@ -282,6 +282,12 @@ sam_status sam_menu(int32_t prec, int32_t weighted, int32_t capacity, int32_t* c
 sam_status sam_plan_select(sam_plan* plan, int32_t prec, const int32_t* order, int32_t count,
                            sam_stream_t stream);
 
+/* The variants that the plan's plain builds in precision `prec` use now, as an
+ * order for sam_plan_select: host outputs of `capacity` entries (may be NULL
+ * for 0); *count receives their number.  SAM_ERR_ARG for NULL and for an
+ * unknown precision. */
+sam_status sam_plan_order(const sam_plan* plan, int32_t prec, int32_t capacity, int32_t* count, int32_t* order);
+
 /* Numeric SAM build on a plan (Section 2): for every column j solve
  * min ||A_k(I_j,J_j) m - A_0(I_j,j)||_2 by Householder QR and back
  * substitution (prec selects FP64 or FP32 + FP64-residual refinement), write
@@ -463,6 +469,9 @@ sam_status sam_sequence_pattern(sam_seq* seq, int32_t k, int32_t* S_colptr, int3
 
 /* sam_plan_select for the sequence's precision; the next run re-captures. */
 sam_status sam_sequence_select(sam_seq* seq, const int32_t* order, int32_t count, sam_stream_t stream);
+
+/* sam_plan_order of the sequence's classes (its precision). */
+sam_status sam_sequence_order(const sam_seq* seq, int32_t capacity, int32_t* count, int32_t* order);
 
 /* Build every map of the sequence: Ak_vals (host array of n_src device
  * pointers), M_vals (host array of n_src device pointers), res2 (device,

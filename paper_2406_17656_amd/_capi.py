@@ -73,7 +73,9 @@ SIGNATURES = {
     "sam_plan_cost_weighted": (c_int32, [P, c_int32, c_int32, ctypes.POINTER(c_double), ctypes.POINTER(c_double)]),
     "sam_menu": (c_int32, [c_int32, c_int32, c_int32, ctypes.POINTER(c_int32), P, P, P, P]),
     "sam_plan_select": (c_int32, [P, c_int32, P, c_int32, P]),
+    "sam_plan_order": (c_int32, [P, c_int32, c_int32, P, P]),
     "sam_sequence_select": (c_int32, [P, P, c_int32, P]),
+    "sam_sequence_order": (c_int32, [P, c_int32, P, P]),
     "sam_build_planned": (c_int32, [P, P, P, c_int32, P, P, P, P]),
     "sam_workspace_size": (c_int32, [P, CSCP, CSCP, P, P, c_int64, c_int32, SZ, P]),
     "sam_build": (c_int32, [P, CSCP, CSCP, P, P, c_int64, c_int32, P, P, P, P, c_size_t, P]),

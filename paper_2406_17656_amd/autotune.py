@@ -4,8 +4,9 @@ The library compiles a menu of kernel variants per precision (lanes per
 column problem G, rows per lane R, columns NC, LDS tile chunk TC; see
 sam_menu).  A plan buckets each column into the first variant of an ordered
 list that its block fits.  ``tune`` times candidate orders on the plan's own
-shape histogram -- the default order and, for every variant, the order that
-puts it first -- then refines the class boundaries of the fastest by leaving
+shape histogram -- the classes it has (those the library picked, until others
+were selected), the menu's order and, for every variant, the order that puts it
+first -- then refines the class boundaries of the fastest by leaving
 classes out and swapping neighbours, keeps the fastest (sam_plan_select) and
 caches the choice per device, precision, menu and shape signature in a JSON file
 ($SAM_TUNE_CACHE, default ~/.cache/sam_mi355x_tune.json).
@@ -128,7 +129,8 @@ def tune(plan, Ak_val, A0_val, prec="f32", reps=10, use_cache=True, refine=True)
         return us
 
     best = None
-    for order in candidate_orders(n_var):
+    # completed: the classes appended after it get no column and no launch
+    for order in [complete(plan.order(prec), prec)] + candidate_orders(n_var):
         us = trial(order)
         if us is not None and (best is None or us < best[1]):
             best = (order, us)
@@ -165,8 +167,9 @@ def tune_sequence(seq, vals, order, prec="f32", reps=3, refine=True) -> dict:
     ``tune`` times orders on one source's plan; the sources of a sequence can
     differ in shape (a threshold drops more couplings from some sources than
     from others), and which classes pay off depends on all of them.  The
-    candidates are ``order`` and the orders that put each variant first (the
-    menu's other variants appended, see ``complete``); the fastest is refined
+    candidates are the classes the sequence has, ``order`` and the orders that
+    put each variant first (the menu's other variants appended, see
+    ``complete``); the fastest is refined
     as in ``tune`` (a class moved to the end, neighbours swapped, kept when 2 %
     faster).  Leaves the sequence selected; returns {"order", "ms",
     "timings"}."""
@@ -197,7 +200,7 @@ def tune_sequence(seq, vals, order, prec="f32", reps=3, refine=True) -> dict:
         return o, ms
 
     best = None
-    for cand in [list(order)] + candidate_orders(n_var):
+    for cand in [seq.order(), list(order)] + candidate_orders(n_var):
         o, ms = trial(cand)
         if ms is not None and (best is None or ms < best[1]):
             best = (o, ms)

@@ -1249,6 +1249,16 @@ std::vector<const NumericVariant*> menu_subset(int prec, int weighted, const int
     return out;
 }
 
+sam_status combo_order(const Combo& cb, int prec, int32_t capacity, int32_t* count, int32_t* order) {
+    if (!count || capacity < 0 || (capacity > 0 && !order)) return SAM_ERR_ARG;
+    std::vector<const NumericVariant*> all;
+    menu_table(prec, 0, &all);
+    *count = (int32_t)cb.variants.size();
+    for (int32_t i = 0; i < capacity && i < *count; ++i)
+        order[i] = (int32_t)(std::find(all.begin(), all.end(), cb.variants[(size_t)i]) - all.begin());
+    return SAM_OK;
+}
+
 sam_status plan_select(sam_plan* pl, int prec, const std::vector<const NumericVariant*>& vars, hipStream_t s) {
     sam_ctx* ctx = pl->ctx;
     Combo& cb = pl->combo[prec][0];
@@ -1283,6 +1293,12 @@ sam_status sam_menu(int32_t prec, int32_t weighted, int32_t capacity, int32_t* c
         if (TC) TC[i] = all[i]->TC;
     }
     return SAM_OK;
+}
+
+sam_status sam_plan_order(const sam_plan* plan, int32_t prec, int32_t capacity, int32_t* count, int32_t* order) {
+    if (!plan || !prec_ok(prec)) return SAM_ERR_ARG;
+    const int p = prec == SAM_PREC_F32_REFINE ? 1 : 0;
+    return combo_order(plan->combo[p][0], p, capacity, count, order);
 }
 
 sam_status sam_plan_select(sam_plan* plan, int32_t prec, const int32_t* order, int32_t count,

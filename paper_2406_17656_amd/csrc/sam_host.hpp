@@ -256,6 +256,8 @@ samk::BucketTable table_of(const std::vector<const samk::NumericVariant*>& vars,
 // Variants of sam_menu(prec, weighted) in the given order (nullptr entries when out of range).
 std::vector<const samk::NumericVariant*> menu_subset(int prec, int weighted, const int32_t* order, int32_t count,
                                                      bool* ok);
+// The menu indices of a combination's classes, in their order.
+sam_status combo_order(const Combo& cb, int prec, int32_t capacity, int32_t* count, int32_t* order);
 // Re-bucket a plan's plain builds over a selected variant order (synchronising).
 sam_status plan_select(sam_plan* pl, int prec, const std::vector<const samk::NumericVariant*>& vars, hipStream_t s);
 // Capacity of a plan's partial-sum buffer: every bucket's launch at the

@@ -619,6 +619,11 @@ sam_status sam_sequence_select(sam_seq* q, const int32_t* order, int32_t count, 
     return SAM_OK;
 }
 
+sam_status sam_sequence_order(const sam_seq* q, int32_t capacity, int32_t* count, int32_t* order) {
+    if (!q) return SAM_ERR_ARG;
+    return combo_order(q->plan->combo[q->prec][0], q->prec, capacity, count, order);
+}
+
 sam_status sam_sequence_run(sam_seq* q, const double* const* Ak_vals, void* const* M_vals, double* res2,
                             sam_stream_t stream) {
     if (!q || !q->ctx) return SAM_ERR_ARG;

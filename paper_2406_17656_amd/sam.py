@@ -263,6 +263,12 @@ class Context:
                         replan_each_run)
 
 
+def _order(ctx, fn, *args) -> list[int]:
+    out, cnt = (ctypes.c_int32 * 16)(), ctypes.c_int32()
+    ctx.check(fn(*args, 16, ctypes.byref(cnt), out))
+    return list(out[:cnt.value])
+
+
 class Plan:
     """sam_plan: symbolic analysis of the column problems."""
 
@@ -310,6 +316,10 @@ class Plan:
         """sam_plan_select: serve columns with the first listed menu variant that fits."""
         arr = (ctypes.c_int32 * len(order))(*order)
         self.ctx.check(self.ctx.lib.sam_plan_select(self.h, _prec(prec), arr, len(order), self.ctx.stream()))
+
+    def order(self, prec="f32") -> list[int]:
+        """sam_plan_order: the classes in use, as an order for select."""
+        return _order(self.ctx, self.ctx.lib.sam_plan_order, self.h, _prec(prec))
 
     def cost(self, prec="f32") -> dict:
         f32 = ctypes.c_double(); f64 = ctypes.c_double(); by = ctypes.c_double()
@@ -429,6 +439,10 @@ class Sequence:
     def select(self, order):
         arr = (ctypes.c_int32 * len(order))(*order)
         self.ctx.check(self.ctx.lib.sam_sequence_select(self.h, arr, len(order), self.ctx.stream()))
+
+    def order(self) -> list[int]:
+        """sam_sequence_order: the classes in use, as an order for select."""
+        return _order(self.ctx, self.ctx.lib.sam_sequence_order, self.h)
 
     def run(self, Ak_vals, M_vals, res2):
         arr_a = (ctypes.c_void_p * self.n_src)(*[t.data_ptr() for t in Ak_vals])

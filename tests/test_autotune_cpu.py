@@ -54,3 +54,48 @@ def test_cached_order_that_is_refused_is_tuned_again():
     plan = Plan(refused=[best])
     res = autotune.tune(plan, None, None, "f32")
     assert not res["cached"] and res["order"] != best and plan.selected == res["order"]
+
+
+def test_plan_keeps_its_classes_where_they_are_fastest(monkeypatch):
+    """No order of the menu's first-variant family is as fast as the classes that
+    the plan came with."""
+    own = [5, 3, 9]
+    monkeypatch.setattr(autotune, "_time", lambda plan, *a: 5.0 if plan.selected[:3] == own else 9.0)
+    plan = Plan(first=own)
+    res = autotune.tune(plan, None, None, "f32", use_cache=False)
+    assert res["order"][:3] == own and res["us"] == 5.0 and plan.selected == res["order"]
+
+
+def test_sequence_keeps_its_classes_where_they_are_fastest(monkeypatch):
+    own = [5, 3, 9]
+
+    class Seq(Plan):
+        n_src, now = 2, 0.0
+
+        def order(self):
+            return list(self.selected)
+
+        def select(self, order):
+            Plan.select(self, order, "f32")
+
+        def alloc_maps(self):
+            return []
+
+        def run(self, *a):
+            Seq.now += 1.0 if self.selected[:3] == own else 2.0
+
+    import time
+    monkeypatch.setattr(time, "perf_counter", lambda: Seq.now)
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda: None)
+    seq = Seq(first=own)
+    res = autotune.tune_sequence(seq, [torch.zeros(1)], [0], "f32", reps=2)
+    assert res["order"][:3] == own and seq.selected == res["order"]
+
+
+def test_order_calls_validate_arguments():
+    import ctypes
+    from paper_2406_17656_amd import _capi as C
+    lib = C.load()
+    out, cnt = (ctypes.c_int32 * 16)(), ctypes.c_int32()
+    assert lib.sam_plan_order(None, 1, 16, ctypes.byref(cnt), out) == C.SAM_ERR_ARG
+    assert lib.sam_sequence_order(None, 16, ctypes.byref(cnt), out) == C.SAM_ERR_ARG
