@@ -348,95 +348,166 @@ int class_counts(const sam_plan* pl, const BucketTable& tab, std::vector<int>* c
 // from every column's cheapest class, a class is given up, or exchanged for
 // one not in use, while that helps.  Columns fall into few distinct sets of
 // fitting classes, so this is some ten thousand operations.
-// shrinks: the shapes are the largest each column can have (a sequence with
-// a sparsification rule).  What its sources leave is not known, so eighths of
-// the columns are taken at each eighth f of the width, with the rows at f^0.8
-// (a smaller stencil of the same kind), f^0.5 and f^0.3 (a thresholded column
-// keeps most of its rows), and the classes that pay off for that are used:
-// few at small n, where a launch costs more than its columns save.  A launch
-// counts more here, for a class may turn out to get hardly any columns.
+// shrinks: the shapes are the largest each column can have (a sequence with a
+// sparsification rule): spread_order.
 // Empty: some column fits no class.
-std::vector<const NumericVariant*> fitted_order(const sam_plan* pl, int prec, bool shrinks) {
-    const double launch_us = shrinks ? 8.0 : 2.0;   // beyond the class's own time
-    std::vector<const NumericVariant*> all;
-    menu_table(prec, 0, &all);
-    auto is_long = [&](const NumericVariant* v) { return v->long_columns(pl->n, pl->nnzA, pl->max_len_A); };
-    auto col_ns = [&](const NumericVariant* v) { return is_long(v) ? v->col_ns_long : v->col_ns; };
-    std::stable_sort(all.begin(), all.end(),
-                     [&](const NumericVariant* a, const NumericVariant* b) { return col_ns(a) < col_ns(b); });
-    if (pl->shapes.empty() || pl->shapes[samk::kShapeCells - 1] > 0) return {};
-    std::vector<std::pair<unsigned, double>> sets;   // fitting classes (bits), columns
-    auto add = [&](int r, int c, double cnt) {
+namespace {
+
+struct FitModel {
+    std::vector<const NumericVariant*> all;   // the cheapest per column first
+    std::vector<float> round, col;            // their figures on this matrix
+    using Sets = std::vector<std::pair<unsigned, double>>;   // fitting classes (bits), columns
+
+    FitModel(const sam_plan* pl, int prec) {
+        menu_table(prec, 0, &all);
+        auto is_long = [&](const NumericVariant* v) { return v->long_columns(pl->n, pl->nnzA, pl->max_len_A); };
+        auto col_ns = [&](const NumericVariant* v) { return is_long(v) ? v->col_ns_long : v->col_ns; };
+        std::stable_sort(all.begin(), all.end(),
+                         [&](const NumericVariant* a, const NumericVariant* b) { return col_ns(a) < col_ns(b); });
+        for (const NumericVariant* v : all) {
+            round.push_back(is_long(v) ? v->round_us_long : v->round_us);
+            col.push_back(col_ns(v));
+        }
+    }
+    unsigned every() const { return (1u << all.size()) - 1u; }
+    // false: the block fits none
+    bool add(Sets* sets, int r, int c, double cnt) const {
         unsigned fits = 0;
         for (size_t v = 0; v < all.size(); ++v)
             if (r <= all[v]->max_rows() && c <= all[v]->NC) fits |= 1u << v;
         if (!fits) return false;
-        auto it = std::find_if(sets.begin(), sets.end(), [&](const auto& p) { return p.first == fits; });
-        if (it == sets.end()) sets.emplace_back(fits, cnt);
+        auto it = std::find_if(sets->begin(), sets->end(), [&](const auto& p) { return p.first == fits; });
+        if (it == sets->end()) sets->emplace_back(fits, cnt);
         else it->second += cnt;
         return true;
-    };
-    for (int r = 0; r <= samk::kShapeRows; ++r)
-        for (int c = 0; c <= samk::kShapeCols; ++c) {
-            const int cnt = pl->shapes[(size_t)r * (samk::kShapeCols + 1) + c];
-            if (!cnt) continue;
-            if (!shrinks) {
-                if (!add(r, c, cnt)) return {};
-                continue;
-            }
-            for (int e = 1; e <= 8; ++e) {
-                const double f = e / 8.0;
-                const int ce = (int)std::ceil(c * f);
-                for (double x : {0.8, 0.5, 0.3})
-                    if (!add((int)std::ceil(r * std::pow(f, x)), ce, cnt / 24.0)) return {};
-            }
-        }
-    std::vector<double> counts(all.size());
-    auto cost = [&](unsigned use) {   // us, or -1 where a column fits none
-        std::fill(counts.begin(), counts.end(), 0.0);
+    }
+    // us of the classes `use`, launch_us a launch beyond the class's own time
+    // (empty_too: also where no column comes); -1 where a column fits none.
+    // served: the classes that get columns.
+    double cost(const Sets& sets, unsigned use, double launch_us, bool empty_too, unsigned* served = nullptr) const {
+        double counts[32] = {};
         for (const auto& p : sets) {
             if (!(p.first & use)) return -1.0;
-            counts[(size_t)__builtin_ctz(p.first & use)] += p.second;
+            counts[__builtin_ctz(p.first & use)] += p.second;
         }
         double t = 0.0;
-        for (size_t v = 0; v < all.size(); ++v)
-            if (counts[v] > 0.0)
-                t += launch_us + std::max<double>(is_long(all[v]) ? all[v]->round_us_long : all[v]->round_us,
-                                                  1e-3 * col_ns(all[v]) * counts[v]);
-        return t;
-    };
-    auto in_use = [&](unsigned use) {   // without the classes that get no column
-        (void)cost(use);
-        unsigned u = 0;
-        for (size_t v = 0; v < all.size(); ++v)
-            if (counts[v] > 0.0) u |= 1u << v;
-        return u;
-    };
-    unsigned use = in_use((1u << all.size()) - 1u);
-    double now = cost(use);
-    for (bool better = true; better;) {
-        better = false;
-        unsigned best = use;
-        auto consider = [&](unsigned cand) {
-            const double t = cost(cand);
-            if (t >= 0.0 && t < now) {
-                now = t;
-                best = cand;
-                better = true;
-            }
-        };
+        unsigned got = 0;
         for (size_t v = 0; v < all.size(); ++v) {
-            if (!(use >> v & 1u)) continue;
-            consider(use & ~(1u << v));
-            for (size_t u = 0; u < all.size(); ++u)
-                if (!(use >> u & 1u)) consider((use & ~(1u << v)) | 1u << u);
+            if (counts[v] > 0.0) {
+                got |= 1u << v;
+                t += std::max<double>(round[v], 1e-3 * col[v] * counts[v]);
+            }
+            if (counts[v] > 0.0 || (empty_too && (use >> v & 1u))) t += launch_us;
         }
-        use = in_use(best);
+        if (served) *served = got;
+        return t;
     }
-    std::vector<const NumericVariant*> order;
-    for (size_t v = 0; v < all.size(); ++v)
-        if (use >> v & 1u) order.push_back(all[v]);
-    return order;
+    // From `use`: the best class to give up, exchange or (grow) take, again and
+    // again while that makes f (negative: not possible) smaller.
+    template <typename F, typename P>
+    double improve(unsigned* use, bool grow, F f, P prune) const {
+        double now = f(*use);
+        for (bool better = true; better;) {
+            better = false;
+            unsigned best = *use;
+            auto consider = [&](unsigned cand) {
+                const double t = f(cand);
+                if (t >= 0.0 && t < now) {
+                    now = t;
+                    best = cand;
+                    better = true;
+                }
+            };
+            for (size_t v = 0; v < all.size(); ++v) {
+                if (!(*use >> v & 1u)) {
+                    if (grow) consider(*use | 1u << v);
+                    continue;
+                }
+                consider(*use & ~(1u << v));
+                for (size_t u = 0; u < all.size(); ++u)
+                    if (!(*use >> u & 1u)) consider((*use & ~(1u << v)) | 1u << u);
+            }
+            *use = prune(best);
+        }
+        return now;
+    }
+    std::vector<const NumericVariant*> listed(unsigned use) const {
+        std::vector<const NumericVariant*> order;
+        for (size_t v = 0; v < all.size(); ++v)
+            if (use >> v & 1u) order.push_back(all[v]);
+        return order;
+    }
+};
+
+// Classes for columns whose shapes are only known to lie within (r, c): what
+// the rule leaves is not known when the sequence is made.  Rules leave from
+// the diagonal alone (columns of 1) to everything; around a share f of the
+// width most columns lie within 2/3 and 3/2 of it, and the rows go with the
+// width to the power 0.40 to 0.66 (first and last decile and median 0.53 over
+// global, column and lfil rules on 5-, 7- and 9-point matrices, levels 1 and
+// 2).  So ten cases are laid out, and the classes are those whose time is on
+// average the least multiple of each case's best: a class more costs every
+// case a launch (kLaunch us, empty or not), one too few costs the thin cases a
+// multiple of their build.  Weighing the cases by their time instead left
+// 7-point FP64 level-2 columns thinned to the diagonal in the 64 x 25 class:
+// 790 us a run of three at 60^3 where the whole menu takes 390.
+std::vector<const NumericVariant*> spread_order(const sam_plan* pl, const FitModel& m) {
+    constexpr double kLaunch = 6.0;
+    constexpr double kShares[] = {1.0, 0.75, 0.55, 0.4, 0.28, 0.2, 0.14, 0.1, 0.0};   // 0: the diagonal
+    constexpr double kAround[] = {2.0 / 3.0, 1.0, 1.5}, kPowers[] = {0.4, 0.53, 0.66};
+    std::vector<FitModel::Sets> cases(1 + sizeof kShares / sizeof kShares[0]);
+    for (int r = 0; r <= samk::kShapeRows; ++r)
+        for (int c = 0; c <= samk::kShapeCols; ++c) {
+            const double cnt = pl->shapes[(size_t)r * (samk::kShapeCols + 1) + c];
+            if (cnt == 0.0) continue;
+            if (!m.add(&cases[0], r, c, cnt)) return {};   // everything kept
+            for (size_t i = 0; i + 1 < cases.size(); ++i)
+                for (double w : kAround) {
+                    const double f = std::max(std::min(kShares[i] * w, 1.0), 1.0 / std::max(c, 1));
+                    for (double x : kPowers)   // fits: the shape is within (r, c)
+                        (void)m.add(&cases[i + 1], std::min(r, (int)std::ceil(r * std::pow(f, x) - 1e-9)),
+                                    std::min(c, (int)std::ceil(c * f - 1e-9)), cnt / 9.0);
+                }
+        }
+    auto same = [](unsigned use) { return use; };
+    std::vector<double> best;
+    for (const FitModel::Sets& sets : cases) {
+        unsigned use = m.every();
+        best.push_back(m.improve(&use, true, [&](unsigned u) { return m.cost(sets, u, kLaunch, true); }, same));
+    }
+    unsigned use = m.every();
+    m.improve(&use, true, [&](unsigned u) {
+        double t = 0.0;
+        for (size_t i = 0; i < cases.size(); ++i) {
+            const double x = m.cost(cases[i], u, kLaunch, true);
+            if (x < 0.0) return -1.0;
+            t += x / best[i];
+        }
+        return t;
+    }, same);
+    return m.listed(use);
+}
+
+}  // namespace
+
+std::vector<const NumericVariant*> fitted_order(const sam_plan* pl, int prec, bool shrinks) {
+    const FitModel m(pl, prec);
+    if (pl->shapes.empty() || pl->shapes[samk::kShapeCells - 1] > 0) return {};
+    if (shrinks) return spread_order(pl, m);
+    constexpr double kLaunch = 2.0;
+    FitModel::Sets sets;
+    for (int r = 0; r <= samk::kShapeRows; ++r)
+        for (int c = 0; c <= samk::kShapeCols; ++c)
+            if (const int cnt = pl->shapes[(size_t)r * (samk::kShapeCols + 1) + c])
+                if (!m.add(&sets, r, c, cnt)) return {};
+    auto in_use = [&](unsigned use) {   // without the classes that get no column
+        unsigned got = 0;
+        (void)m.cost(sets, use, kLaunch, false, &got);
+        return got;
+    };
+    unsigned use = in_use(m.every());
+    m.improve(&use, false, [&](unsigned u) { return m.cost(sets, u, kLaunch, false); }, in_use);
+    return m.listed(use);
 }
 
 void plan_combo_with(sam_plan* pl, int prec, int weighted, const std::vector<const NumericVariant*>& vars) {

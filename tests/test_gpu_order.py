@@ -58,3 +58,25 @@ def test_sequence_order(kind):
         assert torch.equal(res2, res[0][1]) and all(torch.equal(a, b) for a, b in zip(Ms, res[0][0]))
     seq.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("grid,small", [((8, 8, 8), False), ((40, 40, 40), True)])
+def test_rule_sequence_has_classes_for_thin_columns(grid, small, prec):
+    """What a rule leaves is not known when a sequence is made: at 64000 columns
+    some class is made for columns that keep little, beside one for the whole
+    63 x 25 block; few columns have one class for all."""
+    from paper_2406_17656_amd import Context, DeviceCSC, autotune
+    A0h, Ash = P.config3(m=grid[0])
+    ctx = Context(0)
+    A0, Ak = DeviceCSC.from_host(A0h), DeviceCSC.from_host(Ash[0])
+    seq = ctx.sequence(A0, Ak, 1, prec=prec, power=2, kind="column", tau=0.6, replan_each_run=True)
+    menu = autotune.menu(prec)
+    cells = [menu[i]["max_rows"] * menu[i]["NC"] for i in seq.order()]
+    assert max(cells) >= 63 * 25
+    # the narrowest class is at most a quarter of the block, where there is one
+    assert min(cells) <= 63 * 25 // 4 if small else len(cells) == 1
+    if small and prec == "f64":
+        assert min(cells) <= 16 * 8    # 0.16 ns a column against 6.8
+    seq.close()
+    ctx.close()
