@@ -1129,8 +1129,8 @@ const NumericVariant kMenu[] = {
     SAM_PLAIN_LONG(float, 1, 4, 12, 14, 1, 2, 16.4f, 0.637f, 17.7f, 0.71f),
     SAM_PLAIN(float, 1, 4, 12, 16, 1, 2, 18.8f, 0.76f, 22.f, 0.871f),
     SAM_PLAIN(float, 1, 4, 10, 20, 1, 2, 22.f, 0.916f, 25.f, 1.036f),
-    SAM_PLAIN(float, 1, 8, 6, 25, 1, 1, 23.6f, 1.99f, 27.f, 2.154f),
-    SAM_PLAIN(float, 1, 8, 8, 25, 1, 1, 27.7f, 2.24f, 31.f, 2.442f),
+    SAM_PLAIN_LONG(float, 1, 8, 6, 25, 1, 1, 23.6f, 1.99f, 26.5f, 2.25f),
+    SAM_PLAIN_LONG(float, 1, 8, 8, 25, 1, 1, 27.7f, 2.24f, 31.f, 2.6f),
     SAM_PLAIN(float, 1, 32, 4, 32, 1, 1, 49.6f, 13.1f, 49.6f, 13.1f),
     SAM_PLAIN(float, 1, 1, 13, 5, 1, 5, 7.2f, 0.077f, 7.2f, 0.077f),   // one problem per lane, no reductions
     SAM_PLAIN(float, 1, 8, 4, 13, 2, 1, 10.1f, 0.572f, 14.7f, 0.78f),
