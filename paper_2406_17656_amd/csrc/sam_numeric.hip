@@ -111,8 +111,11 @@ constexpr int numeric_min_waves(bool f32, int G, int R, int NC, int MODE) {
     return (G == 16 && R == 4 && NC == 25) ? 3 : is_tight(f32, R, NC, MODE) ? 2 : 1;
 }
 
+// The code of the wide classes (97 KB for 64 x 25 in FP64) is larger than the
+// instruction cache, and where it starts shows: other kernels put before it
+// moved that class from 1803 to 1825 us at 64^3; on a 4 KiB boundary 1809.
 template <typename TQ, int G, int R, int NC, int TC, int LPL, int MODE>
-__global__ void __launch_bounds__(64)
+__attribute__((aligned(4096))) __global__ void __launch_bounds__(64)
 __attribute__((amdgpu_waves_per_eu(numeric_min_waves(std::is_same<TQ, float>::value, G, R, NC, MODE))))
 k_numeric(NumericArgs a) {
     constexpr bool WEIGHTED = MODE >= 1;
