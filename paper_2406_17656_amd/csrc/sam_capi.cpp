@@ -356,9 +356,12 @@ namespace {
 struct FitModel {
     std::vector<const NumericVariant*> all;   // the cheapest per column first
     std::vector<float> round, col;            // their figures on this matrix
+    std::vector<double> few;                  // columns that their form for few takes
     using Sets = std::vector<std::pair<unsigned, double>>;   // fitting classes (bits), columns
 
-    FitModel(const sam_plan* pl, int prec) {
+    // exact: the shapes' counts are the launches'; else a launch is sized for
+    // more columns than come, at most all
+    FitModel(const sam_plan* pl, int prec, bool exact) {
         menu_table(prec, 0, &all);
         auto is_long = [&](const NumericVariant* v) { return v->long_columns(pl->n, pl->nnzA, pl->max_len_A); };
         auto col_ns = [&](const NumericVariant* v) { return is_long(v) ? v->col_ns_long : v->col_ns; };
@@ -367,7 +370,13 @@ struct FitModel {
         for (const NumericVariant* v : all) {
             round.push_back(is_long(v) ? v->round_us_long : v->round_us);
             col.push_back(col_ns(v));
+            const double most = (double)v->few_columns(pl->ctx->CUs);
+            few.push_back(exact || pl->n <= most ? most : 0.0);
         }
+    }
+    double time(size_t v, double cnt) const {
+        if (cnt <= few[v]) return std::max<double>(all[v]->few->round_us, 1e-3 * all[v]->few->col_ns * cnt);
+        return std::max<double>(round[v], 1e-3 * col[v] * cnt);
     }
     unsigned every() const { return (1u << all.size()) - 1u; }
     // false: the block fits none
@@ -395,7 +404,7 @@ struct FitModel {
         for (size_t v = 0; v < all.size(); ++v) {
             if (counts[v] > 0.0) {
                 got |= 1u << v;
-                t += std::max<double>(round[v], 1e-3 * col[v] * counts[v]);
+                t += time(v, counts[v]);
             }
             if (counts[v] > 0.0 || (empty_too && (use >> v & 1u))) t += launch_us;
         }
@@ -491,7 +500,7 @@ std::vector<const NumericVariant*> spread_order(const sam_plan* pl, const FitMod
 }  // namespace
 
 std::vector<const NumericVariant*> fitted_order(const sam_plan* pl, int prec, bool shrinks) {
-    const FitModel m(pl, prec);
+    const FitModel m(pl, prec, !shrinks);
     if (pl->shapes.empty() || pl->shapes[samk::kShapeCells - 1] > 0) return {};
     if (shrinks) return spread_order(pl, m);
     constexpr double kLaunch = 2.0;
@@ -773,11 +782,14 @@ sam_status run_numeric(sam_plan* pl, const double* Ak_val, const double* A0_val,
         if (cnt <= 0) continue;
         const NumericVariant* v = cb.variants[b];
         a.bucket = cb.slot.empty() ? (int)b : cb.slot[b];
+        // as many waves as the few-column form is made for
+        const int few = cnt <= v->few_columns(ctx->CUs) ? 4 * v->few_waves : 0;
+        if (few) v = v->few;
         const int groups = (cnt + v->per_wave() - 1) / v->per_wave();
         // one round of resident blocks for the plain maps; the weighted
         // forms run faster over two rounds (as the adjoint's launch)
         const bool lng = v->launch_long && v->long_columns(pl->n, pl->nnzA, pl->max_len_A);
-        const int per_cu = weighted ? std::min(16, 2 * resident_blocks(ctx, v)) : resident_blocks(ctx, v, lng);
+        const int per_cu = few ? few : weighted ? std::min(16, 2 * resident_blocks(ctx, v)) : resident_blocks(ctx, v, lng);
         const int grid = samk::launch_grid(groups, ctx->CUs * per_cu);
         if (res2 && parts + grid > pl->partcap)
             return fail(ctx, SAM_ERR_HIP, "partial-sum buffer too small (%d blocks)", parts + grid);

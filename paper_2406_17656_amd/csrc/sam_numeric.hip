@@ -1092,16 +1092,39 @@ using LaunchFn = hipError_t (*)(const NumericArgs&, int, hipStream_t);
 
 #define SAM_PLAIN(TQ, PREC, G, R, NC, TC, LPL, ...)                                        \
     NumericVariant{PREC, G, R, NC, 0, TC, LPL, &launch_numeric<TQ, G, R, NC, TC, LPL, 0>,  \
-                   nullptr, &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, 0>, nullptr, nullptr, __VA_ARGS__}
+                   nullptr, &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, 0>, nullptr, nullptr, __VA_ARGS__, nullptr, 0}
+// few, waves: the entry of kFew, and its few_waves
+#define SAM_PLAIN_FEW(few, waves, TQ, PREC, G, R, NC, TC, LPL, ...)                               \
+    NumericVariant{PREC, G, R, NC, 0, TC, LPL, &launch_numeric<TQ, G, R, NC, TC, LPL, 0>,  \
+                   nullptr, &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, 0>, nullptr, nullptr, __VA_ARGS__, &kFew[few], waves}
+#define SAM_PLAIN_LONG_FEW(few, waves, TQ, PREC, G, R, NC, TC, LPL, ...)                          \
+    NumericVariant{PREC, G, R, NC, 0, TC, LPL, &launch_numeric<TQ, G, R, NC, TC, LPL, 0>,  \
+                   nullptr, &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, 0>,              \
+                   &launch_numeric<TQ, G, R, NC, TC, LPL + 1, 0>,                          \
+                   &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL + 1, 0>, __VA_ARGS__, &kFew[few], waves}
 #define SAM_PLAIN_LONG(TQ, PREC, G, R, NC, TC, LPL, ...)                                   \
     NumericVariant{PREC, G, R, NC, 0, TC, LPL, &launch_numeric<TQ, G, R, NC, TC, LPL, 0>,  \
                    nullptr, &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, 0>,              \
                    &launch_numeric<TQ, G, R, NC, TC, LPL + 1, 0>,                          \
-                   &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL + 1, 0>, __VA_ARGS__}
+                   &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL + 1, 0>, __VA_ARGS__, nullptr, 0}
 #define SAM_WEIGHTED(TQ, PREC, G, R, NC, TC, LPL)                                          \
     NumericVariant{PREC, G, R, NC, 1, TC, LPL, &launch_numeric<TQ, G, R, NC, TC, LPL, 1>,  \
                    &launch_numeric<TQ, G, R, NC, TC, LPL, 2>,                              \
-                   &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, 1>, nullptr, nullptr, 0, 0, 0, 0}
+                   &numeric_blocks_per_cu<TQ, G, R, NC, TC, LPL, 1>, nullptr, nullptr, 0, 0, 0, 0, nullptr, 0}
+
+// Eight lanes a problem for the few columns of four classes of four lanes: a
+// wave takes half as many problems and is done sooner, which is what counts
+// while the waves have a SIMD to themselves (48 x 16: while they are resident
+// at once).  Four lanes / eight, us: 48 x 16 96 columns 24.2 / 15.7, 8000 25.3
+// / 18.7, 24000 34.9 / 31.3; 40 x 20 23.6 / 18.9, 30.2 / 23.0, 16000 33.2 /
+// 30.6, 20000 40.2 / 43.8; 40 x 14 16.5 / 13.3, 17.5 / 16.5, 12000 18.6 /
+// 20.4; 36 x 12 in the last 8500 17.0 / 19.8.
+const NumericVariant kFew[] = {
+    SAM_PLAIN(float, 1, 8, 5, 16, 1, 2, 15.f, 2.2f, 15.f, 2.2f),
+    SAM_PLAIN(float, 1, 8, 6, 14, 1, 2, 13.3f, 2.f, 13.3f, 2.f),
+    SAM_PLAIN(float, 1, 8, 6, 16, 1, 2, 15.7f, 1.3f, 15.7f, 1.3f),
+    SAM_PLAIN(float, 1, 8, 5, 20, 1, 2, 18.8f, 1.9f, 18.8f, 1.9f),
+};
 
 // Menu per precision, cheapest first.  Shapes of the workloads: 2D 5-point
 // level 1 (13 x 5), level 2 (25 x 13); 3D 7-point level 2 (63 x 25); 2D
@@ -1128,10 +1151,10 @@ const NumericVariant kMenu[] = {
     SAM_PLAIN_LONG(float, 1, 4, 9, 10, 1, 2, 9.5f, 0.318f, 11.2f, 0.396f),   // ragged 9-point / thresholded blocks
     SAM_PLAIN(float, 1, 4, 9, 12, 1, 2, 10.9f, 0.39f, 15.3f, 0.546f),
     SAM_PLAIN(float, 1, 4, 7, 13, 1, 2, 11.1f, 0.392f, 15.4f, 0.54f),
-    SAM_PLAIN(float, 1, 4, 10, 16, 1, 2, 16.6f, 0.69f, 19.8f, 0.804f),
-    SAM_PLAIN_LONG(float, 1, 4, 12, 14, 1, 2, 16.4f, 0.637f, 17.7f, 0.71f),
-    SAM_PLAIN(float, 1, 4, 12, 16, 1, 2, 18.8f, 0.76f, 22.f, 0.871f),
-    SAM_PLAIN(float, 1, 4, 10, 20, 1, 2, 22.f, 0.916f, 25.f, 1.036f),
+    SAM_PLAIN_FEW(0, 1, float, 1, 4, 10, 16, 1, 2, 16.6f, 0.69f, 19.8f, 0.804f),
+    SAM_PLAIN_LONG_FEW(1, 1, float, 1, 4, 12, 14, 1, 2, 16.4f, 0.637f, 17.7f, 0.71f),
+    SAM_PLAIN_FEW(2, 3, float, 1, 4, 12, 16, 1, 2, 18.8f, 0.76f, 22.f, 0.871f),
+    SAM_PLAIN_FEW(3, 2, float, 1, 4, 10, 20, 1, 2, 22.f, 0.916f, 25.f, 1.036f),
     SAM_PLAIN_LONG(float, 1, 8, 6, 25, 1, 1, 23.6f, 1.99f, 26.5f, 2.25f),
     SAM_PLAIN_LONG(float, 1, 8, 8, 25, 1, 1, 27.7f, 2.24f, 31.f, 2.6f),
     SAM_PLAIN(float, 1, 32, 4, 32, 1, 1, 49.6f, 13.1f, 49.6f, 13.1f),

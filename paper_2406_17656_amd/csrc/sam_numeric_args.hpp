@@ -66,8 +66,13 @@ struct NumericVariant {
     // (us), and a column once the GPU is full (ns); then the same on such
     // matrices
     float round_us, col_ns, round_us_long, col_ns_long;
+    // the plain form for few columns: more lanes a problem, the same blocks or
+    // larger (null: none), and the waves a SIMD up to which it is the faster
+    const NumericVariant* few;
+    int few_waves;
     int max_rows() const { return G * R; }
     int per_wave() const { return 64 / G; }
+    int64_t few_columns(int CUs) const { return few ? (int64_t)4 * few_waves * CUs * few->per_wave() : 0; }
     // Columns longer than the lanes hold take a memory loop, a load at a time.
     // A few of them (boundary rows, one dense column) are cheaper left to it
     // than an entry more per lane for all: most columns have to be that long.
