@@ -357,6 +357,7 @@ struct FitModel {
     std::vector<const NumericVariant*> all;   // the cheapest per column first
     std::vector<float> round, col;            // their figures on this matrix
     std::vector<double> few;                  // columns that their form for few takes
+    unsigned rows_fit[samk::kShapeRows + 1] = {}, cols_fit[samk::kShapeCols + 1] = {};   // classes (bits)
     using Sets = std::vector<std::pair<unsigned, double>>;   // fitting classes (bits), columns
 
     // exact: the shapes' counts are the launches'; else a launch is sized for
@@ -373,6 +374,10 @@ struct FitModel {
             const double most = (double)v->few_columns(pl->ctx->CUs);
             few.push_back(exact || pl->n <= most ? most : 0.0);
         }
+        for (size_t v = 0; v < all.size(); ++v) {
+            for (int r = 0; r <= std::min(samk::kShapeRows, all[v]->max_rows()); ++r) rows_fit[r] |= 1u << v;
+            for (int c = 0; c <= std::min(samk::kShapeCols, all[v]->NC); ++c) cols_fit[c] |= 1u << v;
+        }
     }
     double time(size_t v, double cnt) const {
         if (cnt <= few[v]) return std::max<double>(all[v]->few->round_us, 1e-3 * all[v]->few->col_ns * cnt);
@@ -381,9 +386,7 @@ struct FitModel {
     unsigned every() const { return (1u << all.size()) - 1u; }
     // false: the block fits none
     bool add(Sets* sets, int r, int c, double cnt) const {
-        unsigned fits = 0;
-        for (size_t v = 0; v < all.size(); ++v)
-            if (r <= all[v]->max_rows() && c <= all[v]->NC) fits |= 1u << v;
+        const unsigned fits = rows_fit[r] & cols_fit[c];
         if (!fits) return false;
         auto it = std::find_if(sets->begin(), sets->end(), [&](const auto& p) { return p.first == fits; });
         if (it == sets->end()) sets->emplace_back(fits, cnt);
@@ -394,27 +397,27 @@ struct FitModel {
     // (empty_too: also where no column comes); -1 where a column fits none.
     // served: the classes that get columns.
     double cost(const Sets& sets, unsigned use, double launch_us, bool empty_too, unsigned* served = nullptr) const {
-        double counts[32] = {};
-        for (const auto& p : sets) {
-            if (!(p.first & use)) return -1.0;
-            counts[__builtin_ctz(p.first & use)] += p.second;
-        }
-        double t = 0.0;
+        double counts[samk::kMaxBuckets] = {};
         unsigned got = 0;
-        for (size_t v = 0; v < all.size(); ++v) {
-            if (counts[v] > 0.0) {
-                got |= 1u << v;
-                t += time(v, counts[v]);
-            }
-            if (counts[v] > 0.0 || (empty_too && (use >> v & 1u))) t += launch_us;
+        for (const auto& p : sets) {
+            const unsigned fits = p.first & use;
+            if (!fits) return -1.0;
+            counts[__builtin_ctz(fits)] += p.second;
+            got |= fits & -fits;
+        }
+        double t = launch_us * __builtin_popcount(empty_too ? use : got);
+        for (unsigned left = got; left; left &= left - 1) {
+            const size_t v = (size_t)__builtin_ctz(left);
+            t += time(v, counts[v]);
         }
         if (served) *served = got;
         return t;
     }
-    // From `use`: the best class to give up, exchange or (grow) take, again and
-    // again while that makes f (negative: not possible) smaller.
+    // From `use`: the best class to give up, exchange (for one at most `reach`
+    // places from it) or (grow) take, again and again while that makes f
+    // (negative: not possible) smaller.
     template <typename F, typename P>
-    double improve(unsigned* use, bool grow, F f, P prune) const {
+    double improve(unsigned* use, bool grow, size_t reach, F f, P prune) const {
         double now = f(*use);
         for (bool better = true; better;) {
             better = false;
@@ -433,7 +436,7 @@ struct FitModel {
                     continue;
                 }
                 consider(*use & ~(1u << v));
-                for (size_t u = 0; u < all.size(); ++u)
+                for (size_t u = v > reach ? v - reach : 0; u < all.size() && u <= v + reach; ++u)
                     if (!(*use >> u & 1u)) consider((*use & ~(1u << v)) | 1u << u);
             }
             *use = prune(best);
@@ -464,28 +467,45 @@ std::vector<const NumericVariant*> spread_order(const sam_plan* pl, const FitMod
     constexpr double kLaunch = 6.0;
     constexpr double kShares[] = {1.0, 0.75, 0.55, 0.4, 0.28, 0.2, 0.14, 0.1, 0.0};   // 0: the diagonal
     constexpr double kAround[] = {2.0 / 3.0, 1.0, 1.5}, kPowers[] = {0.4, 0.53, 0.66};
-    std::vector<FitModel::Sets> cases(1 + sizeof kShares / sizeof kShares[0]);
+    constexpr int kCols = samk::kShapeCols + 1;
+    std::vector<FitModel::Sets> cases(1);
+    struct Cell { int r, c; double cnt; };
+    std::vector<Cell> cells;
     for (int r = 0; r <= samk::kShapeRows; ++r)
-        for (int c = 0; c <= samk::kShapeCols; ++c) {
-            const double cnt = pl->shapes[(size_t)r * (samk::kShapeCols + 1) + c];
-            if (cnt == 0.0) continue;
-            if (!m.add(&cases[0], r, c, cnt)) return {};   // everything kept
-            for (size_t i = 0; i + 1 < cases.size(); ++i)
-                for (double w : kAround) {
-                    const double f = std::max(std::min(kShares[i] * w, 1.0), 1.0 / std::max(c, 1));
-                    for (double x : kPowers)   // fits: the shape is within (r, c)
-                        (void)m.add(&cases[i + 1], std::min(r, (int)std::ceil(r * std::pow(f, x) - 1e-9)),
-                                    std::min(c, (int)std::ceil(c * f - 1e-9)), cnt / 9.0);
-                }
+        for (int c = 0; c < kCols; ++c)
+            if (const int cnt = pl->shapes[(size_t)r * kCols + c]) {
+                if (!m.add(&cases[0], r, c, cnt)) return {};   // everything kept
+                cells.push_back({r, c, (double)cnt});
+            }
+    std::vector<double> left(pl->shapes.size());
+    for (double share : kShares) {
+        std::fill(left.begin(), left.end(), 0.0);
+        for (double w : kAround) {
+            int cols[kCols];
+            double rows[kCols][3];
+            for (int c = 0; c < kCols; ++c) {
+                const double f = std::max(std::min(share * w, 1.0), 1.0 / std::max(c, 1));
+                cols[c] = std::min(c, (int)std::ceil(c * f - 1e-9));
+                for (int x = 0; x < 3; ++x) rows[c][x] = std::pow(f, kPowers[x]);
+            }
+            for (const Cell& k : cells)
+                for (double f : rows[k.c])
+                    left[(size_t)std::min(k.r, (int)std::ceil(k.r * f - 1e-9)) * kCols + cols[k.c]] += k.cnt / 9.0;
         }
+        cases.emplace_back();
+        for (size_t i = 0; i < left.size(); ++i)   // fits: within a shape that does
+            if (left[i] > 0.0) (void)m.add(&cases.back(), (int)i / kCols, (int)i % kCols, left[i]);
+    }
     auto same = [](unsigned use) { return use; };
     std::vector<double> best;
+    unsigned use = 0;   // from every case's own best
     for (const FitModel::Sets& sets : cases) {
-        unsigned use = m.every();
-        best.push_back(m.improve(&use, true, [&](unsigned u) { return m.cost(sets, u, kLaunch, true); }, same));
+        unsigned own = 0;
+        (void)m.cost(sets, m.every(), kLaunch, true, &own);
+        best.push_back(m.improve(&own, true, 2, [&](unsigned u) { return m.cost(sets, u, kLaunch, true); }, same));
+        use |= own;
     }
-    unsigned use = m.every();
-    m.improve(&use, true, [&](unsigned u) {
+    m.improve(&use, true, 2, [&](unsigned u) {
         double t = 0.0;
         for (size_t i = 0; i < cases.size(); ++i) {
             const double x = m.cost(cases[i], u, kLaunch, true);
@@ -515,7 +535,7 @@ std::vector<const NumericVariant*> fitted_order(const sam_plan* pl, int prec, bo
         return got;
     };
     unsigned use = in_use(m.every());
-    m.improve(&use, false, [&](unsigned u) { return m.cost(sets, u, kLaunch, false); }, in_use);
+    m.improve(&use, false, m.all.size(), [&](unsigned u) { return m.cost(sets, u, kLaunch, false); }, in_use);
     return m.listed(use);
 }
 
