@@ -446,9 +446,11 @@ sam_status sam_sequence_size(sam_ctx* ctx, const sam_csc* A0, const sam_csc* Ak_
  * `replan_each_run` is nonzero; value-dependent rules are recomputed for every
  * source inside each run, sized to the unsparsified bound.  Everything lives
  * in the caller's `mem` (mem_bytes >= sam_sequence_size), owned by the
- * sequence until sam_sequence_destroy.  The first run with a given set of
- * pointers is captured into a HIP graph; later runs with the same pointers
- * replay it.  M_vals[k] must hold nnz_bound entries (sam_sequence_info).
+ * sequence until sam_sequence_destroy.  A run is enqueued on its stream and
+ * two of the sequence's own; pointers that come a fifth time are captured into
+ * a HIP graph, which later runs with them replay (four graphs at most, kept
+ * until the sequence ends).  M_vals[k] must hold nnz_bound entries
+ * (sam_sequence_info).
  * Errors: SAM_ERR_ARG also for n = 0 (nothing to map) and for memory too
  * small; SAM_ERR_UNSORTED (a bad structure).  Synchronising. */
 sam_status sam_sequence_create(sam_ctx* ctx, const sam_csc* A0, const sam_csc* Ak_struct,
@@ -467,7 +469,9 @@ sam_status sam_sequence_info(const sam_seq* seq, int64_t* nnz_bound);
 sam_status sam_sequence_pattern(sam_seq* seq, int32_t k, int32_t* S_colptr, int32_t* S_rowind, int64_t* nnz_S,
                                 sam_stream_t stream);
 
-/* sam_plan_select for the sequence's precision; the next run re-captures. */
+/* sam_plan_select for the sequence's precision.  Waits for the last run, on
+ * whatever stream it is; graphs of the classes before are not launched again.
+ * Synchronising. */
 sam_status sam_sequence_select(sam_seq* seq, const int32_t* order, int32_t count, sam_stream_t stream);
 
 /* sam_plan_order of the sequence's classes (its precision). */
@@ -475,8 +479,10 @@ sam_status sam_sequence_order(const sam_seq* seq, int32_t capacity, int32_t* cou
 
 /* Build every map of the sequence: Ak_vals (host array of n_src device
  * pointers), M_vals (host array of n_src device pointers), res2 (device,
- * n_src doubles: ||A_k M_k - A_0||_F^2).  Graph-replayed after the first call
- * with the same pointers.  Allocates nothing after the first call. */
+ * n_src doubles: ||A_k M_k - A_0||_F^2).  Asynchronous.  Replays a graph from
+ * the fifth call with the same pointers on (sam_sequence_create); a stream that
+ * is being captured takes the launches themselves.  Runs of one sequence must
+ * not overlap in time.  Allocates no device memory. */
 sam_status sam_sequence_run(sam_seq* seq, const double* const* Ak_vals, void* const* M_vals,
                             double* res2, sam_stream_t stream);
 

@@ -189,7 +189,7 @@ def tune_sequence(seq, vals, order, prec="f32", reps=3, refine=True) -> dict:
             seq.select(o)
         except SamError:
             return o, None
-        seq.run(vals, Ms, res2)          # captures the graph for this order
+        seq.run(vals, Ms, res2)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         for _ in range(reps):

@@ -1,5 +1,13 @@
 // sam_sequence.cpp -- a sequence of sources A_1..A_N mapped to the target A_0
-// (Section 2: every map goes back to A_0), run as one HIP graph.
+// (Section 2: every map goes back to A_0).
+//
+// A run is enqueued on the caller's stream and two of the sequence's own.
+// Pointers that keep coming are captured into a HIP graph after kDirect runs.
+// What a graph saves is the host's time for some 30 launches a map: a level-2
+// sequence of seven maps of 4096 columns takes 175 us instead of 218, one of
+// 512^2 the same either way.  Capture and instantiation cost 0.4 to 1 ms (a
+// first run of the 4096 columns 623 us, 257 without), which trial runs of other
+// classes or outputs that change never earn back.
 //
 // Static mode (structure-only pattern, replan_each_run = 0): the pattern
 // S((I + B)^p) and the plan are computed once at creation; a run is the
@@ -60,25 +68,32 @@ struct sam_seq {
     };
     Scratch part[kBranches];
     std::vector<int*> Sk_cp, Sk_ri;
-    // graph: source k runs on branch k mod kBranches, branch 0 being the
-    // capture stream and the others side[] (parallel branches of the graph,
-    // forked and joined by events)
-    hipStream_t cap = nullptr;
-    hipStream_t side[kBranches - 1] = {};
-    std::vector<hipEvent_t> ev;    // fork, then one join per side stream
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    std::vector<const void*> key;
-    // the stream of exec's last launch: no wait has followed it yet
+    // source k runs on branch k mod kBranches, branch 0 being the run's stream
+    // and the others side streams, forked and joined by events
+    struct Branches {
+        std::vector<hipStream_t> side;     // kBranches - 1 (replanning)
+        std::vector<hipEvent_t> ev;        // fork, then one join per side stream
+    };
+    Branches own;
+    // A captured run: its graph, and the streams and events it was captured with.
+    // They stay until the sequence ends: a graph that may still run is not
+    // destroyed, and no stream or event is captured with twice.
+    struct Captured {
+        std::vector<const void*> key;      // the run's pointers
+        int selection = 0;                 // and the classes they were captured with
+        hipStream_t cap = nullptr;
+        Branches br;
+        hipGraph_t graph = nullptr;
+        hipGraphExec_t exec = nullptr;
+    };
+    std::vector<Captured> graphs;          // at most kGraphs
+    // pointers without a graph, and how many runs had them: the kGraphs that
+    // came last (a caller may alternate between a few sets of outputs)
+    std::vector<std::pair<std::vector<const void*>, int>> seen;
+    int selection = 0;                     // counts the selections
+    // the stream of the last run: no wait of ours has followed it yet
     bool running = false;
     hipStream_t last = nullptr;
-    // replaced graphs whose last launch may still run, oldest first
-    struct Retired {
-        hipGraph_t graph;
-        hipGraphExec_t exec;
-        hipEvent_t end;
-    };
-    std::vector<Retired> retired;
 };
 
 namespace {
@@ -129,27 +144,35 @@ sam_status set_bounds(sam_seq* q, hipStream_t s) {
     return SAM_OK;
 }
 
-void forget_graph(sam_seq* q) {
-    q->exec = nullptr;
-    q->graph = nullptr;
-    q->key.clear();
-    q->running = false;
+// Runs with the same pointers before these are captured, and graphs a sequence
+// keeps at most (further pointers run without one).
+constexpr int kDirect = 4;
+constexpr size_t kGraphs = 4;
+
+hipError_t make_branches(sam_seq::Branches* br) {
+    br->side.assign(kBranches - 1, nullptr);
+    br->ev.assign(kBranches, nullptr);
+    for (hipStream_t& x : br->side)
+        if (const hipError_t e = hipStreamCreateWithFlags(&x, hipStreamNonBlocking); e != hipSuccess) return e;
+    for (hipEvent_t& x : br->ev)
+        if (const hipError_t e = hipEventCreateWithFlags(&x, hipEventDisableTiming); e != hipSuccess) return e;
+    return hipSuccess;
 }
 
-// Only a graph that no launch runs any more is destroyed: the caller waits
-// first (settle), or leaves it to retire_graph.
-void drop_graph(sam_seq* q) {
-    if (q->exec) (void)hipGraphExecDestroy(q->exec);
-    if (q->graph) (void)hipGraphDestroy(q->graph);
-    forget_graph(q);
+// (nothing runs any more)
+void drop_branches(sam_seq::Branches* br) {
+    for (hipStream_t x : br->side)
+        if (x) (void)hipStreamDestroy(x);
+    for (hipEvent_t x : br->ev)
+        if (x) (void)hipEventDestroy(x);
+    *br = {};
 }
 
-void drop_oldest(sam_seq* q) {
-    const sam_seq::Retired r = q->retired.front();
-    q->retired.erase(q->retired.begin());
-    (void)hipGraphExecDestroy(r.exec);
-    (void)hipGraphDestroy(r.graph);
-    (void)hipEventDestroy(r.end);
+void drop_captured(sam_seq::Captured* c) {
+    if (c->exec) (void)hipGraphExecDestroy(c->exec);
+    if (c->graph) (void)hipGraphDestroy(c->graph);
+    if (c->cap) (void)hipStreamDestroy(c->cap);
+    drop_branches(&c->br);
 }
 
 // Wait for the last run, whatever stream it is on (s is the caller's stream; the
@@ -159,32 +182,6 @@ hipError_t settle(sam_seq* q, hipStream_t s) {
     const hipError_t e = q->last == s ? hipStreamSynchronize(s) : hipDeviceSynchronize();
     if (e == hipSuccess) q->running = false;
     return e;
-}
-
-// Other pointers than the captured ones: the graph goes once its last launch
-// has ended.  A run on the same stream need not wait for that; at most
-// kRetired graphs are kept.
-constexpr size_t kRetired = 4;
-hipError_t retire_graph(sam_seq* q, hipStream_t s) {
-    while (!q->retired.empty()) {
-        hipError_t e = q->retired.size() < kRetired ? hipEventQuery(q->retired.front().end)
-                                                    : hipEventSynchronize(q->retired.front().end);
-        if (e == hipErrorNotReady) break;
-        if (e != hipSuccess) return e;
-        drop_oldest(q);
-    }
-    if (!q->running || q->last != s) {
-        const hipError_t e = settle(q, s);
-        if (e == hipSuccess) drop_graph(q);
-        return e;
-    }
-    hipEvent_t end = nullptr;
-    hipError_t e = hipEventCreateWithFlags(&end, hipEventDisableTiming);
-    if (e == hipSuccess && (e = hipEventRecord(end, s)) != hipSuccess) (void)hipEventDestroy(end);
-    if (e != hipSuccess) return e;
-    q->retired.push_back({q->graph, q->exec, end});
-    forget_graph(q);
-    return hipSuccess;
 }
 
 // Symbolic work for source k (replanning mode) into scratch set R: the
@@ -249,36 +246,62 @@ sam_status enqueue_symbolic(sam_seq* q, int k, sam_seq::Scratch& R, const double
 // of the GPU's registers), the others' symbolic chains take whatever the
 // build leaves free, and a symbolic chain's last kernel hands over to its
 // build with no edge between branches.
-sam_status enqueue_pipelined(sam_seq* q, const double* const* vals, void* const* M, double* res2, hipStream_t s) {
+sam_status enqueue_pipelined(sam_seq* q, const double* const* vals, void* const* M, double* res2,
+                             const sam_seq::Branches& br, hipStream_t s) {
     sam_ctx* ctx = q->ctx;
     const int N = q->n_src;
-    hipEvent_t fork = q->ev[0];
-    HIP_TRY(ctx, hipEventRecord(fork, s));
-    for (hipStream_t x : q->side) HIP_TRY(ctx, hipStreamWaitEvent(x, fork, 0));
+    HIP_TRY(ctx, hipEventRecord(br.ev[0], s));
+    for (hipStream_t x : br.side) HIP_TRY(ctx, hipStreamWaitEvent(x, br.ev[0], 0));
     for (int k = 0; k < N; ++k) {
         const int b = k % kBranches;
         sam_seq::Scratch& R = q->part[b];
-        hipStream_t x = b == 0 ? s : q->side[b - 1];
+        hipStream_t x = b == 0 ? s : br.side[(size_t)b - 1];
         sam_status st = enqueue_symbolic(q, k, R, vals[k], x);
         if (st) return st;
         st = run_numeric(&R.dplan, vals[k], q->A0_val, nullptr, 0.0, q->prec, 0, M[k], nullptr, res2 + k, x);
         if (st) return st;
     }
     for (int b = 1; b < kBranches; ++b) {
-        HIP_TRY(ctx, hipEventRecord(q->ev[b], q->side[b - 1]));
-        HIP_TRY(ctx, hipStreamWaitEvent(s, q->ev[b], 0));
+        HIP_TRY(ctx, hipEventRecord(br.ev[(size_t)b], br.side[(size_t)b - 1]));
+        HIP_TRY(ctx, hipStreamWaitEvent(s, br.ev[(size_t)b], 0));
     }
     return SAM_OK;
 }
 
-sam_status enqueue_run(sam_seq* q, const double* const* vals, void* const* M, double* res2, hipStream_t s) {
-    if (q->replan) return enqueue_pipelined(q, vals, M, res2, s);
+sam_status enqueue_run(sam_seq* q, const double* const* vals, void* const* M, double* res2,
+                       const sam_seq::Branches& br, hipStream_t s) {
+    if (q->replan) return enqueue_pipelined(q, vals, M, res2, br, s);
     for (int k = 0; k < q->n_src; ++k) {
         sam_status st = run_numeric(q->plan, vals[k], q->A0_val, nullptr, 0.0, q->prec, 0, M[k], nullptr,
                                     res2 + k, s);
         if (st) return st;
     }
     return SAM_OK;
+}
+
+// The run captured, with streams and events of its own, as the sequence's last
+// graph; none is kept where that fails.
+sam_status capture_run(sam_seq* q, const std::vector<const void*>& key, const double* const* vals, void* const* M,
+                       double* res2) {
+    sam_ctx* ctx = q->ctx;
+    sam_seq::Captured c;
+    c.key = key;
+    c.selection = q->selection;
+    auto capture = [&]() -> sam_status {
+        HIP_TRY(ctx, hipStreamCreateWithFlags(&c.cap, hipStreamNonBlocking));
+        if (q->replan) HIP_TRY(ctx, make_branches(&c.br));
+        HIP_TRY(ctx, hipStreamBeginCapture(c.cap, hipStreamCaptureModeThreadLocal));
+        const sam_status st = enqueue_run(q, vals, M, res2, c.br, c.cap);
+        const hipError_t e = hipStreamEndCapture(c.cap, &c.graph);
+        if (st) return st;
+        if (e != hipSuccess) return fail(ctx, SAM_ERR_HIP, "graph capture: %s", hipGetErrorString(e));
+        HIP_TRY(ctx, hipGraphInstantiate(&c.exec, c.graph, nullptr, nullptr, 0));
+        return SAM_OK;
+    };
+    const sam_status st = capture();
+    if (st) drop_captured(&c);
+    else q->graphs.push_back(std::move(c));
+    return st;
 }
 
 // Sizes that fix a sequence's memory layout: the structural pattern's level
@@ -504,7 +527,8 @@ sam_status sam_sequence_create(sam_ctx* ctx, const sam_csc* A0, const sam_csc* A
         sam_plan* pl = new (std::nothrow) sam_plan();
         if (!pl) return bail(fail(ctx, SAM_ERR_NOMEM, "host allocation failed"));
         q->plan = pl;
-        if ((st = plan_init(ctx, pl, &skel, A0, q->S_cp, q->S_ri, q->nnzS, plan_mem, plan_sz, -1,
+        // the classes of the sequence's precision: it runs no others
+        if ((st = plan_init(ctx, pl, &skel, A0, q->S_cp, q->S_ri, q->nnzS, plan_mem, plan_sz, q->prec,
                             spec->kind != SAM_SPARSIFY_NONE, s)))
             return bail(st);
         if (pl->E > d.Ebound) return bail(fail(ctx, SAM_ERR_HIP, "gathered entries exceed their bound"));
@@ -531,16 +555,9 @@ sam_status sam_sequence_create(sam_ctx* ctx, const sam_csc* A0, const sam_csc* A
             dp.combo[q->prec][0].ok = true;
             dp.device_counts = true;
         }
-        for (hipStream_t& x : q->side)
-            if (hipStreamCreateWithFlags(&x, hipStreamNonBlocking) != hipSuccess)
-                return bail(fail(ctx, SAM_ERR_HIP, "stream creation failed"));
-        q->ev.assign(kBranches, nullptr);
-        for (hipEvent_t& e : q->ev)
-            if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess)
-                return bail(fail(ctx, SAM_ERR_HIP, "event creation failed"));
+        if (make_branches(&q->own) != hipSuccess)
+            return bail(fail(ctx, SAM_ERR_HIP, "stream or event creation failed"));
     }
-    if (hipStreamCreateWithFlags(&q->cap, hipStreamNonBlocking) != hipSuccess)
-        return bail(fail(ctx, SAM_ERR_HIP, "stream creation failed"));
     // runs may come on any stream: wait for the buckets (set_bounds does)
     if (q->replan) {
         sam_status st2 = set_bounds(q, s);
@@ -558,13 +575,8 @@ sam_status sam_sequence_destroy(sam_seq* q) {
         (void)hipSetDevice(q->ctx->device);
         (void)hipDeviceSynchronize();
     }
-    drop_graph(q);
-    while (!q->retired.empty()) drop_oldest(q);
-    if (q->cap) (void)hipStreamDestroy(q->cap);
-    for (hipStream_t x : q->side)
-        if (x) (void)hipStreamDestroy(x);
-    for (hipEvent_t e : q->ev)
-        if (e) (void)hipEventDestroy(e);
+    for (sam_seq::Captured& c : q->graphs) drop_captured(&c);
+    drop_branches(&q->own);
     delete q->plan;   // host record: its arrays live in the sequence memory
     delete q;
     return SAM_OK;
@@ -615,7 +627,8 @@ sam_status sam_sequence_select(sam_seq* q, const int32_t* order, int32_t count, 
     HIP_TRY(ctx, settle(q, S(stream)));
     if ((st = plan_select(q->plan, q->prec, vars, S(stream)))) return st;
     if (q->replan && (st = set_bounds(q, S(stream)))) return st;
-    drop_graph(q);  // the next run captures the new launches
+    ++q->selection;   // earlier graphs hold the launches of other classes
+    q->seen.clear();
     return SAM_OK;
 }
 
@@ -641,28 +654,34 @@ sam_status sam_sequence_run(sam_seq* q, const double* const* Ak_vals, void* cons
         key.push_back(M_vals[k]);
     }
     key.push_back(res2);
-    if (!q->exec || key != q->key) {
-        HIP_TRY(ctx, retire_graph(q, S(stream)));
-        HIP_TRY(ctx, hipStreamBeginCapture(q->cap, hipStreamCaptureModeThreadLocal));
-        st = enqueue_run(q, Ak_vals, M_vals, res2, q->cap);
-        hipGraph_t g = nullptr;
-        hipError_t e = hipStreamEndCapture(q->cap, &g);
-        if (st) {
-            if (g) (void)hipGraphDestroy(g);
-            return st;
+    hipStream_t s = S(stream);
+    auto captured = [&]() -> const sam_seq::Captured* {
+        for (const sam_seq::Captured& c : q->graphs)
+            if (c.selection == q->selection && c.key == key) return &c;
+        return nullptr;
+    };
+    // a caller's capture takes the launches themselves (so does a stream that
+    // cannot say: the launches then report why)
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const bool eager = hipStreamIsCapturing(s, &status) == hipSuccess && status == hipStreamCaptureStatusNone;
+    const sam_seq::Captured* c = eager ? captured() : nullptr;
+    if (eager && !c) {
+        auto it = std::find_if(q->seen.begin(), q->seen.end(), [&](const auto& x) { return x.first == key; });
+        if (it == q->seen.end()) {
+            if (q->seen.size() == kGraphs) q->seen.erase(q->seen.begin());
+            it = q->seen.insert(q->seen.end(), {key, 0});
         }
-        if (e != hipSuccess) return fail(ctx, SAM_ERR_HIP, "graph capture: %s", hipGetErrorString(e));
-        q->graph = g;
-        e = hipGraphInstantiate(&q->exec, q->graph, nullptr, nullptr, 0);
-        if (e != hipSuccess) {
-            drop_graph(q);
-            return fail(ctx, SAM_ERR_HIP, "graph instantiate: %s", hipGetErrorString(e));
+        it->second = std::min(it->second + 1, kDirect + 1);
+        if (it->second > kDirect && q->graphs.size() < kGraphs) {
+            if ((st = capture_run(q, key, Ak_vals, M_vals, res2))) return st;
+            q->seen.erase(it);
+            c = captured();
         }
-        q->key = key;
     }
-    HIP_TRY(ctx, hipGraphLaunch(q->exec, S(stream)));
+    if (c) HIP_TRY(ctx, hipGraphLaunch(c->exec, s));
+    else if ((st = enqueue_run(q, Ak_vals, M_vals, res2, q->own, s))) return st;
     q->running = true;
-    q->last = S(stream);
+    q->last = s;
     return SAM_OK;
 }
 

@@ -388,7 +388,7 @@ class Plan:
 
 
 class Sequence:
-    """sam_seq: maps A_1..A_N to A_0 with one graph launch per run."""
+    """sam_seq: maps A_1..A_N to A_0; runs whose tensors keep coming are one graph launch."""
 
     def __init__(self, ctx: Context, A0: DeviceCSC, Ak_struct: DeviceCSC, n_src: int, prec: int,
                  spec: C.sam_pattern_spec, replan_each_run: bool):

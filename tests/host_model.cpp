@@ -19,6 +19,7 @@ namespace {
 
 using Op = std::function<void()>;
 int g_errors = 0;
+int g_graph_launches = 0;
 
 void wrong(const char* what, long a = 0, long b = 0) {
     if (++g_errors <= 10) printf("WRONG: %s (%ld, %ld)\n", what, a, b);
@@ -26,6 +27,7 @@ void wrong(const char* what, long a = 0, long b = 0) {
 
 struct Stream {
     std::deque<Op> ops;
+    int captures = 0;
 };
 struct Graph {
     std::vector<Op> ops;
@@ -36,7 +38,7 @@ struct Exec {
 };
 struct Event {
     Stream* on = nullptr;
-    int pending = 0;
+    int recorded = 0, reached = 0, captures = 0;
 };
 std::set<Stream*> g_streams;
 Stream g_null;
@@ -46,6 +48,11 @@ Stream* of(hipStream_t s) { return s ? (Stream*)s : &g_null; }
 hipError_t enqueue(hipStream_t s, Op op) {
     if (g_capture) g_capture->ops.push_back(std::move(op));
     else of(s)->ops.push_back(std::move(op));
+    return hipSuccess;
+}
+// Streams and events are captured with once in the library.
+hipError_t note_capture(int* captures) {
+    if (++*captures > 1) wrong("captured with twice");
     return hipSuccess;
 }
 void drain(Stream* s) {
@@ -98,38 +105,46 @@ hipError_t hipStreamDestroy(hipStream_t s) {
     delete (Stream*)s;
     return hipSuccess;
 }
-// inside a capture, events add nothing: the order of the calls is an order of
-// the graph
+// Inside a capture, events add nothing: the order of the calls is an order of
+// the graph.  Elsewhere a wait is for the last record before it: whoever runs it
+// runs the recorded stream up to there first.
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
     *e = (hipEvent_t) new Event;
     return hipSuccess;
 }
 hipError_t hipEventDestroy(hipEvent_t e) {
-    if (((Event*)e)->pending) wrong("event destroyed before it is reached");
-    else delete (Event*)e;
+    auto* x = (Event*)e;
+    if (x->reached != x->recorded) wrong("event destroyed before it is reached");
+    else delete x;
     return hipSuccess;
 }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
-    if (g_capture) return hipSuccess;
     auto* x = (Event*)e;
+    if (g_capture) return note_capture(&x->captures);
     x->on = of(s);
-    ++x->pending;
-    return enqueue(s, [x] { --x->pending; });
+    const int at = ++x->recorded;
+    return enqueue(s, [x, at] { x->reached = at; });
 }
-hipError_t hipEventQuery(hipEvent_t e) { return ((Event*)e)->pending ? hipErrorNotReady : hipSuccess; }
-hipError_t hipEventSynchronize(hipEvent_t e) {
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
     auto* x = (Event*)e;
-    while (x->pending) {
-        Op op = std::move(x->on->ops.front());
-        x->on->ops.pop_front();
-        op();
-    }
+    if (g_capture) return hipSuccess;
+    const int at = x->recorded;
+    Stream* on = x->on;
+    return enqueue(s, [x, at, on] {
+        while (x->reached < at) {
+            Op op = std::move(on->ops.front());
+            on->ops.pop_front();
+            op();
+        }
+    });
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) {
+    *st = hipStreamCaptureStatusNone;
     return hipSuccess;
 }
-hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
-hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) {
+hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) {
     g_capture = new Graph;
-    return hipSuccess;
+    return note_capture(&of(s)->captures);
 }
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
     *g = (hipGraph_t)g_capture;
@@ -144,6 +159,7 @@ hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t g, hipGraphNode_t*,
 }
 hipError_t hipGraphLaunch(hipGraphExec_t e, hipStream_t s) {
     auto* x = (Exec*)e;
+    ++g_graph_launches;
     for (const Op& op : x->ops) (void)enqueue(s, op);
     ++x->in_flight;
     return enqueue(s, [x] { --x->in_flight; });
@@ -530,32 +546,62 @@ int main(int argc, char** argv) {
                 served(q.N, "columns of a run");
                 ++done;
             }
-    } else if (what == "outputs") {   // new outputs while the last runs are still on their way
+    } else if (what == "outputs") {   // other outputs while the last runs are still on their way
         for (hipStream_t second : {s, other}) {
             Seq q(ctx, 6, 4, SAM_SPARSIFY_COLUMN, 2, 1, s);
             clear(q.A.n);
-            q.run(0, s);
+            for (int k = 0; k < 7; ++k) q.run(0, s);   // some of them a graph's
             const bool waited = of(s)->ops.empty();
+            if (second != s) (void)hipStreamSynchronize(s);   // runs of one sequence do not overlap
             q.run(1, second);
             if (second == s && (waited || of(s)->ops.empty())) wrong("a run waited for another on its stream");
             for (int k = 0; k < 9; ++k) q.run(k & 1, second);
             (void)hipDeviceSynchronize();
-            served(11 * q.N, "columns of the runs");
+            served(17 * q.N, "columns of the runs");
+            ++done;
+        }
+    } else if (what == "graphs") {   // which runs a graph takes
+        for (int replan : {0, 1}) {
+            Seq q(ctx, 5, 3, SAM_SPARSIFY_NONE, 2, replan, s);
+            const int32_t wide[] = {3};
+            auto runs = [&](int which, int k, int graph, const char* what) {
+                const int before = g_graph_launches;
+                clear(q.A.n);
+                for (int i = 0; i < k; ++i) q.run(which, s);
+                (void)hipStreamSynchronize(s);
+                served(k * q.N, "columns of the runs");
+                if (g_graph_launches - before != graph) wrong(what, g_graph_launches - before, graph);
+            };
+            runs(0, 7, 3, "the fifth run is captured");
+            runs(1, 2, 0, "other outputs are not, at first");
+            for (int i = 0; i < 2; ++i) {   // alternating outputs
+                runs(0, 1, 1, "the first come back to their graph");
+                runs(1, 1, 0, "outputs that came fewer than five times");
+            }
+            runs(1, 3, 3, "the fifth time");
+            ok(sam_sequence_select(q.seq, wide, 1, s), ctx, "select");
+            runs(0, 4, 0, "a graph of other classes is not launched");
+            runs(0, 2, 2, "the new classes get one of their own");
+            for (int i = 0; i < 5; ++i) {
+                ok(sam_sequence_select(q.seq, wide, 1, s), ctx, "select");
+                runs(0, 6, i == 0 ? 2 : 0, "four graphs at most");
+            }
             ++done;
         }
     } else if (what == "select") {   // other classes while the last run is still on its way on another stream
-        for (int replan : {0, 1}) {
-            Seq q(ctx, 6, 4, SAM_SPARSIFY_NONE, 2, replan, s);
-            const int32_t wide[] = {3}, many[] = {0, 1, 2, 3};
-            ok(sam_sequence_select(q.seq, many, 4, s), ctx, "select");
-            clear(q.A.n);
-            q.run(0, s);
-            ok(sam_sequence_select(q.seq, wide, 1, other), ctx, "select");
-            q.run(0, other);
-            (void)hipDeviceSynchronize();
-            served(2 * q.N, "columns of two runs");
-            ++done;
-        }
+        for (int replan : {0, 1})
+            for (int before : {1, 6}) {   // runs, the last by a graph or not
+                Seq q(ctx, 6, 4, SAM_SPARSIFY_NONE, 2, replan, s);
+                const int32_t wide[] = {3}, many[] = {0, 1, 2, 3};
+                ok(sam_sequence_select(q.seq, many, 4, s), ctx, "select");
+                clear(q.A.n);
+                for (int k = 0; k < before; ++k) q.run(0, s);
+                ok(sam_sequence_select(q.seq, wide, 1, other), ctx, "select");
+                q.run(0, other);
+                (void)hipDeviceSynchronize();
+                served((before + 1) * q.N, "columns of the runs");
+                ++done;
+            }
     } else if (what == "orders") {   // every kind of order, good and refused, runs between them
         std::mt19937 rng(argc > 2 ? (unsigned)atoi(argv[2]) : 0);
         auto pick = [&](int k) { return (int)(rng() % (unsigned)k); };
@@ -573,9 +619,9 @@ int main(int argc, char** argv) {
                 if (pick(3) == 0) continue;
                 (void)hipDeviceSynchronize();
                 clear(q.A.n);
-                const int runs = 1 + pick(2);
+                const int runs = 1 + pick(8);
                 const hipStream_t on = pick(2) ? s : other;
-                for (int k = 0; k < runs; ++k) q.run(pick(2), on);
+                for (int k = 0, which = pick(2); k < runs; ++k) q.run(pick(4) ? which : 1 - which, on);
                 (void)hipDeviceSynchronize();
                 served(runs * q.N, "columns of a selected run");
             }

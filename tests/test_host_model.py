@@ -45,6 +45,13 @@ def test_sequence_changed_while_it_runs(model, changed):
     check(model, changed)
 
 
+def test_which_runs_a_graph_takes(model):
+    """The fifth run in a row with the same pointers is captured, four graphs at
+    most, none of them after its classes have changed, and no stream or event is
+    captured with twice."""
+    check(model, "graphs")
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_sequence_orders(model, seed):
     """Selections, refused ones among them, between runs on two streams with
