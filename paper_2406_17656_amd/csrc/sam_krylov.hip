@@ -5,8 +5,9 @@
 //
 // The orthogonalisation is classical Gram-Schmidt taken twice: all dot
 // products of a pass in one kernel, all updates in the next, so a step is four
-// launches whatever k is (modified Gram-Schmidt needs a reduction over the
-// whole vector per earlier vector), and the basis is orthogonal to rounding.
+// launches whatever k is, six beyond kInlineChunks chunks (modified Gram-Schmidt
+// needs a reduction over the whole vector per earlier vector), and the basis is
+// orthogonal to rounding.
 //
 // A chunk of rows per block of 16 waves: the block that forms w (or subtracts a
 // pass) goes straight on to its chunk's share of the next dot products.  The
@@ -37,8 +38,11 @@ static_assert(kParts == kSpmvLanes, "k_gm_apply_dots gives a row of its product 
 constexpr int kRowWaves = kRows / 64;
 constexpr int kFlat = 256;          // threads per block of the kernels without chunks
 constexpr int kTile = 8;            // basis vectors whose loads are in flight together
-// up to here every block sums the chunks' partials itself (one load per lane
-// and product; a launch of its own costs about 3 us twice a step)
+// Up to here every block sums the chunks' partials itself, one load per lane
+// and product; beyond it a launch does, twice a step.  Microseconds per step of a
+// cycle of 50, every block against a launch: 33.0 / 35.8 at 64 chunks (n = 16384),
+// 34.1 / 36.4 at 67, 35.5 / 37.3 at 128, 38.5 / 38.7 at 256 and 55.4 / 53.0 at 512
+// (the blocks' reads grow with the square of the chunks).
 constexpr int kInlineChunks = 64;
 constexpr int kMaxChunks = 1024;
 

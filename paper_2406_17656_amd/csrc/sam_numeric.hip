@@ -157,7 +157,7 @@ k_numeric(NumericArgs a) {
     __shared__ int mta[P][9];             // next group: valid, j, scol, nJ, nIj, eo (2), a0, a1
     __shared__ double alsh[BACKWARD ? P * RS : 1];  // A lambda (adjoint)
     __shared__ double racc;               // the block's running sum of column residuals
-    __shared__ double out_sh[TIGHT ? P : 1];   // out_j across the QR (see `again`)
+    __shared__ double out_sh[TIGHT ? P : 1];   // out_j across the QR (in no register there)
     __shared__ int long_sh;
     __shared__ double pen_sh[WEIGHTED ? P * NC : 1];  // penalties p_c of the group's problems
     // The weighted and adjoint forms keep their length-NC FP64 vectors (m,
