@@ -10,11 +10,12 @@ import pde_inputs as P
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("kind,replan", [("none", False), ("none", True), ("global", True)])
-@pytest.mark.parametrize("side", [False, True])
-def test_runs_agree(kind, replan, side):
+@pytest.mark.parametrize("side,m,kind,replan", [
+    (side, 20, kind, replan) for side in (False, True)
+    for kind, replan in (("none", False), ("none", True), ("global", True))] + [(False, 512, "none", True)])
+def test_runs_agree(side, m, kind, replan):
     from paper_2406_17656_amd import Context, DeviceCSC
-    A0h, Ash = P.config4(m=20, nmat=6)
+    A0h, Ash = P.config4(m=m, nmat=6)
     kw = dict(kind="global", thresh=0.1) if kind == "global" else {}
     ctx = Context(0)
     A0, As = DeviceCSC.from_host(A0h), [DeviceCSC.from_host(A) for A in Ash]
