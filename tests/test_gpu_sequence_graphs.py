@@ -47,3 +47,39 @@ def test_runs_agree(side, m, kind, replan):
     ctx.sync_status()
     seq.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("replan", [False, True])
+def test_callers_capture(replan):
+    """A run inside the caller's own capture: its replays give the eager run's maps."""
+    from paper_2406_17656_amd import Context, DeviceCSC
+    A0h, Ash = P.config4(m=20, nmat=5)
+    ctx = Context(0)
+    A0, As = DeviceCSC.from_host(A0h), [DeviceCSC.from_host(A) for A in Ash]
+    vals = [A.val for A in As]
+    seq = ctx.sequence(A0, As[0], len(As), prec="f64", power=2, replan_each_run=replan)
+    Ms, res2 = seq.alloc_maps(), torch.empty(len(As), dtype=torch.float64, device="cuda")
+    seq.run(vals, Ms, res2)
+    want = [M.clone() for M in Ms] + [res2.clone()]
+    ctx.sync_status()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        seq.run(vals, Ms, res2)
+    junk = torch.randn(1 << 16, device="cuda")
+    for i in range(5):
+        for M in Ms:
+            M.zero_()
+        junk = junk * 1.0001 + 1.0
+        g.replay()
+        if i % 2:
+            torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(want, Ms + [res2])), i
+    for i in range(6):       # and the sequence's own graph, beside it
+        res2.zero_()
+        seq.run(vals, Ms, res2)
+        assert all(torch.equal(a, b) for a, b in zip(want, Ms + [res2])), i
+    ctx.sync_status()
+    torch.cuda.synchronize()
+    del g
+    seq.close()
+    ctx.close()
